@@ -242,10 +242,18 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                 stages.push_back(group_res32(gb, cs));
                 stages.push_back(group_finish(gb, cs));
                 stages.push_back(group_update(gb, cs));
-                for (int k = 0; k < cx[act[0]].P->opt.inner; ++k) {
-                    for (int l = 0; l < maxL; ++l) stages.push_back(group_march32(gb, cs, l, false, k == 0));
+                const int inner = cx[act[0]].P->opt.inner;
+                for (int k = 0; k < inner; ++k) {
+                    // each level's problems: those of the pair march, then the strip kernels'
+                    for (int l = 0; l < maxL; ++l) {
+                        stages.push_back(group_pair32(gb, cs, l, true, k, inner));
+                        stages.push_back(group_march32(gb, cs, l, false, k == 0));
+                    }
                     stages.push_back(group_lds32(gb, cs));
-                    for (int l = maxL - 1; l >= 0; --l) stages.push_back(group_march32(gb, cs, l, true, false));
+                    for (int l = maxL - 1; l >= 0; --l) {
+                        stages.push_back(group_pair32(gb, cs, l, false, k, inner));
+                        stages.push_back(group_march32(gb, cs, l, true, false));
+                    }
                 }
                 stages.push_back(group_addcorr(gb, cs));
                 if (gb.host.size() > table_bytes) {
@@ -274,6 +282,7 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                 for (int it = 0; it < cur.chunk; ++it)
                     for (const GStage& g : stages) {
                         if (g.kind == G_PRE32 || g.kind == G_POST32) group_launch_march(g, dev, st[0]);
+                        else if (g.kind >= G_PAIR_PRE) group_launch_pair(g, dev, st[0]);
                         else group_launch_mg(g, dev, st[0]);
                     }
                 for (int i : act) cx[i].cycles += cur.chunk;

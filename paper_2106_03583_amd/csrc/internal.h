@@ -98,6 +98,12 @@ struct BusyFlag {
     bool held() const { return v.load(); }
 };
 
+// One strip list of the pair march: strips [off, off + cnt) of the plan's
+// list, at most `rows` rows each.
+struct PairSet {
+    int off = 0, cnt = 0, rows = 0;
+};
+
 struct FFTPlan {
     int n = 0, m = 0;              // real length, complex length n/2
     std::vector<int> radices;      // Stockham stages, product = m
@@ -134,7 +140,10 @@ struct mbp_plan {
     std::vector<char> use_rmarch;           // level runs its pre-smoothing as a register march
     int wg_target = 256 * 3;               // strip-form launches: workgroups aimed at
     std::vector<char> march_ok;   // level runs the fused one-pass sweeps
+    std::vector<char> pair_ok;    // level runs the pair march instead
+    std::vector<std::vector<mbp::PairSet>> pair_sets;  // its strip lists, by rows a strip
     void* d_mtiles = nullptr;
+    void* d_ptiles = nullptr;
     size_t mtile_bytes = 0;
     // host tables (uploaded into one device allocation)
     std::vector<mbp::DBlock> hblk;
@@ -233,17 +242,37 @@ size_t resnorm_scratch_doubles(const mbp_plan* P);
 void launch_resnorm3d(const mbp_plan* P, const double* f, const double* p, double shift, double* part,
                       double* out, hipStream_t s);
 
-// One V-cycle on every active mode.  p0 / f0: finest-level iterate and rhs;
-// p0B: second finest buffer for the out-of-place sweeps (the result is
-// always left in p0).  With norm0 the finest post-smoothing sweep also
-// produces per-strip squared residuals; returns the partial count then (0 if
-// the caller must evaluate the residual itself).  zero0: p0 holds zeros
-// (the first cycle), so the fused finest sweeps need not read it.
+// One V-cycle on every active mode.  With norm the finest level also leaves
+// per-strip squared residuals; launch_vcycle returns their count (0 if the
+// caller must evaluate the residual itself).
 template <typename T>
-int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const int* nact,
-                  int nitems, bool norm0, bool zero0, hipStream_t s);
-void launch_finish(const mbp_plan* P, int nparts, double* out, const int* act, const int* nact,
+struct VcycleArgs {
+    T* p;              // finest iterate
+    T* pB;             // second finest buffer of the out-of-place sweeps
+    T* f;              // finest rhs
+    const int* act;
+    const int* nact;
+    int nitems;
+    // The strip kernels leave the result in p.  The pair march writes it to
+    // the other buffer: flipped is set, or, with cycle (the device count of
+    // convergence tests), the buffers alternate by its parity: a mode that
+    // took c V-cycles lies in p for even c, in pB for odd c, and the partial
+    // count is on the device as well.
+    const int* cycle = nullptr;
+    bool norm = false;
+    bool zero = false;   // p holds zeros (the first cycle) and need not be read
+    bool last = false;   // no V-cycle from the result follows
+    bool ready = false;  // in / out: the next level's rhs already holds the restricted
+                         // residual of the pre-smoothed p (the pair march leaves it there)
+    bool flipped = false;  // out
+};
+template <typename T>
+int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s);
+// dyn (optional): device count of the partials, read instead of nparts
+void launch_finish(const mbp_plan* P, int nparts, const int* dyn, double* out, const int* act, const int* nact,
                    int nitems, hipStream_t s);
+// Copy the planes of the modes that took an odd number of V-cycles from pB to p.
+void launch_take_odd(const mbp_plan* P, double* p, const double* pB, hipStream_t s);
 // Whole solve of every mode for plans whose hierarchy fits in LDS.
 void launch_lds_full(const mbp_plan* P, double* p, const double* f, const int* act, const int* nact,
                      int nitems, int maxc, double rtol2, double etol2, int* cyc, double* rnorm,
@@ -267,6 +296,19 @@ void march_sweep(const mbp_plan* P, int l, const T* pold, T* pnew, const T* f, c
                  const int* nact, int nitems, bool zero_in, hipStream_t s);
 template <typename T>
 void march_post(const mbp_plan* P, int l, const T* pold, T* pnew, const T* f, const T* ec, bool norm,
+                const int* act, const int* nact, int nitems, hipStream_t s);
+// pair.hip
+bool pair_level_ok(const mbp_plan* P, int l);
+void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes, std::vector<PairSet>& sets);
+int pair_max_strips(const mbp_plan* P, int l);
+template <typename T>
+void pair_pre(const mbp_plan* P, int l, const T* p, const T* f, T* fc, const int* act, const int* nact, int nitems,
+              hipStream_t s);
+template <typename T>
+void pair_post(const mbp_plan* P, int l, const T* p, T* pnew, const T* f, const T* ec, const int* act, const int* nact,
+               int nitems, hipStream_t s);
+template <typename T>
+void pair_cycle(const mbp_plan* P, int l, T* pa, T* pb, const int* cycle, const T* f, const T* ec, T* fc, bool zero,
                 const int* act, const int* nact, int nitems, hipStream_t s);
 void launch_residual_norm(const mbp_plan* P, const double* p, const double* f, double* rnorm,
                           const int* act, const int* nact, int nitems, hipStream_t s);
@@ -310,6 +352,8 @@ struct SolveCtx {
     int status = 0;
     double removed = 0.0;
     int nitems = 0;       // host upper bound on the active modes (grid sizes)
+    bool flip = false;    // the finest iterate alternates between phat and phatB (pair march)
+    bool ready = false;   // VcycleArgs::ready of the next V-cycle
     int fused_parts = 0;  // partials left by the last V-cycle (0: explicit residual)
     int cycles = 0;       // V-cycles launched so far
     bool done = false;
@@ -334,7 +378,10 @@ int plan_autotune(mbp_plan* P, const double* rhs, hipStream_t s, mbp_tuning* out
 struct GEnt {
     int wg0, gx, job, pad;
 };
-enum GKind { G_RES32 = 0, G_FINISH, G_UPDATE, G_PRE32, G_LDS32, G_POST32, G_ADDCORR };
+enum GKind {
+    G_RES32 = 0, G_FINISH, G_UPDATE, G_PRE32, G_LDS32, G_POST32, G_ADDCORR,
+    G_PAIR_PRE, G_PAIR_POST0, G_PAIR_POST, G_PAIR_CYCLE0, G_PAIR_CYCLE  // (0: from a zero iterate)
+};
 struct GStage {
     int kind = 0;
     int wgs = 0;            // workgroups of the launch
@@ -414,5 +461,8 @@ GStage group_march32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level,
 // ... and their launches from the uploaded image (phase 2, capturable).
 void group_launch_mg(const GStage& st, const unsigned char* dev, hipStream_t s);
 void group_launch_march(const GStage& st, const unsigned char* dev, hipStream_t s);
+// The pair-march levels of inner cycle k of `inner`: on the way down (down) or up.
+GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, bool down, int k, int inner);
+void group_launch_pair(const GStage& st, const unsigned char* dev, hipStream_t s);
 
 }  // namespace mbp

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "wave.h"
 
 namespace mbp {
 
@@ -81,43 +82,6 @@ constexpr int kWaveCoarse = 6;              // coarse rows of the correction sta
 static_assert(kLdsRows % 4 == 0, "four waves share the strip rows");
 static_assert(2 * (kWaveCoarse - 2) + 1 >= kRowsPerWave, "a wave's rows fit its coarse rows");
 
-// Sum over the 64 lanes of a wave with DPP moves (no LDS round trips);
-// lane 63 ends up with the total.
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
-// a / d by a hardware reciprocal refined with Newton-Raphson steps and one
-// residual correction of the quotient (d is a nonzero diagonal of moderate
-// magnitude here; within an ulp or two of the rounded quotient).
-__device__ __forceinline__ double div_nr(double a, double d) {
-    double r = __builtin_amdgcn_rcp(d);
-    double e = fma(-d, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-d, r, 1.0);
-    r = fma(r, e, r);
-    const double q = a * r;
-    return fma(fma(-d, q, a), r, q);
-}
-__device__ __forceinline__ float div_nr(float a, float d) {
-    float r = __builtin_amdgcn_rcpf(d);
-    r = fmaf(r, fmaf(-d, r, 1.0f), r);
-    const float q = a * r;
-    return fmaf(fmaf(-d, q, a), r, q);
-}
-
-__device__ __forceinline__ double wave_sum63(double v) {
-    v += dpp_move<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);   // quad_perm [2,3,0,1]: every lane holds its quad's sum
-    v += dpp_move<0x114>(v);  // row_shr:4
-    v += dpp_move<0x118>(v);  // row_shr:8: lane 15 of each row holds the row's sum
-    v += dpp_move<0x142>(v);  // row_bcast:15
-    v += dpp_move<0x143>(v);  // row_bcast:31
-    return v;
-}
 constexpr int kNoRow = -1000000;            // row table: not a row of the strip's own block
 
 // Offset and sign of coarse value (I, J) of block b, one cell beyond a face
@@ -714,22 +678,6 @@ k_tile_group(const GEnt* __restrict__ e, int n, const MArgs<float>* __restrict__
 // for every lane (joined blocks are congruent along their common faces).
 constexpr int kRing = 8;
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_shift(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-// value of lane - 1 (0 at lane 0) and of lane + 1 (0 at lane 63)
-template <typename T>
-__device__ __forceinline__ T from_left(T v) { return dpp_shift<0x138>(v); }
-template <typename T>
-__device__ __forceinline__ T from_right(T v) { return dpp_shift<0x130>(v); }
-
 template <typename T, bool RES, bool NRM>
 __global__ void __launch_bounds__(256) k_rmarch(const MArgs<T> args, const double* __restrict__ dp) {
     // dp: the coefficient pool, passed on its own so that uniform row
@@ -1203,7 +1151,7 @@ bool group_ok(const SolveCtx& c) {
     const mbp_plan* P = c.P;
     if (!c.mixed || c.full_lds || P->opt.nu1 != 1 || P->opt.nu2 != 1) return false;
     for (int l = 0; l < P->lds_level32; ++l)
-        if (!P->march_ok[l] || P->use_rmarch[l] || P->p32B[l] == nullptr) return false;
+        if (!P->pair_ok[l] && (!P->march_ok[l] || P->use_rmarch[l] || P->p32B[l] == nullptr)) return false;
     return true;
 }
 
@@ -1218,10 +1166,10 @@ GStage group_march32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level,
     // chip, so each can reuse its strip set-up for more modes than alone
     double total = 0.0;
     for (const SolveCtx* c : cs)
-        if (level < c->P->lds_level32) total += double(c->P->mtile_cnt[level]) * c->nitems;
+        if (level < c->P->lds_level32 && !c->P->pair_ok[level]) total += double(c->P->mtile_cnt[level]) * c->nitems;
     for (const SolveCtx* c : cs) {
         const mbp_plan* P = c->P;
-        if (level >= P->lds_level32) continue;
+        if (level >= P->lds_level32 || P->pair_ok[level]) continue;
         const int l = level;
         MArgs<float> a = post ? margs<float>(P, l, P->p32B[l], P->p32[l], P->f32[l], P->p32[l + 1], nullptr,
                                              nullptr, P->d_act, P->d_nact)

@@ -402,13 +402,14 @@ struct FinJob {
     const int* nact;
     double* out;
     double* out2;
+    const int* dyn = nullptr;  // device count of the partials (optional, instead of ntiles)
 };
 
 __device__ __forceinline__ void finish_body(const FinJob& J, int item) {
     __shared__ double scratch[8];
     if (J.act && item >= *J.nact) return;
     const int q = J.act ? J.act[item] : item;
-    const int ntiles = J.ntiles;
+    const int ntiles = J.dyn ? *J.dyn : J.ntiles;
     double acc = 0.0, acc2 = 0.0;
     for (int t = threadIdx.x; t < ntiles; t += blockDim.x) {
         acc += J.part[2 * ((long long)q * ntiles + t)];
@@ -580,6 +581,29 @@ __global__ void k_zero_unrelaxed(double* __restrict__ p, long long plane, const 
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < plane;
          i += (long long)gridDim.x * blockDim.x)
         pq[i] = 0.0;
+}
+
+// Zero the planes of the active modes.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_zero_active(T* __restrict__ p, long long plane, const int* __restrict__ act, const int* __restrict__ nact) {
+    if (int(blockIdx.y) >= *nact) return;
+    T* pq = p + act[blockIdx.y] * plane;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < plane;
+         i += (long long)gridDim.x * blockDim.x)
+        pq[i] = T(0);
+}
+
+// Planes of the modes that took an odd number of V-cycles: from pB to p.
+__global__ void __launch_bounds__(256)
+k_take_odd(double* __restrict__ p, const double* __restrict__ pB, long long plane, const int* __restrict__ cyc) {
+    const int q = blockIdx.y;
+    if (!(cyc[q] & 1)) return;
+    const double2* s = reinterpret_cast<const double2*>(pB + q * plane);  // even planes only (pair march)
+    double2* d = reinterpret_cast<double2*>(p + q * plane);
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < plane / 2;
+         i += (long long)gridDim.x * blockDim.x)
+        d[i] = s[i];
 }
 
 // sum(a x) over one plane (single workgroup, fixed order).
@@ -1187,17 +1211,23 @@ template <>
 float* level_pB<float>(const mbp_plan* P, int l) { return P->p32B[l]; }
 
 template <typename T>
-int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const int* nact, int nitems,
-                  bool norm0, bool zero0, hipStream_t s) {
+int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s) {
     const bool is32 = sizeof(T) == 4;
     const int L = is32 ? P->lds_level32 : P->lds_level;
     const dim3 blk(kTileX, kRowsPerPass);
     const int nu1 = P->opt.nu1, nu2 = P->opt.nu2;
+    const int *act = v.act, *nact = v.nact;
+    const int nitems = v.nitems;
     const bool fused_ok = ((nu1 + nu2) % 2 == 0) && nu1 >= 1 && nu2 >= 1;
-    auto P_ = [&](int l) -> T* { return l == 0 ? p0 : level_p<T>(P, l); };
-    auto PB_ = [&](int l) -> T* { return l == 0 ? p0B : level_pB<T>(P, l); };
-    auto F_ = [&](int l) -> T* { return l == 0 ? f0 : level_f<T>(P, l); };
-    auto use_march = [&](int l) __attribute__((always_inline)) { return fused_ok && P->march_ok[l] && PB_(l) != nullptr; };
+    auto P_ = [&](int l) -> T* { return l == 0 ? v.p : level_p<T>(P, l); };
+    auto PB_ = [&](int l) -> T* { return l == 0 ? v.pB : level_pB<T>(P, l); };
+    auto F_ = [&](int l) -> T* { return l == 0 ? v.f : level_f<T>(P, l); };
+    auto use_pair = [&](int l) { return P->pair_ok[l] != 0; };
+    auto use_march = [&](int l) __attribute__((always_inline)) {
+        return !use_pair(l) && fused_ok && P->march_ok[l] && PB_(l) != nullptr;
+    };
+    // the next level's initial guess: zeros are written only where it is read
+    auto guess = [&](int l) -> T* { return (l < L && !use_pair(l) && !use_march(l)) ? P_(l) : nullptr; };
     auto rbgs = [&](int l) __attribute__((always_inline)) {
         const Level& Lf = P->levels[l];
         for (int colour = 0; colour < (Lf.oddwrap ? 4 : 2); ++colour)
@@ -1205,14 +1235,20 @@ int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const
                                P->d_tiles + Lf.tile_off, Lf.ntiles, P->d_dbl, P_(l), F_(l),
                                (long long)Lf.plane, P->d_shift, act, nact, colour);
     };
+    v.flipped = false;
     for (int l = 0; l < L; ++l) {
         const Level& Lf = P->levels[l];
         const Level& Lc = P->levels[l + 1];
-        if (use_march(l)) {
+        if (use_pair(l)) {
+            // the finest level's cycle form has already restricted for this cycle
+            if (l == 0 && v.ready) continue;
+            if (l == 0) prof_begin(P, 0, s, double(Lf.plane) * nitems);
+            pair_pre<T>(P, l, l == 0 && !v.zero ? v.p : nullptr, F_(l), F_(l + 1), act, nact, nitems, s);
+            if (l == 0) prof_end(P, 0, s);
+        } else if (use_march(l)) {
             // sweeps alternate A -> B -> A ...; the restricting sweep ends in B.
-            // Coarse levels start from zero, so their first sweep reads no p;
-            // the next level needs zeros written only if it reads its guess.
-            bool zin = l == 0 ? zero0 : true;
+            // Coarse levels start from zero, so their first sweep reads no p.
+            bool zin = l == 0 ? v.zero : true;
             T* a = P_(l);
             T* b = PB_(l);
             for (int it = 0; it + 1 < nu1; ++it) {
@@ -1220,11 +1256,15 @@ int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const
                 zin = false;
                 std::swap(a, b);
             }
-            T* pc = (l + 1 < L && !use_march(l + 1)) ? P_(l + 1) : nullptr;
             if (l == 0) prof_begin(P, 0, s, double(Lf.plane) * nitems);
-            march_pre<T>(P, l, a, b, F_(l), F_(l + 1), pc, act, nact, nitems, zin, s);
+            march_pre<T>(P, l, a, b, F_(l), F_(l + 1), guess(l + 1), act, nact, nitems, zin, s);
             if (l == 0) prof_end(P, 0, s);
         } else {
+            // below a pair level nobody has zeroed the guess this level reads
+            // (the cycle form still reads it as the correction of the last cycle)
+            if (l > 0 && use_pair(l - 1))
+                hipLaunchKernelGGL(k_zero_active<T>, dim3(int(std::min<int64_t>(64, (Lf.plane + 255) / 256)), nitems),
+                                   dim3(256), 0, s, P_(l), (long long)Lf.plane, act, nact);
             for (int it = 0; it < nu1; ++it) rbgs(l);
             hipLaunchKernelGGL(k_restrict<T>, dim3(Lc.ntiles, nitems), blk, 0, s, P->d_blk + Lf.blk_off,
                                P->d_blk + Lc.blk_off, P->d_tiles + Lc.tile_off, Lc.ntiles, P->d_dbl,
@@ -1244,22 +1284,33 @@ int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const
     for (int l = L - 1; l >= 0; --l) {
         const Level& Lf = P->levels[l];
         const Level& Lc = P->levels[l + 1];
-        if (use_march(l)) {
+        if (use_pair(l)) {
+            if (l > 0) {
+                pair_post<T>(P, l, nullptr, P_(l), F_(l), P_(l + 1), act, nact, nitems, s);
+                continue;
+            }
+            prof_begin(P, 1, s, double(Lf.plane) * nitems);
+            if (v.last)
+                pair_post<T>(P, 0, v.zero ? nullptr : v.p, v.pB, v.f, P_(1), act, nact, nitems, s);
+            else
+                pair_cycle<T>(P, 0, v.p, v.pB, v.cycle, v.f, P_(1), F_(1), v.zero, act, nact, nitems, s);
+            prof_end(P, 1, s);
+            v.ready = !v.last;
+            v.flipped = true;
+            nparts = v.norm ? 1 : 0;  // the count itself is on the device
+        } else if (use_march(l)) {
             // the current iterate sits in A after nu1 - 1 swaps and one more sweep: B if nu1 odd
             T* a = P_(l);
             T* b = PB_(l);
             T* cur = (nu1 % 2 == 1) ? b : a;
             T* oth = (cur == a) ? b : a;
-            const bool nrm = norm0 && l == 0 && nu2 == 1;
+            const bool nrm = v.norm && l == 0 && nu2 == 1;
             if (l == 0) prof_begin(P, 1, s, double(Lf.plane) * nitems);
             march_post<T>(P, l, cur, oth, F_(l), P_(l + 1), nrm, act, nact, nitems, s);
             if (l == 0) prof_end(P, 1, s);
             std::swap(cur, oth);
             for (int it = 1; it < nu2; ++it) {
-                const bool last = it == nu2 - 1;
-                if (norm0 && l == 0 && last) {
-                    // extra sweeps do not carry the norm; the caller evaluates it
-                }
+                // (extra sweeps do not carry the norm; the caller evaluates it)
                 march_sweep<T>(P, l, cur, oth, F_(l), act, nact, nitems, false, s);
                 std::swap(cur, oth);
             }
@@ -1275,10 +1326,8 @@ int launch_vcycle(const mbp_plan* P, T* p0, T* p0B, T* f0, const int* act, const
     return nparts;
 }
 
-template int launch_vcycle<double>(const mbp_plan*, double*, double*, double*, const int*, const int*,
-                                   int, bool, bool, hipStream_t);
-template int launch_vcycle<float>(const mbp_plan*, float*, float*, float*, const int*, const int*, int,
-                                  bool, bool, hipStream_t);
+template int launch_vcycle<double>(const mbp_plan*, VcycleArgs<double>&, hipStream_t);
+template int launch_vcycle<float>(const mbp_plan*, VcycleArgs<float>&, hipStream_t);
 
 __global__ void k_norm_from_rhs(const double* __restrict__ fnorm, double* __restrict__ rnorm,
                                 double* __restrict__ pnorm, const int* __restrict__ act,
@@ -1295,9 +1344,9 @@ void launch_norm_from_rhs(const mbp_plan* P, int nitems, hipStream_t s) {
                        P->d_pnorm, P->d_act, P->d_nact);
 }
 
-void launch_finish(const mbp_plan* P, int nparts, double* out, const int* act, const int* nact,
+void launch_finish(const mbp_plan* P, int nparts, const int* dyn, double* out, const int* act, const int* nact,
                    int nitems, hipStream_t s) {
-    const FinJob F{P->d_part, nparts, act, nact, out, P->d_pnorm};
+    const FinJob F{P->d_part, nparts, act, nact, out, P->d_pnorm, dyn};
     hipLaunchKernelGGL(k_finish, dim3(nitems), dim3(256), 0, s, F);
 }
 
@@ -1366,6 +1415,11 @@ void launch_zero_unrelaxed(const mbp_plan* P, double* p, hipStream_t s) {
     const int chunks = int(std::min<long long>(64, (P->plane0 + 1023) / 1024));
     hipLaunchKernelGGL(k_zero_unrelaxed, dim3(chunks, P->g.nz), dim3(256), 0, s, p, (long long)P->plane0,
                        P->d_cyc);
+}
+
+void launch_take_odd(const mbp_plan* P, double* p, const double* pB, hipStream_t s) {
+    const int chunks = int(std::min<long long>(64, (P->plane0 + 2047) / 2048));
+    hipLaunchKernelGGL(k_take_odd, dim3(chunks, P->g.nz), dim3(256), 0, s, p, pB, (long long)P->plane0, P->d_cyc);
 }
 
 // The first V-cycle from a zero iterate reads no finest-level p: its first
@@ -1466,7 +1520,7 @@ __global__ void __launch_bounds__(1024) k_lds_vcycle_group(const GEnt* __restric
 float* fp32_guess_to_zero(const mbp_plan* P) {
     const int nu1 = P->opt.nu1, nu2 = P->opt.nu2;
     const bool fused_ok = ((nu1 + nu2) % 2 == 0) && nu1 >= 1 && nu2 >= 1;
-    const bool strip0 = fused_ok && P->march_ok[0] && P->p32B[0] != nullptr;
+    const bool strip0 = fused_ok && P->march_ok[0] && P->p32B[0] != nullptr;  // (and the pair march)
     return (P->lds_level32 == 0 || strip0) ? nullptr : P->p32[0];
 }
 
@@ -1525,7 +1579,9 @@ GStage group_addcorr(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     for (const SolveCtx* c : cs) {
         const mbp_plan* P = c->P;
         const Level& L = P->levels[0];
-        jobs.push_back(AddJob{P->phat, P->p32[0], (long long)L.plane, P->d_act, P->d_nact});
+        // the pair march leaves the correction of an odd cycle count in the second buffer
+        const float* e = P->lds_level32 > 0 && P->pair_ok[0] && (P->opt.inner & 1) ? P->p32B[0] : P->p32[0];
+        jobs.push_back(AddJob{P->phat, e, (long long)L.plane, P->d_act, P->d_nact});
         gx.push_back(add_chunks(L.plane));
         gy.push_back(c->nitems);
     }

@@ -19,13 +19,13 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct Layout {
-    size_t blk, ints, dbls, tiles, shift, cwl, cwr, cmu, area0, ftf, fti, mt, fhat, phat, phatB, part,
+    size_t blk, ints, dbls, tiles, shift, cwl, cwr, cmu, area0, ftf, fti, mt, pt, fhat, phat, phatB, part,
         fnorm, rnorm, pnorm, sabs, act, nact, cyc, flag, scal;
     std::vector<size_t> p64, f64, p32, f32, p64B, p32B;
     size_t total;
 };
 
-Layout layout(const mbp_plan* P, size_t ftile_bytes, size_t mtile_bytes, int nparts) {
+Layout layout(const mbp_plan* P, size_t ftile_bytes, size_t mtile_bytes, size_t ptile_bytes, int nparts) {
     Layout L{};
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -47,6 +47,7 @@ Layout layout(const mbp_plan* P, size_t ftile_bytes, size_t mtile_bytes, int npa
     L.ftf = take(ftile_bytes);
     L.fti = take(ftile_bytes);
     L.mt = take(mtile_bytes);
+    L.pt = take(ptile_bytes);
     L.fhat = take(nz * P->plane0 * sizeof(double));
     L.phat = take(nz * P->plane0 * sizeof(double));
     const bool mixed = P->opt.precision == MBP_MIXED;
@@ -60,7 +61,8 @@ Layout layout(const mbp_plan* P, size_t ftile_bytes, size_t mtile_bytes, int npa
     for (int l = 1; l < P->nlev; ++l) {
         L.p64[l] = take(nz * P->levels[l].plane * sizeof(double));
         L.f64[l] = take(nz * P->levels[l].plane * sizeof(double));
-        if (!mixed && march(l)) L.p64B[l] = take(nz * P->levels[l].plane * sizeof(double));
+        // (the pair march keeps no pre-smoothed iterate on the coarse levels)
+        if (!mixed && march(l) && !P->pair_ok[l]) L.p64B[l] = take(nz * P->levels[l].plane * sizeof(double));
     }
     L.p32.assign(P->nlev, 0);
     L.f32.assign(P->nlev, 0);
@@ -94,7 +96,7 @@ constexpr int kMarchSeg = 26;  // rows per fused-sweep strip (the LDS tile heigh
 // register march; both live in one descriptor array.
 constexpr int kRMarchSeg = 128;  // rows per register-march strip
 
-void plan_march_tables(mbp_plan* P, std::vector<unsigned char>& bytes) {
+void plan_march_tables(mbp_plan* P, std::vector<unsigned char>& bytes, std::vector<unsigned char>& pbytes) {
     P->march_ok.assign(P->nlev, 0);
     P->mtile_off.assign(P->nlev, 0);
     P->mtile_cnt.assign(P->nlev, 0);
@@ -120,29 +122,40 @@ void plan_march_tables(mbp_plan* P, std::vector<unsigned char>& bytes) {
         }
         P->use_rmarch[l] = char(P->opt.march);  // the autotuner may change it per level
     }
+    // the pair march, which replaces both forms on the levels it takes: four
+    // halo lanes on the finest level (cycle form), two on the coarse ones
+    P->pair_ok.assign(P->nlev, 0);
+    P->pair_sets.assign(P->nlev, {});
+    pbytes.clear();
+    const int Lg = P->opt.precision == MBP_MIXED ? P->lds_level32 : P->lds_level;
+    for (int l = 0; l < Lg; ++l) {
+        if (!pair_level_ok(P, l)) continue;
+        P->pair_ok[l] = 1;
+        pair_build(P, l, l == 0 ? 4 : 2, pbytes, P->pair_sets[l]);
+    }
 }
 
 static int partial_count(const mbp_plan* P) {
     if (P->mtile_cnt.empty()) return 0;
-    return std::max(4 * P->mtile_cnt[0], P->rtile_cnt[0]);
+    return std::max({4 * P->mtile_cnt[0], P->rtile_cnt[0], pair_max_strips(P, 0)});
 }
 
 size_t plan_device_bytes(const mbp_plan* P) {
     mbp_plan tmp = *P;
-    std::vector<unsigned char> mt;
-    plan_march_tables(&tmp, mt);
+    std::vector<unsigned char> mt, pt;
+    plan_march_tables(&tmp, mt, pt);
     const int W = fft_columns_per_wg(P);
     size_t nt = 0;
     for (int b = 0; b < P->g.nb; ++b) nt += (size_t(P->g.nx[b]) * P->g.ny[b] + W - 1) / W;
-    return layout(&tmp, nt * 32, mt.size(), partial_count(&tmp)).total;
+    return layout(&tmp, nt * 32, mt.size(), pt.size(), partial_count(&tmp)).total;
 }
 
 int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pinned) {
-    std::vector<unsigned char> ftf, fti, mt;
+    std::vector<unsigned char> ftf, fti, mt, pt;
     fft_build_tiles(P, ftf, fti, &P->fft_ntiles);
     if (const int st = fft_stream_setup(P)) return st;
-    plan_march_tables(P, mt);
-    Layout L = layout(P, ftf.size(), mt.size(), partial_count(P));
+    plan_march_tables(P, mt, pt);
+    Layout L = layout(P, ftf.size(), mt.size(), pt.size(), partial_count(P));
     void* mem = ext_mem;
     if (ext_mem) {
         if (ext_bytes < L.total) return MBP_ERR_NOMEM;
@@ -169,6 +182,7 @@ int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pin
     P->d_ftiles_fwd = b + L.ftf;
     P->d_ftiles_inv = b + L.fti;
     P->d_mtiles = b + L.mt;
+    P->d_ptiles = b + L.pt;
     P->mtile_bytes = mt.size();
     P->fhat = reinterpret_cast<double*>(b + L.fhat);
     P->phat = reinterpret_cast<double*>(b + L.phat);
@@ -218,6 +232,7 @@ int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pin
     put(L.ftf, ftf.data(), ftf.size());
     put(L.fti, fti.data(), fti.size());
     put(L.mt, mt.data(), mt.size());
+    put(L.pt, pt.data(), pt.size());
     if (hipMemcpy(mem, img.data(), img.size(), hipMemcpyHostToDevice) != hipSuccess) return MBP_ERR_HIP;
     // (the error-test bounds sit after the fields)
     if (hipMemcpy(P->d_sabs, P->sabs.data(), P->sabs.size() * sizeof(double), hipMemcpyHostToDevice) !=
@@ -307,6 +322,7 @@ void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rto
     c.retire = (flags & MBP_RETIRE) != 0;
     c.warm = (flags & MBP_WARM_START) != 0;
     c.full_lds = !c.mixed && P->lds_level == 0;
+    c.flip = !c.mixed && !c.full_lds && !P->pair_ok.empty() && P->pair_ok[0];
     c.nitems = P->g.nz;
 }
 
@@ -360,7 +376,7 @@ void ctx_test(SolveCtx& c, hipStream_t s, double* state_out) {
     else if (zero)
         launch_norm_from_rhs(P, c.nitems, s);
     else if (c.fused_parts > 0)
-        launch_finish(P, c.fused_parts, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
+        launch_finish(P, c.fused_parts, c.flip ? P->d_flag + 3 : nullptr, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
     else
         launch_residual_norm(P, P->phat, P->fhat, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
     launch_update_active(P, c.rtol2, c.etol2, c.retire ? 1 : 0, P->opt.max_cycles, s, state_out);
@@ -372,13 +388,25 @@ void ctx_vcycle(SolveCtx& c, hipStream_t s) {
     if (c.mixed) {
         // refinement step: the FP32 correction equation is solved by `inner`
         // V-cycles from zero, then the correction is added in FP64
-        for (int k = 0; k < P->opt.inner; ++k)
-            launch_vcycle<float>(P, P->p32[0], P->p32B[0], P->f32[0], P->d_act, P->d_nact, c.nitems, false,
-                                 k == 0, s);
-        launch_add_correction(P, P->phat, P->p32[0], P->d_act, P->d_nact, c.nitems, s, zero);
+        VcycleArgs<float> v{P->p32[0], P->p32B[0], P->f32[0], P->d_act, P->d_nact, c.nitems};
+        bool ready = false;
+        for (int k = 0; k < P->opt.inner; ++k) {
+            v.zero = k == 0;
+            v.last = k + 1 == P->opt.inner;
+            v.ready = ready;
+            launch_vcycle<float>(P, v, s);
+            ready = v.ready;
+            if (v.flipped) std::swap(v.p, v.pB);
+        }
+        launch_add_correction(P, P->phat, v.p, P->d_act, P->d_nact, c.nitems, s, zero);
     } else {
-        c.fused_parts = launch_vcycle<double>(P, P->phat, P->phatB, P->fhat, P->d_act, P->d_nact, c.nitems,
-                                              true, zero, s);
+        VcycleArgs<double> v{P->phat, P->phatB, P->fhat, P->d_act, P->d_nact, c.nitems};
+        v.cycle = P->d_flag + 1;
+        v.norm = true;
+        v.zero = zero;
+        v.ready = c.ready;
+        c.fused_parts = launch_vcycle<double>(P, v, s);
+        c.ready = v.ready;
     }
     ++c.cycles;
 }
@@ -416,6 +444,7 @@ void ctx_epilogue(SolveCtx& c, hipStream_t s) {
     mbp_plan* P = c.P;
     if (c.status == MBP_OK || c.status == MBP_ERR_NOT_CONVERGED) {
         if (c.lazy_zero) launch_zero_unrelaxed(P, P->phat, s);
+        if (c.flip) launch_take_odd(P, P->phat, P->phatB, s);
         if (P->g.singular) launch_singular_fix(P, P->phat, P->d_scal + 5, s);
         launch_inverse(P, P->phat, c.p, s);
     }
