@@ -249,6 +249,7 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                         stages.push_back(group_pair32(gb, cs, l, true, k, inner));
                         stages.push_back(group_march32(gb, cs, l, false, k == 0));
                     }
+                    for (int form = 0; form < 3; ++form) stages.push_back(group_coarse32(gb, cs, form));
                     stages.push_back(group_lds32(gb, cs));
                     for (int l = maxL - 1; l >= 0; --l) {
                         stages.push_back(group_pair32(gb, cs, l, false, k, inner));
@@ -283,6 +284,7 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                     for (const GStage& g : stages) {
                         if (g.kind == G_PRE32 || g.kind == G_POST32) group_launch_march(g, dev, st[0]);
                         else if (g.kind >= G_PAIR_PRE) group_launch_pair(g, dev, st[0]);
+                        else if (g.kind >= G_COARSE0) group_launch_coarse(g, dev, st[0]);
                         else group_launch_mg(g, dev, st[0]);
                     }
                 for (int i : act) cx[i].cycles += cur.chunk;

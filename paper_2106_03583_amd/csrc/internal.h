@@ -53,6 +53,7 @@ struct Level {
     int tile_off = 0;             // first tile in the tile table
     int64_t lds_off = 0;          // element offset of this level in the LDS image
     bool oddwrap = false;         // some block needs the two extra smoothing colours
+    bool odd = false;             // that, or a ring of several blocks of odd length, which no two-colouring fits
     int cx = 1, cy = 1;           // the next coarser level halves x / y in every block (the transfer
                                   // tables carry each block's own step)
     int dp_begin = 0, ip_begin = 0;  // first entries of this level's tables in the pools
@@ -104,6 +105,19 @@ struct PairSet {
     int off = 0, cnt = 0, rows = 0;
 };
 
+// The LDS-resident levels as coarse.hip runs them: places of the tables in
+// the pools and of the parts of the LDS image (CArgs names them).
+struct CoarseInfo {
+    int ok = 0;          // 0: the generic LDS kernels of mg.hip run
+    int lev = 0, nl = 0, ls = 0, wt = 0, wlds = 0;
+    int oT = 0, oRed = 0, oMu = 0, oW = 0, oP = 0, oTab = 0, oRec = 0, nslot = 0, oS = 0;
+    int tab0 = 0, ntab = 0, rec0 = 0, nrec = 0;
+    int ncell = 0;       // most top-level cells of one colour
+    int nthr = 0, per = 0, odd = 0;  // threads, most top-level cells of a colour per thread (2 or 4)
+    int64_t bytes = 0;
+};
+constexpr int kCoarseInLds = 32;  // coarsest planes up to this many cells have their matrices in LDS
+
 struct FFTPlan {
     int n = 0, m = 0;              // real length, complex length n/2
     std::vector<int> radices;      // Stockham stages, product = m
@@ -121,6 +135,7 @@ struct mbp_plan {
     int dp_levels_end = 0, ip_levels_end = 0;  // pool entries of all level tables
     int64_t lds_bytes64 = 0, lds_bytes32 = 0;
     int lds_fglob64 = 0;          // FP64: level lds_level's rhs read from device memory
+    mbp::CoarseInfo coarse;       // the LDS-resident levels (of the plan's precision) in the form of coarse.hip
     int coarse_n = 0;             // cells of the coarsest plane
     std::vector<double> lambda;   // Table-1 eigenvalues
     std::vector<double> shift;    // lambda_q / dz^2
@@ -284,6 +299,17 @@ void launch_norm_from_rhs(const mbp_plan* P, int nitems, hipStream_t s);
 void prof_begin(const mbp_plan* P, int cls, hipStream_t s, double cells);
 void prof_end(const mbp_plan* P, int cls, hipStream_t s);
 
+// coarse.hip (plan.cpp: the rule and the LDS size)
+bool coarse_levels_ok(const mbp_plan* P, int L);
+int64_t coarse_lds_need(const mbp_plan* P, int L, int64_t elem);
+void coarse_build(mbp_plan* P, int L, int64_t elem);
+// ncyc V-cycles from zero on levels L .. of every active mode
+template <typename T>
+void launch_coarse(const mbp_plan* P, int L, T* pL, const T* fL, int ncyc, const int* act, const int* nact, int nitems,
+                   hipStream_t s);
+void launch_coarse_full(const mbp_plan* P, double* p, const double* f, const int* act, const int* nact, int nitems, int maxc,
+                        double rtol2, double etol2, int* cyc, double* rnorm, double* fnorm, hipStream_t s);
+
 // march.hip
 struct MTile;
 bool march_level_ok(const mbp_plan* P, int l);
@@ -380,6 +406,7 @@ struct GEnt {
 };
 enum GKind {
     G_RES32 = 0, G_FINISH, G_UPDATE, G_PRE32, G_LDS32, G_POST32, G_ADDCORR,
+    G_COARSE0, G_COARSE1, G_COARSE2,
     G_PAIR_PRE, G_PAIR_POST0, G_PAIR_POST, G_PAIR_CYCLE0, G_PAIR_CYCLE  // (0: from a zero iterate)
 };
 struct GStage {
@@ -464,5 +491,7 @@ void group_launch_march(const GStage& st, const unsigned char* dev, hipStream_t 
 // The pair-march levels of inner cycle k of `inner`: on the way down (down) or up.
 GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, bool down, int k, int inner);
 void group_launch_pair(const GStage& st, const unsigned char* dev, hipStream_t s);
+GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form);
+void group_launch_coarse(const GStage& st, const unsigned char* dev, hipStream_t s);
 
 }  // namespace mbp

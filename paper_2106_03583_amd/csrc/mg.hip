@@ -1272,7 +1272,9 @@ int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s) {
                                (long long)Lc.plane, P->d_shift, act, nact);
         }
     }
-    {
+    if (P->coarse.ok) {
+        launch_coarse<T>(P, L, P_(L), F_(L), is32 && L == 0 ? P->opt.inner : 1, act, nact, nitems, s);
+    } else {
         LdsArgs a = lds_args(P, L);
         a.fglob = is32 ? 0 : P->lds_fglob64;
         const size_t bytes = size_t(is32 ? P->lds_bytes32 : P->lds_bytes64);
@@ -1353,6 +1355,10 @@ void launch_finish(const mbp_plan* P, int nparts, const int* dyn, double* out, c
 void launch_lds_full(const mbp_plan* P, double* p, const double* f, const int* act, const int* nact,
                      int nitems, int maxc, double rtol2, double etol2, int* cyc, double* rnorm,
                      double* fnorm, hipStream_t s) {
+    if (P->coarse.ok) {
+        launch_coarse_full(P, p, f, act, nact, nitems, maxc, rtol2, etol2, cyc, rnorm, fnorm, s);
+        return;
+    }
     LdsArgs a = lds_args(P, 0);
     const size_t bytes = size_t(P->lds_bytes64);
     set_lds(reinterpret_cast<const void*>(k_lds_full), bytes);
@@ -1594,6 +1600,7 @@ GStage group_lds32(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     size_t bytes = 0;
     for (const SolveCtx* c : cs) {
         const mbp_plan* P = c->P;
+        if (P->coarse.ok) continue;
         const int L = P->lds_level32;
         jobs.push_back(LdsJob<float>{lds_args(P, L), P->p32[L], P->f32[L], (long long)P->levels[L].plane,
                                      P->d_shift, P->d_act, P->d_nact});

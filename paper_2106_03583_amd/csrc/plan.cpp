@@ -266,6 +266,36 @@ void plan_set_shifts(mbp_plan* P) {
     P->g.singular = !g.dirichlet_xy && !zd && alpha == 0.0;
 }
 
+// The form of coarse.hip takes levels L .. when every step below L halves
+// every block both ways, with one sweep before and after the correction, and
+// level L has at most 4096 cells: its 512 threads hold four of each colour.
+// (A form with 1024 threads for up to 8192 cells spilled half of its state: 65 us
+// a V-cycle on 101 x 78 cells against 52 us in the generic kernel.)
+bool coarse_levels_ok(const mbp_plan* P, int L) {
+    if (L + 1 >= P->nlev || P->opt.nu1 != 1 || P->opt.nu2 != 1 || P->levels[L].plane > 4096) return false;
+    for (int l = L; l + 1 < P->nlev; ++l)
+        if (!P->levels[l].cx || !P->levels[l].cy) return false;
+    int64_t e = 0;
+    for (int b = 0; b < P->g.nb; ++b) e += P->levels[L].nx[b] + P->levels[L].ny[b];
+    return e < 60000;
+}
+
+int64_t coarse_lds_need(const mbp_plan* P, int L, int64_t elem) {
+    const int64_t nc = P->coarse_n;
+    int64_t o = 2 * ((nc * 8 + 15) & ~int64_t(15)) + 128 + (nc <= kCoarseInLds ? 2 * nc * nc * 8 : 0);
+    int64_t e = 0, t = 0, r = 0;
+    for (int l = L; l < P->nlev; ++l) {
+        const Level& F = P->levels[l];
+        e += F.plane;
+        for (int b = 0; b < P->g.nb; ++b) {
+            if (l + 1 < P->nlev) e += int64_t(F.odd ? 4 : 2) * ((F.nx[b] + 1) / 2) * ((F.ny[b] + 1) / 2);
+            t += 6 * (F.nx[b] + F.ny[b]);
+        }
+        if (l >= L + 2) r += F.plane * 32;
+    }
+    return o + (e + t) * elem + r + 512 + 48 * int64_t(P->nlev - L) + 64;
+}
+
 int build_plan_host(const mbp_block_desc* blocks, int nblocks, const mbp_synth_desc* z,
                     const mbp_options* opt, mbp_plan* P, std::string* err) {
     return build_plan_host_limits(blocks, nblocks, z, opt, 64 * 1024, P, err);
@@ -534,6 +564,11 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
             }
         }
         for (int b = 0; b < nb; ++b) {
+            const int kx = g.nbr[b][XP], ky = g.nbr[b][YP];
+            if (kx >= 0 && ((par[b] + L.nx[b] + par[kx]) & 1)) L.odd = true;
+            if (ky >= 0 && ((par[b] + L.ny[b] + par[ky]) & 1)) L.odd = true;
+        }
+        for (int b = 0; b < nb; ++b) {
             DBlock d{};
             d.nx = L.nx[b];
             d.ny = L.ny[b];
@@ -548,7 +583,7 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
             d.oddwrap = 0;
             if (g.bc[b][XP] == MBP_PERIODIC && g.nbr[b][XP] == b && (L.nx[b] & 1)) d.oddwrap |= 1;
             if (g.bc[b][YP] == MBP_PERIODIC && g.nbr[b][YP] == b && (L.ny[b] & 1)) d.oddwrap |= 2;
-            if (d.oddwrap) L.oddwrap = true;
+            if (d.oddwrap) L.oddwrap = L.odd = true;
             // coefficients along each axis
             for (int axis = 0; axis < 2; ++axis) {
                 const std::vector<double>& F = axis == 0 ? L.xf[b] : L.yf[b];
@@ -751,12 +786,9 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
     }
 
     // ---- LDS-resident levels: the smallest index whose remaining hierarchy
-    //      (p and rhs of every level) fits the LDS budget.  The FP64 V-cycle
-    //      may take a workgroup's whole budget.  The FP32 one (mixed
-    //      precision, run for many modes and problems at once) is kept to a
-    //      quarter of it: most of its phases keep few lanes busy, so its
-    //      throughput comes from four workgroups sharing a CU, not from
-    //      one more LDS-resident level ----
+    //      fits the LDS budget, in the form of coarse.hip where it takes that level
+    //      or a finer one.  The generic kernels: p and rhs of every level, the whole budget in
+    //      FP64, a quarter of it in FP32 so that four workgroups share a CU ----
     {
         const int64_t budget = P->lds_limit;
         const int64_t budget32 = std::max<int64_t>(budget / 4, 16 * 1024);
@@ -776,6 +808,14 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
         P->lds_level32 = P->nlev - 1;
         for (int l = P->nlev - 1; l >= 0; --l)
             if (need(l, 4) <= budget32) P->lds_level32 = l;
+        auto pick = [&](int generic, int64_t elem) {
+            int best = generic;
+            for (int l = P->nlev - 2; l >= 0; --l)
+                if (l < best && coarse_levels_ok(P, l) && coarse_lds_need(P, l, elem) <= budget) best = l;
+            return best;
+        };
+        P->lds_level = pick(P->lds_level, 8);
+        P->lds_level32 = pick(P->lds_level32, 4);
         P->lds_bytes64 = need(P->lds_level, 8);
         P->lds_bytes32 = need(P->lds_level32, 4);
         // two FP64 workgroups share a CU when the image fits half the budget;
@@ -792,7 +832,7 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
                 P->lds_bytes64 -= fbytes;
             }
         }
-        if (P->lds_bytes64 > budget) {
+        if (P->lds_bytes64 > budget && !coarse_levels_ok(P, P->lds_level)) {
             if (err) *err = "coarsest plane does not fit the LDS budget";
             return MBP_ERR_INVALID;
         }

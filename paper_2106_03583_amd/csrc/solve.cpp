@@ -127,7 +127,9 @@ void plan_march_tables(mbp_plan* P, std::vector<unsigned char>& bytes, std::vect
     P->pair_ok.assign(P->nlev, 0);
     P->pair_sets.assign(P->nlev, {});
     pbytes.clear();
-    const int Lg = P->opt.precision == MBP_MIXED ? P->lds_level32 : P->lds_level;
+    const bool mixed = P->opt.precision == MBP_MIXED;
+    const int Lg = mixed ? P->lds_level32 : P->lds_level;
+    coarse_build(P, Lg, mixed ? 4 : 8);
     for (int l = 0; l < Lg; ++l) {
         if (!pair_level_ok(P, l)) continue;
         P->pair_ok[l] = 1;
@@ -390,9 +392,11 @@ void ctx_vcycle(SolveCtx& c, hipStream_t s) {
         // V-cycles from zero, then the correction is added in FP64
         VcycleArgs<float> v{P->p32[0], P->p32B[0], P->f32[0], P->d_act, P->d_nact, c.nitems};
         bool ready = false;
-        for (int k = 0; k < P->opt.inner; ++k) {
+        // (a hierarchy that fits LDS whole runs its cycles in one launch)
+        const int inner = P->lds_level32 == 0 && P->coarse.ok ? 1 : P->opt.inner;
+        for (int k = 0; k < inner; ++k) {
             v.zero = k == 0;
-            v.last = k + 1 == P->opt.inner;
+            v.last = k + 1 == inner;
             v.ready = ready;
             launch_vcycle<float>(P, v, s);
             ready = v.ready;
