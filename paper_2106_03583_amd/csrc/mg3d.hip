@@ -22,8 +22,11 @@
 // Fields use the caller's packed layout on every level: block b occupies
 // [nz_l * off_b, nz_l * off_{b+1}) in C order (nz_l, ny_b, nx_b), so the
 // finest level reads the caller's rhs and writes the caller's p directly.
+#include <algorithm>
+
 #include "internal.h"
 #include "mg3d.h"
+#include "wave.h"
 
 namespace mbp {
 
@@ -136,7 +139,7 @@ k3_jacobi(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __res
                 acc += res * res;
                 accp += v * v;
             }
-            if (WRITE) pout[c] = v + omega * res / d;
+            if (WRITE) pout[c] = v + div_nr(omega * res, d);
         }
     }
     if (NORM) {
@@ -152,31 +155,55 @@ k3_jacobi(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __res
 
 // ---------------------------------------------------------------------------
 // The same sweep (pin read, so not the zero start) marching along z: a
-// workgroup owns one 64 x 16 x-y tile and a chunk of kZChunk planes; each
-// thread keeps its four cells' values at planes k-1, k, k+1 in registers and
-// the plane-k tile (with a one-cell ring from the tile's neighbours, or from
-// the partner block across a joined face) in LDS.  Every value of p is read
-// from device memory once per sweep, plus the ring.
+// workgroup owns one 64 x 16 x-y tile and a chunk of planes; each thread keeps
+// its four cells' values at planes k-1, k, k+1 in registers and the plane-k tile
+// (with a one-cell ring from the tile's neighbours, or from the partner block
+// across a joined face) in LDS.  Every value of p is read from device memory
+// once per sweep, plus the ring and two planes per chunk.
+//
+// Bound by memory on the finest level: 24 B a cell, of 256^3 cells 90 us a sweep
+// (4.5 TB/s; a large copy reaches 4.9).  A plane step is a latency chain (LDS, a
+// barrier), so everything the next plane needs is loaded a step ahead, the LDS
+// plane has two copies (one barrier a step) and the division is div_nr; addresses
+// advance by a plane, which keeps four waves a SIMD.
+//
+// Chunk: as short as it takes to fill the chip, as every chunk reads two planes
+// more than it owns.  With 32 planes throughout, a level of 64^3 cells ran in 8
+// workgroups and the coarse levels cost as much as the fine one: 44.7 ms for a
+// 256^3 solve, 23.3 / 22.2 / 23.3 ms with 1024 / 2048 / 4096 workgroups wanted, and
+// 17.7 ms with the address arithmetic out of the step.
 // ---------------------------------------------------------------------------
-constexpr int kZChunk = 32;
+constexpr int kZMost = 32;     // most planes of a chunk
+constexpr int kZWgs = 2048;    // workgroups a launch aims at (eight a CU)
+
+// Planes per workgroup (even) for a level of ntiles x-y tiles and nz planes.
+static int zchunk(int ntiles, int nz) {
+    const int n = std::max(1, (kZWgs + ntiles - 1) / std::max(1, ntiles));  // chunks wanted
+    const int c = ((nz + n - 1) / n + 1) & ~1;
+    return std::min(kZMost, std::max(2, c));
+}
 
 namespace {
 
-// p at (k, jj, ii) of block b where (ii, jj) may lie one cell outside the
-// block: the partner's cell across a joined face, 0 beyond a wall (its
-// coupling coefficient is zero) or diagonally outside.
-__device__ __forceinline__ double ring_value(const Op3& o, const double* __restrict__ p, const DBlock& b, int k,
-                                             int ii, int jj) {
+// Cell (ii, jj) of block b, which may lie one cell outside the block: its
+// offset at plane 0 and its plane stride (the partner's cell across a joined
+// face).  False beyond a wall (the coupling is zero) and diagonally outside.
+__device__ __forceinline__ bool ring_cell(const Op3& o, const DBlock& b, int ii, int jj, long long& off, int& stride) {
     const bool xin = ii >= 0 && ii < b.nx, yin = jj >= 0 && jj < b.ny;
-    if (xin && yin) return p[cell3(b, o.nz, k, jj, ii)];
-    if (yin) {
-        if (ii == -1 && b.nbr[XM] >= 0) { const DBlock& n = o.B[b.nbr[XM]]; return p[cell3(n, o.nz, k, jj, n.nx - 1)]; }
-        if (ii == b.nx && b.nbr[XP] >= 0) { const DBlock& n = o.B[b.nbr[XP]]; return p[cell3(n, o.nz, k, jj, 0)]; }
-    } else if (xin) {
-        if (jj == -1 && b.nbr[YM] >= 0) { const DBlock& n = o.B[b.nbr[YM]]; return p[cell3(n, o.nz, k, n.ny - 1, ii)]; }
-        if (jj == b.ny && b.nbr[YP] >= 0) { const DBlock& n = o.B[b.nbr[YP]]; return p[cell3(n, o.nz, k, 0, ii)]; }
-    }
-    return 0.0;
+    int n = -1;
+    off = (long long)o.nz * b.off + (long long)jj * b.nx + ii;
+    stride = b.nx * b.ny;
+    if (xin && yin) return true;
+    if (yin && ii == -1) n = b.nbr[XM];
+    else if (yin && ii == b.nx) n = b.nbr[XP];
+    else if (xin && jj == -1) n = b.nbr[YM];
+    else if (xin && jj == b.ny) n = b.nbr[YP];
+    if (n < 0) return false;
+    const DBlock& p = o.B[n];
+    const int pi = ii < 0 ? p.nx - 1 : ii == b.nx ? 0 : ii, pj = jj < 0 ? p.ny - 1 : jj == b.ny ? 0 : jj;
+    off = (long long)o.nz * p.off + (long long)pj * p.nx + pi;
+    stride = p.nx * p.ny;
+    return true;
 }
 
 // Plane index of z neighbour k (periodic wrap) or -1 where the ghost rule
@@ -205,46 +232,61 @@ template <int MODE>
 __global__ void __launch_bounds__(256)
 k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __restrict__ pin,
              double* __restrict__ pout, const double* __restrict__ f, double fshift, double omega,
-             double* __restrict__ part, Rst3 rs) {
+             double* __restrict__ part, Rst3 rs, int chunk) {
     constexpr bool NORM = MODE == 1;
-    __shared__ double sp[kTileY + 2][kTileX + 2];
+    __shared__ double sp2[2][kTileY + 2][kTileX + 2];  // two planes: one barrier a step
     __shared__ double sr[MODE == 2 ? kTileY : 1][MODE == 2 ? kTileX : 1];
     const int4 t = tiles[xcd_remap3(blockIdx.x, ntiles)];
     const DBlock b = o.B[t.x];
-    const int k0 = blockIdx.y * kZChunk;
-    const int k1 = min(k0 + kZChunk, o.nz);
-    const int tx = threadIdx.x, ty = threadIdx.y;
+    const int k0 = blockIdx.y * chunk;
+    const int k1 = min(k0 + chunk, o.nz);
+    // a wave is one row group: its rows and their coefficients are uniform
+    const int tx = threadIdx.x, ty = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int tid = ty * kTileX + tx;
     const int i = t.y + tx;
     const bool in_i = i < b.nx;
     const double* dp = o.dp;
-    const long long kz = (long long)b.nx * b.ny;
-    const long long base = (long long)o.nz * b.off;
     constexpr int R = kTileY / kRowsPerPass;  // rows per thread
-    int j[R];
+    const int kz = b.nx * b.ny;
+    const long long own = (long long)o.nz * b.off + (long long)(t.z + ty) * b.nx + i;
     bool act[R];
-    double wym[R], wyp[R], dxy[R];
+    double wym[R], wyp[R], dy[R];
     const double wxm = in_i ? dp[b.cx + i] : 0.0, wxp = in_i ? dp[b.cx + b.nx + i] : 0.0;
-    const double dx = in_i ? dp[b.cx + 2 * b.nx + i] : 0.0;
+    const double dx = (in_i ? dp[b.cx + 2 * b.nx + i] : 1.0) - o.alpha;
+    // every lane's cells: its own, or the cell across a joined edge in a ragged tile
+    long long at[R];
+    int st[R];
+    bool ok[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        j[r] = t.z + ty + kRowsPerPass * r;
-        act[r] = in_i && j[r] < b.ny;
-        wym[r] = act[r] ? dp[b.cy + j[r]] : 0.0;
-        wyp[r] = act[r] ? dp[b.cy + b.ny + j[r]] : 0.0;
-        dxy[r] = act[r] ? dx + dp[b.cy + 2 * b.ny + j[r]] - o.alpha : 1.0;
+        const int j = t.z + ty + kRowsPerPass * r, jc = min(j, b.ny - 1);
+        act[r] = in_i && j < b.ny;
+        wym[r] = dp[b.cy + jc];
+        wyp[r] = dp[b.cy + b.ny + jc];
+        dy[r] = dp[b.cy + 2 * b.ny + jc];
+        ok[r] = ring_cell(o, b, i, j, at[r], st[r]);
     }
+    // the tile's ring: one cell of 160 threads
+    long long rat = 0;
+    int rst = 0;
+    bool rok = false;
+    const int side = tid < 2 * kTileX ? tid / kTileX : (tid - 2 * kTileX) / kTileY;
+    const int along = tid < 2 * kTileX ? tid % kTileX : (tid - 2 * kTileX) % kTileY;
+    if (tid < 2 * kTileX) rok = ring_cell(o, b, t.y + along, side == 0 ? t.z - 1 : t.z + kTileY, rat, rst);
+    else if (tid < 2 * kTileX + 2 * kTileY)
+        rok = ring_cell(o, b, side == 0 ? t.y - 1 : t.y + kTileX, t.z + along, rat, rst);
     auto load = [&](int kp, double* v) {
         const int q = zplane(o, kp);
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = (act[r] && q >= 0) ? pin[base + q * kz + (long long)j[r] * b.nx + i] : 0.0;
+        for (int r = 0; r < R; ++r) v[r] = (ok[r] && q >= 0) ? pin[at[r] + (long long)q * st[r]] : 0.0;
     };
     auto loadf = [&](int kp, double* v) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            v[r] = (act[r] && kp < o.nz) ? f[base + kp * kz + (long long)j[r] * b.nx + i] - fshift : 0.0;
+            v[r] = (act[r] && kp < o.nz) ? f[own + (long long)kp * kz + kRowsPerPass * r * b.nx] - fshift : 0.0;
     };
     double pm[R], pc[R], pp[R], fc[R], pn[R], fn[R];
+    double rc = rok ? pin[rat + (long long)k0 * rst] : 0.0;
     load(k0 - 1, pm);
     load(k0, pc);
     load(k0 + 1, pp);
@@ -256,29 +298,20 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             racc[r] = 0.0;
-            rw[r] = act[r] ? 0.5 * wx * dp[b.rwy + j[r]] : 0.0;  // volume fraction: x, y and the z pair
+            rw[r] = act[r] ? 0.5 * wx * dp[b.rwy + t.z + ty + kRowsPerPass * r] : 0.0;  // volume fraction: x, y and the z pair
         }
     }
     for (int k = k0; k < k1; ++k) {
+        double(*sp)[kTileX + 2] = sp2[k & 1];
+        // plane k into LDS: own cells, edge cells and ring, all from registers
+#pragma unroll
+        for (int r = 0; r < R; ++r) sp[ty + kRowsPerPass * r + 1][tx + 1] = pc[r];
+        if (tid < 2 * kTileX) sp[side == 0 ? 0 : kTileY + 1][along + 1] = rc;
+        else if (tid < 2 * kTileX + 2 * kTileY) sp[along + 1][side == 0 ? 0 : kTileX + 1] = rc;
         if (k + 1 < k1) {  // next plane's loads in flight during this plane's work
             load(k + 2, pn);
             loadf(k + 1, fn);
-        }
-        // plane k into LDS: own cells from registers, the ring and cells of a
-        // ragged tile's edge through ring_value
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int ly = ty + kRowsPerPass * r;
-            sp[ly + 1][tx + 1] = act[r] ? pc[r] : ring_value(o, pin, b, k, i, t.z + ly);
-        }
-        if (tid < 2 * kTileX) {
-            const int side = tid / kTileX, lx = tid % kTileX;
-            const int jj = side == 0 ? t.z - 1 : t.z + kTileY;
-            sp[side == 0 ? 0 : kTileY + 1][lx + 1] = ring_value(o, pin, b, k, t.y + lx, jj);
-        } else if (tid < 2 * kTileX + 2 * kTileY) {
-            const int e = tid - 2 * kTileX, side = e / kTileY, ly = e % kTileY;
-            const int ii = side == 0 ? t.y - 1 : t.y + kTileX;
-            sp[ly + 1][side == 0 ? 0 : kTileX + 1] = ring_value(o, pin, b, k, ii, t.z + ly);
+            rc = rok ? pin[rat + (long long)(k + 1) * rst] : 0.0;
         }
         __syncthreads();
         const double zd = zdiag(o, k);
@@ -286,7 +319,7 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
         for (int r = 0; r < R; ++r) {
             if (!act[r]) continue;
             const int ly = ty + kRowsPerPass * r + 1, lx = tx + 1;
-            const double d = dxy[r] + zd;
+            const double d = dx + dy[r] + zd;
             const double off = wxm * sp[ly][lx - 1] + wxp * sp[ly][lx + 1] + wym[r] * sp[ly - 1][lx] +
                                wyp[r] * sp[ly + 1][lx] + o.idz2 * (pm[r] + pp[r]);
             const double res = fc[r] - off - d * pc[r];
@@ -295,9 +328,8 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
                 accp += pc[r] * pc[r];
             }
             if (MODE == 2) racc[r] += rw[r] * res;
-            else pout[base + k * kz + (long long)j[r] * b.nx + i] = pc[r] + omega * res / d;
+            else pout[own + (long long)k * kz + kRowsPerPass * r * b.nx] = pc[r] + div_nr(omega * res, d);
         }
-        __syncthreads();
         if (MODE == 2 && (k & 1)) {  // planes 2K, 2K + 1 done: sum the x-y children
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -456,21 +488,20 @@ k3_prolong(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, const i
 
 // ---------------------------------------------------------------------------
 // The same correction when both x-y and z coarsen, marching along z: a
-// workgroup owns one 64 x 16 fine tile and kPZChunk fine planes (pairs 2K,
-// 2K+1).  Each coarse plane the chunk needs is staged once into LDS (the
+// workgroup owns one 64 x 16 fine tile and a chunk of fine planes (pairs 2K,
+// 2K+1; short enough to fill the chip, as in the sweep).  Each coarse plane the chunk needs is staged once into LDS (the
 // tile's coarse cells and their ring, through cvalue), and its bilinear
 // interpolant at the thread's four cells kept in registers; fine plane 2K
 // takes 1/4 of plane K-1 and 3/4 of plane K, plane 2K+1 3/4 of K and 1/4 of
 // K+1 (mirror or wrap beyond the z ends).
 // ---------------------------------------------------------------------------
-constexpr int kPZChunk = 16;             // fine planes per workgroup (even)
 constexpr int kPX = kTileX / 2 + 4;      // staged coarse columns (with ring and merge slack)
 constexpr int kPY = kTileY / 2 + 4;      // staged coarse rows
 
 __global__ void __launch_bounds__(256)
 k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, const int4* __restrict__ tiles_f,
               int ntiles_f, int nzf, int nzc, const double* __restrict__ dp, const int* __restrict__ ip,
-              const double* __restrict__ pc, double* __restrict__ pf, int zlo, int zhi) {
+              const double* __restrict__ pc, double* __restrict__ pf, int zlo, int zhi, int chunk) {
     __shared__ double sc[kPY][kPX];
     const int4 t = tiles_f[xcd_remap3(blockIdx.x, ntiles_f)];
     const DBlock bf = Bf[t.x];
@@ -521,7 +552,7 @@ k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, cons
     // (Neumann +, Dirichlet -)
     const double slo = zlo == MBP_DIRICHLET ? -1.0 : 1.0, shi = zhi == MBP_DIRICHLET ? -1.0 : 1.0;
     const bool per = zlo == MBP_PERIODIC;
-    const int K0 = blockIdx.y * (kPZChunk / 2);
+    const int K0 = blockIdx.y * (chunk / 2), K1 = min(K0 + chunk / 2, nzc);
     const long long base = (long long)nzf * bf.off, kz = (long long)bf.nx * bf.ny;
     double em[R], ec[R], ep[R];
     interp(K0, ec);
@@ -529,7 +560,7 @@ k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, cons
     else
 #pragma unroll
         for (int r = 0; r < R; ++r) em[r] = slo * ec[r];
-    for (int K = K0; K < K0 + kPZChunk / 2; ++K) {
+    for (int K = K0; K < K1; ++K) {
         if (K + 1 < nzc || per) interp((K + 1) % nzc, ep);
         else
 #pragma unroll
@@ -677,12 +708,13 @@ long long m3_jacobi(const Mg3Plan& M, int l, const double* pin, double* pout, co
                                 fshift, M.omega, part);
         return (long long)L.ntiles * L.nz;
     }
-    const dim3 g(unsigned(L.ntiles), unsigned((L.nz + kZChunk - 1) / kZChunk));
+    const int chunk = zchunk(L.ntiles, L.nz);
+    const dim3 g(unsigned(L.ntiles), unsigned((L.nz + chunk - 1) / chunk));
     const Rst3 none{nullptr, 0, nullptr};
     if (part) hipLaunchKernelGGL(k3_jacobi_zm<1>, g, kBlk, 0, s, o, tl, L.ntiles, pin, pout, f, fshift, M.omega,
-                                 part, none);
+                                 part, none, chunk);
     else hipLaunchKernelGGL(k3_jacobi_zm<0>, g, kBlk, 0, s, o, tl, L.ntiles, pin, pout, f, fshift, M.omega, part,
-                            none);
+                            none, chunk);
     return (long long)g.x * g.y;
 }
 
@@ -712,10 +744,11 @@ void m3_restrict(const Mg3Plan& M, int l, const double* p, const double* f, doub
     const Mg3Level& F = M.lev[l];
     const Mg3Level& C = M.lev[l + 1];
     const Op3 o = op_of(M, l);
-    if (F.xyc && F.zc && F.xy22 && F.even_xy && F.nz % kZChunk == 0) {  // marching form
-        const dim3 g(unsigned(F.ntiles), unsigned(F.nz / kZChunk));
+    if (F.xyc && F.zc && F.xy22 && F.even_xy && F.nz % 2 == 0) {  // marching form
+        const int chunk = zchunk(F.ntiles, F.nz);
+        const dim3 g(unsigned(F.ntiles), unsigned((F.nz + chunk - 1) / chunk));
         hipLaunchKernelGGL(k3_jacobi_zm<2>, g, kBlk, 0, s, o, M.d_tiles + F.tile_off, F.ntiles, p, nullptr, f, fshift,
-                           M.omega, nullptr, Rst3{M.d_blk + C.blk_off, C.nz, fc});
+                           M.omega, nullptr, Rst3{M.d_blk + C.blk_off, C.nz, fc}, chunk);
         return;
     }
     hipLaunchKernelGGL(k3_restrict, grid_of(C), kBlk, 0, s, o, M.d_blk + C.blk_off, M.d_tiles + C.tile_off, C.ntiles,
@@ -725,10 +758,11 @@ void m3_restrict(const Mg3Plan& M, int l, const double* p, const double* f, doub
 void m3_prolong(const Mg3Plan& M, int l, const double* pc, double* pf, hipStream_t s) {
     const Mg3Level& F = M.lev[l];
     const Mg3Level& C = M.lev[l + 1];
-    if (F.xyc && F.zc && F.xy22 && F.nz % kPZChunk == 0) {  // staged tile: x-y halved
-        const dim3 g(unsigned(F.ntiles), unsigned(F.nz / kPZChunk));
+    if (F.xyc && F.zc && F.xy22 && F.nz % 2 == 0) {  // staged tile: x-y halved
+        const int chunk = zchunk(F.ntiles, F.nz);
+        const dim3 g(unsigned(F.ntiles), unsigned((F.nz + chunk - 1) / chunk));
         hipLaunchKernelGGL(k3_prolong_zm, g, kBlk, 0, s, M.d_blk + F.blk_off, M.d_blk + C.blk_off,
-                           M.d_tiles + F.tile_off, F.ntiles, F.nz, C.nz, M.d_dbl, M.d_int, pc, pf, M.zlo, M.zhi);
+                           M.d_tiles + F.tile_off, F.ntiles, F.nz, C.nz, M.d_dbl, M.d_int, pc, pf, M.zlo, M.zhi, chunk);
         return;
     }
     hipLaunchKernelGGL(k3_prolong, grid_of(F), kBlk, 0, s, M.d_blk + F.blk_off, M.d_blk + C.blk_off,
