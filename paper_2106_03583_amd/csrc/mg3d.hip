@@ -22,53 +22,12 @@
 // Fields use the caller's packed layout on every level: block b occupies
 // [nz_l * off_b, nz_l * off_{b+1}) in C order (nz_l, ny_b, nx_b), so the
 // finest level reads the caller's rhs and writes the caller's p directly.
-#include <algorithm>
-
-#include "internal.h"
 #include "mg3d.h"
-#include "wave.h"
+#include "op3.h"
 
 namespace mbp {
 
 namespace {
-
-__device__ __forceinline__ int xcd_remap3(int g, int n) {
-    int x = g & 7, l = g >> 3;
-    int per = n >> 3, rem = n & 7;
-    return x * per + min(x, rem) + l;
-}
-
-__device__ __forceinline__ long long cell3(const DBlock& b, int nz, int k, int j, int i) {
-    return (long long)nz * b.off + ((long long)k * b.ny + j) * b.nx + i;
-}
-
-// Sum over one workgroup; the result is valid in thread 0.
-__device__ __forceinline__ double wg_sum(double v, double* red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const int t = threadIdx.x + threadIdx.y * blockDim.x;
-    const int w = t >> 6, nw = (blockDim.x * blockDim.y + 63) >> 6;
-    __syncthreads();
-    if ((t & 63) == 0) red[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (t == 0)
-        for (int k = 0; k < nw; ++k) s += red[k];
-    return s;
-}
-
-// (L_h - alpha) p at cell (b, k, j, i) and its diagonal coefficient.  x-y
-// neighbours beyond a joined face come from the partner block; beyond a wall
-// the coefficient already holds the boundary condition (Neumann: none,
-// Dirichlet: folded into the diagonal).  z ends: periodic wrap, or a mirror
-// ghost (Neumann +p, Dirichlet -p) one cell away.
-struct Op3 {
-    const DBlock* B;
-    const double* dp;
-    int nz;
-    double idz2;
-    int zlo, zhi;  // MBP_PERIODIC / MBP_NEUMANN / MBP_DIRICHLET
-    double alpha;
-};
 
 __device__ __forceinline__ double zdiag(const Op3& o, int k) {
     double d = -2.0 * o.idz2;
@@ -161,61 +120,18 @@ k3_jacobi(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __res
 // across a joined face) in LDS.  Every value of p is read from device memory
 // once per sweep, plus the ring and two planes per chunk.
 //
-// Bound by memory on the finest level: 24 B a cell, of 256^3 cells 90 us a sweep
-// (4.5 TB/s; a large copy reaches 4.9).  A plane step is a latency chain (LDS, a
+// Bound by memory on the finest level: 24 B a cell, of 256^3 cells 80 us a sweep
+// (5.0 TB/s, a large copy's rate).  A plane step is a latency chain (LDS, a
 // barrier), so everything the next plane needs is loaded a step ahead, the LDS
-// plane has two copies (one barrier a step) and the division is div_nr; addresses
-// advance by a plane, which keeps four waves a SIMD.
+// plane has two copies (one barrier a step), the division is div_nr, and addresses
+// are resolved once (four waves a SIMD).  Loads carry no branch: cells that do not
+// exist read another, and are masked where they are used (guarded loads 90 us).
 //
-// Chunk: as short as it takes to fill the chip, as every chunk reads two planes
-// more than it owns.  With 32 planes throughout, a level of 64^3 cells ran in 8
-// workgroups and the coarse levels cost as much as the fine one: 44.7 ms for a
-// 256^3 solve, 23.3 / 22.2 / 23.3 ms with 1024 / 2048 / 4096 workgroups wanted, and
-// 17.7 ms with the address arithmetic out of the step.
+// A level of 64^3 cells ran in 8 workgroups when every one took 32 planes, and
+// the coarse levels cost as much as the fine one: 44.7 ms for a 256^3 solve, 22.2
+// with the chunk by level, 17.7 with the address arithmetic out of the step, 14.6
+// with loads free of branches and the prolongation's too.
 // ---------------------------------------------------------------------------
-constexpr int kZMost = 32;     // most planes of a chunk
-constexpr int kZWgs = 2048;    // workgroups a launch aims at (eight a CU)
-
-// Planes per workgroup (even) for a level of ntiles x-y tiles and nz planes.
-static int zchunk(int ntiles, int nz) {
-    const int n = std::max(1, (kZWgs + ntiles - 1) / std::max(1, ntiles));  // chunks wanted
-    const int c = ((nz + n - 1) / n + 1) & ~1;
-    return std::min(kZMost, std::max(2, c));
-}
-
-namespace {
-
-// Cell (ii, jj) of block b, which may lie one cell outside the block: its
-// offset at plane 0 and its plane stride (the partner's cell across a joined
-// face).  False beyond a wall (the coupling is zero) and diagonally outside.
-__device__ __forceinline__ bool ring_cell(const Op3& o, const DBlock& b, int ii, int jj, long long& off, int& stride) {
-    const bool xin = ii >= 0 && ii < b.nx, yin = jj >= 0 && jj < b.ny;
-    int n = -1;
-    off = (long long)o.nz * b.off + (long long)jj * b.nx + ii;
-    stride = b.nx * b.ny;
-    if (xin && yin) return true;
-    if (yin && ii == -1) n = b.nbr[XM];
-    else if (yin && ii == b.nx) n = b.nbr[XP];
-    else if (xin && jj == -1) n = b.nbr[YM];
-    else if (xin && jj == b.ny) n = b.nbr[YP];
-    if (n < 0) return false;
-    const DBlock& p = o.B[n];
-    const int pi = ii < 0 ? p.nx - 1 : ii == b.nx ? 0 : ii, pj = jj < 0 ? p.ny - 1 : jj == b.ny ? 0 : jj;
-    off = (long long)o.nz * p.off + (long long)pj * p.nx + pi;
-    stride = p.nx * p.ny;
-    return true;
-}
-
-// Plane index of z neighbour k (periodic wrap) or -1 where the ghost rule
-// applies (its coupling is folded into the diagonal).
-__device__ __forceinline__ int zplane(const Op3& o, int k) {
-    if (k >= 0 && k < o.nz) return k;
-    if (o.zlo == MBP_PERIODIC) return (k + o.nz) % o.nz;
-    return -1;
-}
-
-}  // namespace
-
 // The coarse level a restricting march writes to.
 struct Rst3 {
     const DBlock* Bc;
@@ -248,13 +164,13 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
     const double* dp = o.dp;
     constexpr int R = kTileY / kRowsPerPass;  // rows per thread
     const int kz = b.nx * b.ny;
-    const long long own = (long long)o.nz * b.off + (long long)(t.z + ty) * b.nx + i;
     bool act[R];
     double wym[R], wyp[R], dy[R];
     const double wxm = in_i ? dp[b.cx + i] : 0.0, wxp = in_i ? dp[b.cx + b.nx + i] : 0.0;
     const double dx = (in_i ? dp[b.cx + 2 * b.nx + i] : 1.0) - o.alpha;
     // every lane's cells: its own, or the cell across a joined edge in a ragged tile
     long long at[R];
+    long long fo[R];  // own cell, of an inactive one the block's first
     int st[R];
     bool ok[R];
 #pragma unroll
@@ -265,6 +181,8 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
         wyp[r] = dp[b.cy + b.ny + jc];
         dy[r] = dp[b.cy + 2 * b.ny + jc];
         ok[r] = ring_cell(o, b, i, j, at[r], st[r]);
+        if (!ok[r]) at[r] = (long long)o.nz * b.off;  // loads need no branch: masked where they are used
+        fo[r] = (long long)o.nz * b.off + (act[r] ? (long long)j * b.nx + i : 0);
     }
     // the tile's ring: one cell of 160 threads
     long long rat = 0;
@@ -275,18 +193,18 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
     if (tid < 2 * kTileX) rok = ring_cell(o, b, t.y + along, side == 0 ? t.z - 1 : t.z + kTileY, rat, rst);
     else if (tid < 2 * kTileX + 2 * kTileY)
         rok = ring_cell(o, b, side == 0 ? t.y - 1 : t.y + kTileX, t.z + along, rat, rst);
+    if (!rok) rat = (long long)o.nz * b.off;
     auto load = [&](int kp, double* v) {
-        const int q = zplane(o, kp);
+        const int q = max(0, zplane(o, kp));
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = (ok[r] && q >= 0) ? pin[at[r] + (long long)q * st[r]] : 0.0;
+        for (int r = 0; r < R; ++r) v[r] = pin[at[r] + (long long)q * st[r]];
     };
     auto loadf = [&](int kp, double* v) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = (act[r] && kp < o.nz) ? f[own + (long long)kp * kz + kRowsPerPass * r * b.nx] - fshift : 0.0;
+        for (int r = 0; r < R; ++r) v[r] = f[fo[r] + (long long)kp * kz];
     };
     double pm[R], pc[R], pp[R], fc[R], pn[R], fn[R];
-    double rc = rok ? pin[rat + (long long)k0 * rst] : 0.0;
+    double rc = pin[rat + (long long)k0 * rst];
     load(k0 - 1, pm);
     load(k0, pc);
     load(k0 + 1, pp);
@@ -305,30 +223,32 @@ k3_jacobi_zm(Op3 o, const int4* __restrict__ tiles, int ntiles, const double* __
         double(*sp)[kTileX + 2] = sp2[k & 1];
         // plane k into LDS: own cells, edge cells and ring, all from registers
 #pragma unroll
-        for (int r = 0; r < R; ++r) sp[ty + kRowsPerPass * r + 1][tx + 1] = pc[r];
-        if (tid < 2 * kTileX) sp[side == 0 ? 0 : kTileY + 1][along + 1] = rc;
-        else if (tid < 2 * kTileX + 2 * kTileY) sp[along + 1][side == 0 ? 0 : kTileX + 1] = rc;
+        for (int r = 0; r < R; ++r) sp[ty + kRowsPerPass * r + 1][tx + 1] = ok[r] ? pc[r] : 0.0;
+        if (tid < 2 * kTileX) sp[side == 0 ? 0 : kTileY + 1][along + 1] = rok ? rc : 0.0;
+        else if (tid < 2 * kTileX + 2 * kTileY) sp[along + 1][side == 0 ? 0 : kTileX + 1] = rok ? rc : 0.0;
         if (k + 1 < k1) {  // next plane's loads in flight during this plane's work
             load(k + 2, pn);
             loadf(k + 1, fn);
-            rc = rok ? pin[rat + (long long)(k + 1) * rst] : 0.0;
+            rc = pin[rat + (long long)(k + 1) * rst];
         }
         __syncthreads();
         const double zd = zdiag(o, k);
+        // ghosts at the z ends are folded into the diagonal
+        const bool lo = k == 0 && o.zlo != MBP_PERIODIC, hi = k == o.nz - 1 && o.zhi != MBP_PERIODIC;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (!act[r]) continue;
             const int ly = ty + kRowsPerPass * r + 1, lx = tx + 1;
             const double d = dx + dy[r] + zd;
             const double off = wxm * sp[ly][lx - 1] + wxp * sp[ly][lx + 1] + wym[r] * sp[ly - 1][lx] +
-                               wyp[r] * sp[ly + 1][lx] + o.idz2 * (pm[r] + pp[r]);
-            const double res = fc[r] - off - d * pc[r];
+                               wyp[r] * sp[ly + 1][lx] + o.idz2 * ((lo ? 0.0 : pm[r]) + (hi ? 0.0 : pp[r]));
+            const double res = fc[r] - fshift - off - d * pc[r];
             if (NORM) {
                 acc += res * res;
                 accp += pc[r] * pc[r];
             }
             if (MODE == 2) racc[r] += rw[r] * res;
-            else pout[own + (long long)k * kz + kRowsPerPass * r * b.nx] = pc[r] + div_nr(omega * res, d);
+            else pout[fo[r] + (long long)k * kz] = pc[r] + div_nr(omega * res, d);
         }
         if (MODE == 2 && (k & 1)) {  // planes 2K, 2K + 1 done: sum the x-y children
 #pragma unroll
@@ -406,11 +326,16 @@ k3_restrict(Op3 of, const DBlock* __restrict__ Bc, const int4* __restrict__ tile
 
 namespace {
 
-// Coarse value at (I, J) of plane K (K inside [0, nzc)) of block b, I in
-// [-1, nx], J in [-1, ny]: beyond a joined face the partner's cell, beyond a
-// wall the mirror image (Neumann +, Dirichlet -); corners through y first.
-__device__ __forceinline__ double cvalue(const double* __restrict__ pc, const DBlock* __restrict__ B, int nzc,
-                                         int b, int I, int J, int K) {
+// Where the coarse value at (I, J) of block b stands, I in [-1, nx], J in [-1, ny]:
+// beyond a joined face the partner's cell, beyond a wall the mirror image
+// (Neumann +, Dirichlet -); corners through y first.  Offset at plane 0, plane
+// stride, sign.
+struct CPlace {
+    long long off;
+    int plane;
+    double sign;
+};
+__device__ __forceinline__ CPlace cplace(const DBlock* __restrict__ B, int nzc, int b, int I, int J) {
     double s = 1.0;
     const DBlock* bb = &B[b];
     if (J < 0) {
@@ -427,10 +352,16 @@ __device__ __forceinline__ double cvalue(const double* __restrict__ pc, const DB
         if (bb->nbr[XP] >= 0) { bb = &B[bb->nbr[XP]]; I = 0; }
         else { if (bb->bc[XP] == MBP_DIRICHLET) s = -s; I = bb->nx - 1; }
     }
-    return s * pc[cell3(*bb, nzc, K, J, I)];
+    return CPlace{cell3(*bb, nzc, 0, J, I), bb->nx * bb->ny, s};
 }
 
-// Bilinear (physical weights) value of coarse plane K at fine cell (i, j).
+// Coarse value at (I, J) of plane K (K inside [0, nzc)).
+__device__ __forceinline__ double cvalue(const double* __restrict__ pc, const DBlock* __restrict__ B, int nzc,
+                                         int b, int I, int J, int K) {
+    const CPlace c = cplace(B, nzc, b, I, J);
+    return c.sign * pc[c.off + (long long)K * c.plane];
+}
+
 __device__ __forceinline__ double bilinear(const double* __restrict__ pc, const DBlock* __restrict__ Bc, int nzc,
                                            const DBlock& bf, int b, const double* __restrict__ dp,
                                            const int* __restrict__ ip, int i, int j, int K) {
@@ -489,11 +420,17 @@ k3_prolong(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, const i
 // ---------------------------------------------------------------------------
 // The same correction when both x-y and z coarsen, marching along z: a
 // workgroup owns one 64 x 16 fine tile and a chunk of fine planes (pairs 2K,
-// 2K+1; short enough to fill the chip, as in the sweep).  Each coarse plane the chunk needs is staged once into LDS (the
-// tile's coarse cells and their ring, through cvalue), and its bilinear
-// interpolant at the thread's four cells kept in registers; fine plane 2K
-// takes 1/4 of plane K-1 and 3/4 of plane K, plane 2K+1 3/4 of K and 1/4 of
-// K+1 (mirror or wrap beyond the z ends).
+// 2K+1; short enough to fill the chip, as in the sweep).  Each coarse plane the
+// chunk needs passes once through LDS (the tile's coarse cells and their ring,
+// two cells a thread, addressed once and loaded a plane ahead; two copies, one
+// barrier a plane), and its bilinear interpolant at the thread's four cells is
+// kept in registers; fine plane 2K takes 1/4 of plane K-1 and 3/4 of plane K,
+// plane 2K+1 3/4 of K and 1/4 of K+1 (mirror or wrap beyond the z ends).
+//
+// Bound by memory on the finest level: p in and out, an eighth of it in.  With
+// the coarse plane's addresses resolved at every step and its loads between two
+// barriers, 86 us on 256^3 cells and 9-18 us on the levels below; now
+// 49 and 6-12.
 // ---------------------------------------------------------------------------
 constexpr int kPX = kTileX / 2 + 4;      // staged coarse columns (with ring and merge slack)
 constexpr int kPY = kTileY / 2 + 4;      // staged coarse rows
@@ -502,7 +439,7 @@ __global__ void __launch_bounds__(256)
 k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, const int4* __restrict__ tiles_f,
               int ntiles_f, int nzf, int nzc, const double* __restrict__ dp, const int* __restrict__ ip,
               const double* __restrict__ pc, double* __restrict__ pf, int zlo, int zhi, int chunk) {
-    __shared__ double sc[kPY][kPX];
+    __shared__ double sc2[2][kPY][kPX];
     const int4 t = tiles_f[xcd_remap3(blockIdx.x, ntiles_f)];
     const DBlock bf = Bf[t.x];
     const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kTileX + tx;
@@ -529,20 +466,31 @@ k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, cons
         ly[r] = act[r] ? ip[bf.pcy + j] - cy0 : 0;
         wy[r] = act[r] ? dp[bf.pwy + j] : 0.0;
     }
-    // bilinear values of coarse plane K (inside [0, nzc)) at the thread's cells
-    auto interp = [&](int K, double* e) {
-        __syncthreads();
-        for (int q = tid; q < ncx * ncy; q += kTileX * kRowsPerPass) {
-            const int a = q % ncx, b = q / ncx;
-            sc[b][a] = cvalue(pc, Bc, nzc, t.x, cx0 + a, cy0 + b, K);
-        }
-        __syncthreads();
+    // the thread's staged cells
+    constexpr int S = (kPX * kPY + kTileX * kRowsPerPass - 1) / (kTileX * kRowsPerPass);
+    CPlace sp[S];
+    double sv[S];
+    int dst[S];
+#pragma unroll
+    for (int n = 0; n < S; ++n) {
+        const int q = tid + n * kTileX * kRowsPerPass, a = q % ncx, b = q / ncx;
+        dst[n] = b < ncy ? b * kPX + a : -1;
+        sp[n] = cplace(Bc, nzc, t.x, cx0 + (b < ncy ? a : 0), cy0 + (b < ncy ? b : 0));
+    }
+    auto fetch = [&](int K) {
+#pragma unroll
+        for (int n = 0; n < S; ++n) sv[n] = pc[sp[n].off + (long long)K * sp[n].plane];
+    };
+    auto stage = [&](int h) {
+#pragma unroll
+        for (int n = 0; n < S; ++n)
+            if (dst[n] >= 0) (&sc2[h][0][0])[dst[n]] = sp[n].sign * sv[n];
+    };
+    // bilinear values of the staged plane at the thread's cells
+    auto interp = [&](int h, double* e) {
+        const double(*sc)[kPX] = sc2[h];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (!act[r]) {
-                e[r] = 0.0;
-                continue;
-            }
             const double e00 = sc[ly[r]][lx], e10 = sc[ly[r]][lx + 1];
             const double e01 = sc[ly[r] + 1][lx], e11 = sc[ly[r] + 1][lx + 1];
             e[r] = wy[r] * (wx * e00 + (1.0 - wx) * e10) + (1.0 - wy[r]) * (wx * e01 + (1.0 - wx) * e11);
@@ -553,24 +501,44 @@ k3_prolong_zm(const DBlock* __restrict__ Bf, const DBlock* __restrict__ Bc, cons
     const double slo = zlo == MBP_DIRICHLET ? -1.0 : 1.0, shi = zhi == MBP_DIRICHLET ? -1.0 : 1.0;
     const bool per = zlo == MBP_PERIODIC;
     const int K0 = blockIdx.y * (chunk / 2), K1 = min(K0 + chunk / 2, nzc);
-    const long long base = (long long)nzf * bf.off, kz = (long long)bf.nx * bf.ny;
+    const int kz = bf.nx * bf.ny;
+    long long c[R];  // own cell at plane 0, of an inactive one the block's first
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        c[r] = (long long)nzf * bf.off + (act[r] ? (t.z + ty + kRowsPerPass * r) * bf.nx + i : 0);
     double em[R], ec[R], ep[R];
-    interp(K0, ec);
-    if (K0 > 0 || per) interp((K0 - 1 + nzc) % nzc, em);
-    else
+    fetch(K0);
+    stage(0);
+    fetch(K0 > 0 || per ? (K0 - 1 + nzc) % nzc : 0);
+    stage(1);
+    fetch((K0 + 1) % nzc);
+    __syncthreads();
+    interp(0, ec);
+    interp(1, em);
+    if (K0 == 0 && !per)
 #pragma unroll
         for (int r = 0; r < R; ++r) em[r] = slo * ec[r];
+    __syncthreads();
     for (int K = K0; K < K1; ++K) {
-        if (K + 1 < nzc || per) interp((K + 1) % nzc, ep);
-        else
+        const int h = K & 1;
+        double f0[R], f1[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            f0[r] = pf[c[r] + (long long)(2 * K) * kz];
+            f1[r] = pf[c[r] + (long long)(2 * K + 1) * kz];
+        }
+        stage(h);
+        fetch((K + 2) % nzc);
+        __syncthreads();
+        interp(h, ep);
+        if (K + 1 == nzc && !per)
 #pragma unroll
             for (int r = 0; r < R; ++r) ep[r] = shi * ec[r];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (!act[r]) continue;
-            const long long c = base + ((long long)t.z + ty + kRowsPerPass * r) * bf.nx + i;
-            pf[c + (2 * K) * kz] += 0.25 * em[r] + 0.75 * ec[r];
-            pf[c + (2 * K + 1) * kz] += 0.75 * ec[r] + 0.25 * ep[r];
+            pf[c[r] + (long long)(2 * K) * kz] = f0[r] + (0.25 * em[r] + 0.75 * ec[r]);
+            pf[c[r] + (long long)(2 * K + 1) * kz] = f1[r] + (0.75 * ec[r] + 0.25 * ep[r]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
