@@ -93,6 +93,23 @@ struct Roots<7> {
                                     -0.97492791218182360702, -0.78183148246802980871};
 };
 
+template <>
+struct Roots<9> {  // up to the product 2 * 2 of the 3 x 3 split
+    static constexpr double c[5] = {1.0, 0.76604444311897803520, 0.17364817766693034885, -0.5,
+                                    -0.93969262078590838405};
+    static constexpr double s[5] = {0.0, 0.64278760968653932632, 0.98480775301220805937, 0.86602540378443864676,
+                                    0.34202014332566873304};
+};
+template <>
+struct Roots<16> {  // up to the product 3 * 3 of the 4 x 4 split
+    static constexpr double c[10] = {1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173, 0.0,
+                                     -0.38268343236508977173, -0.70710678118654752440, -0.92387953251128675613, -1.0,
+                                     -0.92387953251128675613};
+    static constexpr double s[10] = {0.0, 0.38268343236508977173, 0.70710678118654752440, 0.92387953251128675613, 1.0,
+                                     0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173, 0.0,
+                                     -0.38268343236508977173};
+};
+
 // XCD-aware mapping: workgroups are dispatched round-robin over the 8 XCDs;
 // give each XCD one contiguous range of tiles so neighbouring tiles share an L2.
 __device__ __forceinline__ int xcd_remap(int g, int n) {
@@ -169,6 +186,44 @@ __device__ __forceinline__ void dft(double2* v, const TW& tw, int m) {
         }
 #pragma unroll
         for (int s = 0; s < R; ++s) v[s] = y[s];
+    } else if constexpr (R == 6 || R == 10 || R == 12 || R == 15) {
+        // coprime factors A B: sample (B r1 + A r2) mod R and output s with
+        // (s mod A, s mod B) make it an A x B transform without roots between
+        constexpr int A = R == 6 || R == 10 ? 2 : 3, B = R / A;
+        double2 y[A][B];
+#pragma unroll
+        for (int r2 = 0; r2 < B; ++r2) {
+            double2 u[A];
+#pragma unroll
+            for (int r1 = 0; r1 < A; ++r1) u[r1] = v[(B * r1 + A * r2) % R];
+            dft<A>(u, tw, m);
+#pragma unroll
+            for (int r1 = 0; r1 < A; ++r1) y[r1][r2] = u[r1];
+        }
+#pragma unroll
+        for (int s1 = 0; s1 < A; ++s1) dft<B>(y[s1], tw, m);
+#pragma unroll
+        for (int s = 0; s < R; ++s) v[s] = y[s % A][s % B];
+    } else if constexpr (R == 9 || R == 16) {
+        // A x A with the roots e^{-2 pi i r s / R} between
+        constexpr int A = R == 9 ? 3 : 4;
+        double2 y[A][A];
+#pragma unroll
+        for (int r2 = 0; r2 < A; ++r2) {
+            double2 u[A];
+#pragma unroll
+            for (int r1 = 0; r1 < A; ++r1) u[r1] = v[r1 * A + r2];
+            dft<A>(u, tw, m);
+#pragma unroll
+            for (int s1 = 0; s1 < A; ++s1)
+                y[s1][r2] = r2 * s1 ? cmul(u[s1], make_double2(Roots<R>::c[r2 * s1], -Roots<R>::s[r2 * s1])) : u[s1];
+        }
+#pragma unroll
+        for (int s1 = 0; s1 < A; ++s1) {
+            dft<A>(y[s1], tw, m);
+#pragma unroll
+            for (int s2 = 0; s2 < A; ++s2) v[s1 + A * s2] = y[s1][s2];
+        }
     } else {
         double2 y[R];
 #pragma unroll
@@ -544,16 +599,27 @@ __global__ void __launch_bounds__(256) k_r2r(FFTArgs a, const FTile* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Streaming form of the same transforms, for long power-of-two half lengths
-// (m >= 128).  A workgroup loops over tiles of W >= 16 columns (z rows read
-// and written as segments of 128 B or more), and the next tile's input is
-// loaded into registers, kStreamPer values per thread, while the current
-// tile is transformed and stored: the loads stay in flight through the LDS
-// phases.  Every table the loop reads is copied to LDS once per workgroup,
-// because a load from device memory issued after the prefetch would have to
-// wait for it.  The host sets NT = n W / kStreamPer, so every loop below has
-// a fixed trip count.
-constexpr int kStreamPer = 16;
+// Wide form of the same transforms, for half lengths of factors 2, 3, 5 and 7.
+// A workgroup loops over tiles of W columns (z rows are segments of 8 W bytes); the
+// next tile's input, 16 values a thread, is loaded into registers while the
+// current tile is transformed and stored.  All tables the loop reads are in LDS: a
+// load from device memory issued after the prefetch would wait for it.
+//
+// Bound by memory where two workgroups share a CU, by the LDS round trips of the
+// stages (barriers, index arithmetic, 48 B of LDS traffic a complex value) where n
+// is long.  Hence few stages of large radices (180 = 15 x 12, both in registers),
+// lanes along the columns (indices and roots are the same for W lanes, and an odd
+// column stride in complex values spreads a wave over the banks), division by the
+// stage's stride through a high product, bins k and m - k from one pair of values,
+// and for power-of-two lengths the first stage on the loaded values.  The finite
+// check is a running product with zero: a flag kept across the stages spilled.
+//
+// TB/s, forward and inverse alike, 32 million cells, N-N / periodic z, against one
+// pass per tile of short row segments with stages of radix 2 to 8:
+//   n         64   96  128  200  300  360  420  600  768 1024 1200 2048
+//   before   2.9  2.4  2.8  2.4  1.9  2.0  1.7  1.7  1.9  3.4  1.5  1.9
+//   now      4.4  4.2  4.2  4.0  3.6  3.7  3.6  3.2  3.1  3.3  2.6  2.9
+// ---------------------------------------------------------------------------
 
 // v, hidden from the optimiser: index arithmetic built on it is redone in
 // each phase of the tile loop instead of being hoisted out of the loop or
@@ -563,324 +629,275 @@ __device__ __forceinline__ int fresh(int v) {
     return v;
 }
 
-// Raw row of real position p of the sequence the forward FFT takes (the
-// inverse of the placement in k_r2r): PP keeps p; N-N / D-D undo Makhoul's
-// even / odd reordering; N-D undoes the quarter-wave packing, D-N that of the
-// reversed input.
-__device__ __forceinline__ int fwd_row(int kind, int n, int p) {
-    if (kind == Z_PP) return p;
-    if (kind == Z_NN || kind == Z_DD) return p < n / 2 ? 2 * p : 2 * (n - 1 - p) + 1;
-    const int kk = (p & 1) ? n - p : p;
-    return kind == Z_DN ? n - 1 - kk : kk;
-}
+struct SArgs {
+    int n, m, kind, lw, cs, nstage, groups;
+    int radix[8], ns[8], step[8];
+    unsigned magic[8];     // ceil(2^32 / ns): j / ns by the high product, j < 2^16
+    const double *tw, *t1, *t2;
+    int n1, n2;            // entries of t1 and t2
+    int first8;            // 1: the first stage, of radix 8, runs on the loaded values
+};
 
-// The thread's 16 inputs of a tile, gathered so that the first FFT stage
-// runs in registers.  Lanes run over the W columns first (tid mod W), so
-// every load of a wave reads whole row segments.
-//   Forward PP, N-D, D-N: the thread owns first-stage butterfly j = tid / W
-//   of its column, whose inputs are the complex values u = j + r m / 8,
-//   r < 8, each two real positions 2u, 2u + 1 (element 2r + parity).
-//   Forward N-N, D-D: element e is row e NT / W + tid / W.
-//   Inverse cosine kinds: for each of the thread's four groups (k, w) (group
-//   index g NT + tid, k < m / 2), the rows that Z_k and Z_{m-k} need, y at k,
-//   n - k, m - k, m + k (group 0: 0, m, m / 2, 3 m / 2, for Z_0 and Z_{m/2});
-//   rows count in the stored order, reversed for D-D.
-template <int NT>
-__device__ __forceinline__ void stream_load(double (&r)[kStreamPer], const double* __restrict__ in, const FTile& T,
-                                            int lw, int W, int n, int kind, bool inv_cos) {
-    const int tid = fresh(threadIdx.x);
-    // columns past the tile's last read that one (discarded later)
-    const int col = min(tid & (W - 1), T.ncol - 1);
-    const int m = n / 2;
-    const double* base = in + T.in_base + col;
-    if (!inv_cos && (kind == Z_NN || kind == Z_DD)) {
-        // N-N / D-D forward: plain rows e NT / W + tid / W (consecutive rows
-        // in a wave; the gathered order reads rows four apart, which measured
-        // slower), placed in the FFT's input order through LDS
-        const int lane = (tid >> lw) * T.in_stride + col;
-        const long long step = (long long)(NT >> lw) * T.in_stride;
-#pragma unroll
-        for (int e = 0; e < kStreamPer; ++e) r[e] = (in + T.in_base + e * step)[lane];
-        return;
-    }
-    if (!inv_cos) {
-        const int j = tid >> lw, nbf = m / 8;
-#pragma unroll
-        for (int e = 0; e < kStreamPer; ++e) {
-            const int p = 2 * (j + (e >> 1) * nbf) + (e & 1);
-            r[e] = base[(long long)fwd_row(kind, n, p) * T.in_stride];
-        }
-        return;
-    }
-    const bool rev = kind == Z_DD;
-#pragma unroll
-    for (int g = 0; g < kStreamPer / 4; ++g) {
-        const int k = (g * NT + tid) >> lw;
-        const int q[4] = {k, k == 0 ? m : n - k, k == 0 ? m / 2 : m - k, k == 0 ? m + m / 2 : m + k};
-#pragma unroll
-        for (int v = 0; v < 4; ++v) r[4 * g + v] = base[(long long)(rev ? n - 1 - q[v] : q[v]) * T.in_stride];
-    }
-}
+enum { F_PAIRS, F_COS, F_ICOS, F_QUARTER };
 
-// One Stockham stage of the streaming form (the same arithmetic as stage):
-// BPT = 8 / R butterflies per thread, consecutive lanes on consecutive
-// columns, so that the column stride (an odd number of complex values) spreads
-// every access of a wave over the LDS banks whatever the stage's output
-// stride.  The roots w^r of a butterfly are powers of one table value
-// (w^2 = w w, w^3 = w^2 w, ...; a few units in the last place), and the first
-// stage (Ns = 1) needs none.
-template <int R, int BPT, int NT>
-__device__ void stream_stage(double2* z, int cs, int m, int lw, int Ns, const double2* __restrict__ tw) {
-    const int nbf = m / R;
-    const int step = m / (Ns * R);
+// One Stockham stage over the tile, in place.
+template <int R>
+__device__ void wide_stage(double2* z, const SArgs& a, int s, const double2* __restrict__ tw, int nthr) {
+    constexpr int BPT = R >= 8 ? 1 : (8 + R - 1) / R;
+    const int nbf = a.m / R, Ns = a.ns[s], step = a.step[s];
+    const int total = nbf << a.lw;
+    const unsigned magic = a.magic[s];
     const int tid = fresh(threadIdx.x);
     double2 v[BPT][R];
     int dst[BPT];
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
-        const int b = tid + t * NT;
-        const int w = b & ((1 << lw) - 1), j = b >> lw;
-        const int jn = j >> (__ffs(Ns) - 1), k = j & (Ns - 1);  // Ns is a power of two
-        const double2* col = z + w * cs;
+        const int b = tid + t * nthr;
+        dst[t] = -1;
+        if (b < total) {
+            const int w = b & ((1 << a.lw) - 1), j = b >> a.lw;
+            const double2* col = z + w * a.cs + j;
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[t][r] = col[j + r * nbf];
-        if (Ns > 1) {
-            const double2 w1 = tw[k * step];
-            double2 wr = w1;
+            for (int r = 0; r < R; ++r) v[t][r] = col[r * nbf];
+            int k = 0;
+            if (s > 0) {
+                k = j - int(__umulhi(unsigned(j), magic)) * Ns;
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                v[t][r] = cmul(v[t][r], wr);
-                if (r + 1 < R) wr = cmul(wr, w1);
+                for (int r = 1; r < R; ++r) v[t][r] = cmul(v[t][r], tw[k * step * r]);
             }
+            dft<R>(v[t], GlobalTab{nullptr}, a.m);
+            dst[t] = w * a.cs + (j - k) * R + k;
         }
-        dft<R>(v[t], GlobalTab{nullptr}, m);
-        dst[t] = w * cs + jn * Ns * R + k;
     }
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
+        if (dst[t] < 0) continue;
 #pragma unroll
         for (int r = 0; r < R; ++r) z[dst[t] + r * Ns] = v[t][r];
     }
     __syncthreads();
 }
 
-// The Stockham stages of the streaming form: n W = kStreamPer NT gives every
-// thread 8 / R butterflies of each radix R.
-template <int NT>
-__device__ void fft_stream_columns(double2* z, int cs, const FFTArgs& a, const double2* tw, int first) {
-    const int lw = __ffs(a.W) - 1;
-    int Ns = 1;
-    for (int s = 0; s < first; ++s) Ns *= a.radix[s];
-    for (int s = first; s < a.nstage; ++s) {
-        const int R = a.radix[s];
-        if (R == 8) stream_stage<8, 1, NT>(z, cs, a.m, lw, Ns, tw);
-        else if (R == 4) stream_stage<4, 2, NT>(z, cs, a.m, lw, Ns, tw);
-        else stream_stage<2, 4, NT>(z, cs, a.m, lw, Ns, tw);
-        Ns *= R;
+// The thread's 16 inputs of a tile; lanes run over the columns first, so a wave
+// reads whole row segments.  With r0 = tid / W and a pass of NT / W rows:
+//   F_COS: rows r0 + e passes;
+//   F_PAIRS, F_QUARTER: the two real inputs of the FFT's complex input
+//     t = r0 + e passes: rows 2t and 2t + 1, or 2t and n - 1 - 2t (D-N: reversed);
+//   F_ICOS: for k = r0 + g passes the rows that Z_k and Z_{m-k} need, y at k, n - k,
+//     m - k, m + k (k = 0: 0, m, m / 2, 3 m / 2 for Z_0 and Z_{m/2}), reversed for D-D.
+// Lanes past the end repeat the last row, columns past the tile's last read that
+// one: all are discarded later.  Nothing here may use a loaded value, or the wave
+// would wait for it.
+template <int FORM>
+__device__ __forceinline__ void wide_load(double (&r)[kWidePer], const double* __restrict__ in, const FTile& T,
+                                          const SArgs& a, int nthr) {
+    const int tid = fresh(threadIdx.x);
+    const int W = 1 << a.lw, n = a.n, m = a.m, rpp = nthr >> a.lw;
+    const int col = min(tid & (W - 1), T.ncol - 1), r0 = tid >> a.lw;
+    const double* base = in + T.in_base + col;
+    if (FORM == F_COS) {
+#pragma unroll
+        for (int e = 0; e < kWidePer; ++e) r[e] = base[(long long)min(r0 + e * rpp, n - 1) * T.in_stride];
+    } else if (FORM == F_PAIRS || FORM == F_QUARTER) {
+#pragma unroll
+        for (int e = 0; e < kWidePer / 2; ++e) {
+            const int t = min(r0 + e * rpp, m - 1);
+            const int p = 2 * t, q = FORM == F_PAIRS ? 2 * t + 1 : n - 1 - 2 * t;
+            r[2 * e] = base[(long long)(a.kind == Z_DN ? q : p) * T.in_stride];
+            r[2 * e + 1] = base[(long long)(a.kind == Z_DN ? p : q) * T.in_stride];
+        }
+    } else {
+        const bool rev = a.kind == Z_DD;
+#pragma unroll
+        for (int g = 0; g < kWidePer / 4; ++g) {
+            const int k = min(r0 + g * rpp, a.groups - 1);
+            const int q[4] = {k, k == 0 ? m : n - k, k == 0 ? m / 2 : m - k, k == 0 ? m + m / 2 : m + k};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) r[4 * g + v] = base[(long long)(rev ? n - 1 - q[v] : q[v]) * T.in_stride];
+        }
     }
 }
 
-template <int NT>
-__global__ void __launch_bounds__(NT) k_r2r_stream(FFTArgs a, const FTile* __restrict__ tiles, int ntiles, int dir,
-                                                   const double* __restrict__ in, double* __restrict__ out,
-                                                   int* nonfinite) {
+template <int FORM>
+__global__ void __launch_bounds__(1024) k_wide(SArgs a, const FTile* __restrict__ tiles, int ntiles,
+                                                const double* __restrict__ in, double* __restrict__ out,
+                                                int* nonfinite) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double2* z = reinterpret_cast<double2*>(lds_raw);
-    const int n = a.n, m = a.m, W = a.W, cs = a.cs;
-    const int lw = __ffs(W) - 1;
-    const int kind = a.kind;
+    const int n = a.n, m = a.m, lw = a.lw, W = 1 << lw, cs = a.cs, nthr = blockDim.x, rpp = nthr >> lw;
     const double sc2 = sqrt(2.0 / n), sc1 = sqrt(1.0 / n);
-    const double isc2 = sqrt(0.5 * n), isc1 = sqrt(double(n));
-    const bool inv_cos = dir == 1 && (kind == Z_NN || kind == Z_DD);
-    const bool quarter = kind == Z_ND || kind == Z_DN;
-    const bool cosine = !inv_cos && (kind == Z_NN || kind == Z_DD);  // forward N-N / D-D
-    // tables behind the W-column image: tw (m values), then twn (m + 1) and
-    // post (m + 1; the bins above m use post[n - k] = -i conj(post[k])), or
-    // for the quarter-wave kinds pre4 (m) and post4 (m)
-    double2* twl = z + W * cs;
-    double2* t1 = twl + m;
-    double2* t2 = t1 + m + 1;
-    for (int i = threadIdx.x; i < m; i += NT) twl[i] = ld2(a.tw, i);
-    if (quarter) {
-        for (int i = threadIdx.x; i < m; i += NT) {
-            t1[i] = ld2(a.pre4, i);
-            t2[i] = ld2(a.post4, i);
-        }
-    } else {
-        for (int i = threadIdx.x; i <= m; i += NT) {
-            t1[i] = ld2(a.twn, i);
-            t2[i] = ld2(a.post, i);
-        }
-    }
-    __syncthreads();  // the first tile's placement already reads the tables
-
+    double2* tw = z + W * cs;
+    double2* t1 = tw + m;
+    double2* t2 = t1 + a.n1;
+    for (int i = threadIdx.x; i < m; i += nthr) tw[i] = ld2(a.tw, i);
+    for (int i = threadIdx.x; i < a.n1; i += nthr) t1[i] = ld2(a.t1, i);
+    for (int i = threadIdx.x; i < a.n2; i += nthr) t2[i] = ld2(a.t2, i);
+    __syncthreads();
     const int G = gridDim.x;
     int v = blockIdx.x;
     FTile T = tiles[xcd_remap(v, ntiles)];
-    double r[kStreamPer];
-    stream_load<NT>(r, in, T, lw, W, n, kind, inv_cos);
-    bool bad = false;
+    double r[kWidePer];
+    wide_load<FORM>(r, in, T, a, nthr);
     for (;;) {
-        // ---- this tile's input, registers -> LDS: the inverse cosine kinds
-        //      as Z_k (as in k_r2r) made from the gathered values; forward N-N
-        //      and D-D in the order the FFT takes (as in k_r2r); the other
-        //      forward kinds through the first FFT stage
         int tid = fresh(threadIdx.x);
-        if (inv_cos) {
-            const int w = tid & (W - 1);
+        {
+            double chk = 0.0;  // NaN once a value is not finite
+            const int w = tid & (W - 1), r0 = tid >> lw;
             const bool colok = w < T.ncol;
-            const int half = m / 2;
+            double2* zc = z + w * cs;
+            if (FORM == F_COS) {
 #pragma unroll
-            for (int g = 0; g < kStreamPer / 4; ++g) {
-                const int k = (g * NT + tid) >> lw;
-                // y'_q = y_q / c_q of the four gathered rows
-                const double y0 = colok ? r[4 * g] * (k == 0 ? isc1 : isc2) : 0.0;
-                const double y1 = colok ? r[4 * g + 1] * isc2 : 0.0;
-                const double y2 = colok ? r[4 * g + 2] * isc2 : 0.0;
-                const double y3 = colok ? r[4 * g + 3] * isc2 : 0.0;
-                // V_q = e^{i pi q/(2n)} (y'_q - i y'_{n-q});
-                // Z_q = conj((A + conj B) + i (A - conj B) e^{2 pi i q/n}), A = V_q, B = V_{m-q}
-                auto Z = [&](double2 A, double2 B, int q) -> double2 {
-                    const double2 Bc = cconj(B);
-                    const double2 sm = make_double2(A.x + Bc.x, A.y + Bc.y);
-                    const double2 d = make_double2(A.x - Bc.x, A.y - Bc.y);
-                    const double2 id = cmul(make_double2(-d.y, d.x), cconj(t1[q]));
-                    return cconj(make_double2(sm.x + id.x, sm.y + id.y));
-                };
-                double2* zc = z + w * cs;
-                if (k > 0) {
-                    const double2 A = cmul(cconj(t2[k]), make_double2(y0, -y1));       // V_k
-                    const double2 B = cmul(cconj(t2[m - k]), make_double2(y2, -y3));   // V_{m-k}
-                    zc[k] = Z(A, B, k);
-                    zc[m - k] = Z(B, A, m - k);
+                for (int e = 0; e < kWidePer; ++e) {
+                    const int k = r0 + e * rpp;
+                    const double x = colok ? r[e] : 0.0;
+                    chk = fma(x, 0.0, chk);
+                    const int u = (k & 1) ? n - 1 - (k >> 1) : (k >> 1);
+                    if (k < n) reinterpret_cast<double*>(zc)[u] = (a.kind == Z_DD && (k & 1)) ? -x : x;
+                }
+            } else if (FORM == F_PAIRS || FORM == F_QUARTER) {
+                double2 x[kWidePer / 2];
+#pragma unroll
+                for (int e = 0; e < kWidePer / 2; ++e) {
+                    x[e] = make_double2(colok ? r[2 * e] : 0.0, colok ? r[2 * e + 1] : 0.0);
+                    chk = fma(x[e].y, 0.0, fma(x[e].x, 0.0, chk));
+                }
+                if (a.first8) {  // rpp = m / 8: the thread holds a butterfly of the first stage
+                    if (FORM == F_QUARTER)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) x[e] = cmul(x[e], t1[r0 + e * rpp]);
+                    dft<8>(x, GlobalTab{nullptr}, m);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) zc[8 * r0 + e] = x[e];
                 } else {
-                    const double2 A = cmul(cconj(t2[0]), make_double2(y0, 0.0));      // V_0
-                    const double2 B = cmul(cconj(t2[m]), make_double2(y1, -y1));      // V_m
-                    const double2 H = cmul(cconj(t2[half]), make_double2(y2, -y3));   // V_{m/2}
-                    zc[0] = Z(A, B, 0);
-                    zc[half] = Z(H, H, half);
+#pragma unroll
+                    for (int e = 0; e < kWidePer / 2; ++e)
+                        if (r0 + e * rpp < m)
+                            zc[r0 + e * rpp] = FORM == F_QUARTER ? cmul(x[e], t1[r0 + e * rpp]) : x[e];
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < kWidePer / 4; ++g) {
+                    const int k = r0 + g * rpp;
+                    if (k >= a.groups) continue;
+                    const double y0 = colok ? r[4 * g] * (k == 0 ? 1.41421356237309504880 : 1.0) : 0.0;
+                    const double y1 = colok ? r[4 * g + 1] : 0.0;
+                    const double y2 = colok ? r[4 * g + 2] : 0.0;
+                    const double y3 = colok ? r[4 * g + 3] : 0.0;
+                    // V_q = e^{i pi q/(2n)} (y'_q - i y'_{n-q}), y'_0 = sqrt(2) y_0 (the common
+                    // factor waits for the store); with A = V_k, B = V_{m-k},
+                    // s = A + conj B and t = i (A - conj B) e^{2 pi i k/n}:
+                    // Z_k = conj(s + t), Z_{m-k} = s - t
+                    const double2 A = cmul(cconj(t2[k]), make_double2(y0, k == 0 ? 0.0 : -y1));
+                    const double2 B = k == 0 ? cmul(cconj(t2[m]), make_double2(y1, -y1))
+                                             : cmul(cconj(t2[m - k]), make_double2(y2, -y3));
+                    const double2 sm = make_double2(A.x + B.x, A.y - B.y), d = make_double2(A.x - B.x, A.y + B.y);
+                    const double2 t = cmul(make_double2(-d.y, d.x), cconj(t1[k]));
+                    zc[k] = make_double2(sm.x + t.x, -(sm.y + t.y));
+                    if (k > 0) {
+                        zc[m - k] = make_double2(sm.x - t.x, sm.y - t.y);
+                    } else if ((m & 1) == 0) {  // Z_{m/2} of A = B
+                        const double2 H = cmul(cconj(t2[m / 2]), make_double2(y2, -y3));
+                        const double2 th = cmul(make_double2(-2.0 * H.y, 0.0), cconj(t1[m / 2]));
+                        zc[m / 2] = make_double2(2.0 * H.x + th.x, -th.y);
+                    }
                 }
             }
-        } else if (cosine) {
-#pragma unroll
-            for (int e = 0; e < kStreamPer; ++e) {
-                const int idx = e * NT + tid;
-                const int k = idx >> lw, w = idx & (W - 1);
-                const double x = w >= T.ncol ? 0.0 : r[e];
-                if (!isfinite(x)) bad = true;
-                const int u = (k & 1) ? n - 1 - (k >> 1) : (k >> 1);
-                reinterpret_cast<double*>(z + w * cs)[u] = (kind == Z_DD && (k & 1)) ? -x : x;
-            }
-        } else {
-            // the first radix-8 stage (Ns = 1: no twiddles) on the gathered
-            // values, written to its Stockham output positions 8 j + r
-            const int w = tid & (W - 1), j = tid >> lw, nbf = m / 8;
-            const bool colok = w < T.ncol;
-            double2 zin[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int u = j + q * nbf;
-                double re = colok ? r[2 * q] : 0.0, im = colok ? r[2 * q + 1] : 0.0;
-                if (!isfinite(re) || !isfinite(im)) bad = true;
-                zin[q] = make_double2(re, im);
-                if (quarter) zin[q] = cmul(zin[q], t1[u]);
-            }
-            dft<8>(zin, GlobalTab{nullptr}, m);
-            double2* zc = z + w * cs + 8 * j;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) zc[q] = zin[q];
+            if (FORM != F_ICOS && chk != 0.0 && nonfinite) atomicOr(nonfinite, 1);
         }
-        // ---- the next tile's loads, in flight while this one is transformed
         const int vn = v + G;
         FTile Tn = T;
         if (vn < ntiles) {
             Tn = tiles[xcd_remap(vn, ntiles)];
-            stream_load<NT>(r, in, Tn, lw, W, n, kind, inv_cos);
+            wide_load<FORM>(r, in, Tn, a, nthr);
         }
         __syncthreads();
-
-        fft_stream_columns<NT>(z, cs, a, twl, (inv_cos || cosine) ? 0 : 1);
+        for (int s = a.first8; s < a.nstage; ++s) {
+            switch (a.radix[s]) {
+                case 2: wide_stage<2>(z, a, s, tw, nthr); break;
+                case 3: wide_stage<3>(z, a, s, tw, nthr); break;
+                case 4: wide_stage<4>(z, a, s, tw, nthr); break;
+                case 5: wide_stage<5>(z, a, s, tw, nthr); break;
+                case 6: wide_stage<6>(z, a, s, tw, nthr); break;
+                case 7: wide_stage<7>(z, a, s, tw, nthr); break;
+                case 8: wide_stage<8>(z, a, s, tw, nthr); break;
+                case 9: wide_stage<9>(z, a, s, tw, nthr); break;
+                case 10: wide_stage<10>(z, a, s, tw, nthr); break;
+                case 12: wide_stage<12>(z, a, s, tw, nthr); break;
+                case 15: wide_stage<15>(z, a, s, tw, nthr); break;
+                default: wide_stage<16>(z, a, s, tw, nthr); break;
+            }
+        }
         tid = fresh(threadIdx.x);
-
-        if (inv_cos) {
-            const double inv_n = 1.0 / n;
+        const int w = tid & (W - 1), r0 = tid >> lw;
+        const double2* zc = z + w * cs;
+        double* o = out + T.out_base + w;
+        const long long st = T.out_stride;
+        if (w < T.ncol) {
+            if (FORM == F_ICOS) {
+                const double scale = sqrt(0.5 / n);
 #pragma unroll
-            for (int e = 0; e < kStreamPer; ++e) {
-                const int idx = e * NT + tid;
-                const int j = idx >> lw, w = idx & (W - 1);
-                const int u = (j & 1) ? n - 1 - (j >> 1) : (j >> 1);
-                const double2 F = z[w * cs + (u >> 1)];
-                double y = (u & 1) ? -F.y * inv_n : F.x * inv_n;
-                if (kind == Z_DD && (j & 1)) y = -y;
-                if (w < T.ncol) out[T.out_base + (long long)j * T.out_stride + w] = y;
-            }
-        } else if (quarter) {
+                for (int e = 0; e < kWidePer; ++e) {
+                    const int j = r0 + e * rpp;
+                    if (j >= n) continue;
+                    const int u = (j & 1) ? n - 1 - (j >> 1) : (j >> 1);
+                    const double y = reinterpret_cast<const double*>(zc)[u] * scale;
+                    const bool neg = ((u & 1) != 0) != (a.kind == Z_DD && (j & 1));  // conjugate; (-1)^j of D-D
+                    o[j * st] = neg ? -y : y;
+                }
+            } else if (FORM == F_QUARTER) {
 #pragma unroll
-            for (int e = 0; e < kStreamPer / 2; ++e) {
-                const int idx = e * NT + tid;
-                const int k = idx >> lw, w = idx & (W - 1);
-                const double2 u = cmul(z[w * cs + k], t2[k]);
-                const int q0 = 2 * k, q1 = n - 1 - 2 * k;
-                double y0 = sc2 * u.x, y1 = -sc2 * u.y;
-                if (kind == Z_DN) {
-                    if (q0 & 1) y0 = -y0;
-                    if (q1 & 1) y1 = -y1;
+                for (int e = 0; e < kWidePer / 2; ++e) {
+                    const int k = r0 + e * rpp;
+                    if (k >= m) continue;
+                    const double2 u = cmul(zc[k], t2[k]);
+                    const int q0 = 2 * k, q1 = n - 1 - 2 * k;  // even and odd
+                    o[q0 * st] = sc2 * u.x;
+                    o[q1 * st] = a.kind == Z_DN ? sc2 * u.y : -sc2 * u.y;
                 }
-                if (w < T.ncol) {
-                    out[T.out_base + (long long)q0 * T.out_stride + w] = y0;
-                    out[T.out_base + (long long)q1 * T.out_stride + w] = y1;
-                }
-            }
-        } else {
-            // PP / NN / DD: bins k < m give the outputs at k and n - k (as in
-            // k_r2r); bin 0's group also gives bin m.  m W = 8 NT groups.
-            const bool pp = kind == Z_PP, dd = kind == Z_DD;
+            } else {
+                const bool dd = a.kind == Z_DD;
 #pragma unroll
-            for (int e = 0; e < kStreamPer / 2; ++e) {
-                const int idx = e * NT + tid;
-                const int k = idx >> lw, w = idx & (W - 1);
-                // bin q's real DFT value X_q from the half-length FFT
-                auto Xq = [&](int q) -> double2 {
-                    const double2 Zk = z[w * cs + (q == m ? 0 : q)];
-                    const double2 Zc = cconj(z[w * cs + (q == 0 ? 0 : m - q)]);
-                    const double2 sm = make_double2(0.5 * (Zk.x + Zc.x), 0.5 * (Zk.y + Zc.y));
-                    const double2 d = make_double2(0.5 * (Zk.x - Zc.x), 0.5 * (Zk.y - Zc.y));
-                    const double2 t = cmul(t1[q], d);
-                    return make_double2(sm.x + t.y, sm.y - t.x);
-                };
-                // output at row rk of bin q (the only one for q = 0 and q = m)
-                auto first = [&](int q, const double2& X) -> double {
-                    const double2 pk = t2[q];
-                    return pp ? sc1 * (X.x - X.y) : (q == 0 ? sc1 : sc2) * (pk.x * X.x - pk.y * X.y);
-                };
-                const double2 X = Xq(k);
-                const double ya = first(k, X);
-                const int ra = dd ? n - 1 - k : k;
-                double yb;
-                int rb;
-                if (k == 0) {
-                    yb = first(m, Xq(m));
-                    rb = dd ? n - 1 - m : m;
-                } else {
-                    const double2 pk = t2[k];
-                    const double2 pn = make_double2(-pk.y, -pk.x);  // post[n - k]
-                    yb = pp ? sc1 * (X.x + X.y) : sc2 * (pn.x * X.x + pn.y * X.y);
-                    rb = pp ? n - k : dd ? k - 1 : n - k;
-                }
-                if (w < T.ncol) {
-                    double* o = out + T.out_base + w;
-                    o[(long long)ra * T.out_stride] = ya;
-                    o[(long long)rb * T.out_stride] = yb;
+                for (int g = 0; g < kWidePer / 4; ++g) {
+                    const int k = r0 + g * rpp;
+                    if (k >= a.groups) continue;
+                    auto put = [&](int row, double y) { o[(dd ? n - 1 - row : row) * st] = y; };
+                    // outputs q and n - q of the real DFT value X_q
+                    auto both = [&](int q, double2 X) {
+                        if (FORM == F_PAIRS) {
+                            put(q, sc1 * (X.x - X.y));
+                            put(n - q, sc1 * (X.x + X.y));
+                        } else {
+                            const double2 p = t2[q];  // post[n - q] = -i conj(post[q])
+                            put(q, sc2 * (p.x * X.x - p.y * X.y));
+                            put(n - q, -sc2 * (p.y * X.x + p.x * X.y));
+                        }
+                    };
+                    const double2 Z = zc[k];
+                    if (k > 0) {
+                        const double2 Y = zc[m - k];
+                        const double2 s = make_double2(0.5 * (Z.x + Y.x), 0.5 * (Z.y - Y.y));
+                        const double2 d = make_double2(0.5 * (Z.x - Y.x), 0.5 * (Z.y + Y.y));
+                        const double2 t = cmul(t1[k], d);
+                        both(k, make_double2(s.x + t.y, s.y - t.x));
+                        both(m - k, make_double2(s.x - t.y, -s.y - t.x));
+                    } else {
+                        const double x0 = Z.x + Z.y, xm = Z.x - Z.y;
+                        put(0, sc1 * x0);
+                        put(m, FORM == F_PAIRS ? sc1 * xm : sc2 * t2[m].x * xm);
+                        if ((m & 1) == 0) {
+                            const double2 H = zc[m / 2];
+                            both(m / 2, make_double2(H.x, -H.y));
+                        }
+                    }
                 }
             }
         }
         if (vn >= ntiles) break;
-        __syncthreads();  // the next tile overwrites the image
+        __syncthreads();
         T = Tn;
         v = vn;
     }
-    if (bad && nonfinite) atomicOr(nonfinite, 1);
 }
 
 int fft_col_stride(const mbp_plan* P);
@@ -907,30 +924,8 @@ static int fft_width_for(const mbp_plan* P, int64_t lds) {
     return W;
 }
 
-static int radix_class(const mbp_plan* P);
-
-// Streaming form: power-of-two half lengths m >= 128, W the widest power of
-// two in [16, 64] with NT = n W / kStreamPer <= MBP_FFT_STREAM_MAXNT threads
-// and the image plus the tables (3 m + 2 values) in the LDS limit; 0 when the
-// form does not apply (the per-tile kernel runs).
-#ifndef MBP_FFT_STREAM_MAXNT
-#define MBP_FFT_STREAM_MAXNT 1024
-#endif
-static int stream_width(const mbp_plan* P) {
-    const int n = P->fft.n, m = P->fft.m;
-    if (radix_class(P) != 0 || m < 128 || P->fft.radices[0] != 8) return 0;
-    const int cs = fft_col_stride(P);
-    for (int W = 64; W >= 16; W >>= 1) {
-        const int nt = n * W / kStreamPer;
-        if (nt > MBP_FFT_STREAM_MAXNT || nt < 256) continue;
-        if ((int64_t(W) * cs + 3 * m + 2) * 16 <= P->lds_limit) return W;
-    }
-    return 0;
-}
-
 int fft_columns_per_wg(const mbp_plan* P) {
-    const int Ws = stream_width(P);
-    if (Ws) return Ws;
+    if (P->fft.W) return P->fft.W;
     const int W = fft_width_for(P, kFFTLdsSmall);
     return W >= 8 ? W : fft_width_for(P, kFFTLds);
 }
@@ -992,7 +987,7 @@ static FFTArgs make_args(const mbp_plan* P) {
 
 static size_t lds_bytes(const mbp_plan* P) {
     const size_t img = size_t(fft_columns_per_wg(P)) * fft_col_stride(P);
-    return (stream_width(P) ? img + 3 * size_t(P->fft.m) + 2 : img) * sizeof(double2);
+    return img * sizeof(double2);
 }
 
 static int radix_class(const mbp_plan* P) {
@@ -1016,56 +1011,79 @@ static void launch_r2r(const mbp_plan* P, const FFTArgs& a, const void* tiles, i
                        reinterpret_cast<const FTile*>(tiles), P->fft_ntiles, dir, in, out, nonfinite);
 }
 
-template <int NT>
-static void launch_stream(const mbp_plan* P, const FFTArgs& a, const void* tiles, int dir, const double* in,
-                          double* out, int* nonfinite, hipStream_t s) {
-    const size_t bytes = lds_bytes(P);
-    if (bytes > 64 * 1024)
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_r2r_stream<NT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-    hipLaunchKernelGGL(k_r2r_stream<NT>, dim3(P->fft_grid), dim3(NT), bytes, s, a,
-                       reinterpret_cast<const FTile*>(tiles), P->fft_ntiles, dir, in, out, nonfinite);
+static const void* wide_fn(int form) {
+    return form == F_PAIRS    ? reinterpret_cast<const void*>(k_wide<F_PAIRS>)
+           : form == F_COS    ? reinterpret_cast<const void*>(k_wide<F_COS>)
+           : form == F_ICOS   ? reinterpret_cast<const void*>(k_wide<F_ICOS>)
+                              : reinterpret_cast<const void*>(k_wide<F_QUARTER>);
+}
+static int wide_form(int kind, int dir) {
+    return kind == Z_PP ? F_PAIRS : kind == Z_ND || kind == Z_DN ? F_QUARTER : dir ? F_ICOS : F_COS;
 }
 
-// Launch shape of the streaming form on the current device: the thread count
-// and a grid of as many workgroups as fit on the chip at once (a multiple of
+// A grid of as many workgroups as fit on the current device at once (a multiple of
 // 8, so each keeps its XCD's share of tiles), at most one per tile.
-int fft_stream_setup(mbp_plan* P) {
-    P->fft_stream_nt = 0;
-    P->fft_grid = 0;
-    const int W = stream_width(P);
-    if (!W) return MBP_OK;
-    const int nt = P->fft.n * W / kStreamPer;
-    const size_t bytes = lds_bytes(P);
-    const void* fn = nt == 256    ? reinterpret_cast<const void*>(k_r2r_stream<256>)
-                     : nt == 512 ? reinterpret_cast<const void*>(k_r2r_stream<512>)
-                                 : reinterpret_cast<const void*>(k_r2r_stream<1024>);
-    if (bytes > 64 * 1024 &&
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess)
-        return MBP_ERR_HIP;
-    int dev = 0, ncu = 0, per = 0;
+int fft_setup_grid(mbp_plan* P) {
+    FFTPlan& F = P->fft;
+    if (!F.W) return MBP_OK;
+    int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, bytes) != hipSuccess)
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return MBP_ERR_HIP;
-    int g = std::min<int64_t>(P->fft_ntiles, int64_t(std::max(per, 1)) * std::max(ncu, 1));
-    if (g >= 8) g -= g % 8;
-    P->fft_stream_nt = nt;
-    P->fft_grid = std::max(g, 1);
+    for (int dir = 0; dir < 2; ++dir) {
+        const void* fn = wide_fn(wide_form(P->g.zkind, dir));
+        const size_t bytes = F.bytes;
+        int per = 0;
+        if (bytes > 64 * 1024 &&
+            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess)
+            return MBP_ERR_HIP;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, F.nt, bytes) != hipSuccess) return MBP_ERR_HIP;
+        int g = std::min<int64_t>(P->fft_ntiles, int64_t(std::max(per, 1)) * std::max(ncu, 1));
+        if (g >= 8) g -= g % 8;
+        F.grid[dir] = std::max(g, 1);
+    }
     return MBP_OK;
+}
+
+static void run_wide(const mbp_plan* P, const void* tiles, int dir, const double* in, double* out, int* nonfinite,
+                     hipStream_t s) {
+    const FFTPlan& F = P->fft;
+    SArgs a{};
+    a.n = F.n;
+    a.m = F.m;
+    a.kind = P->g.zkind;
+    a.lw = __builtin_ctz(unsigned(F.W));
+    a.cs = F.m | 1;
+    a.nstage = int(F.wide.size());
+    a.first8 = F.first8;
+    for (int i = 0, Ns = 1; i < a.nstage; ++i) {
+        a.radix[i] = F.wide[i];
+        a.ns[i] = Ns;
+        a.step[i] = a.m / (Ns * F.wide[i]);
+        a.magic[i] = unsigned(((1ull << 32) + Ns - 1) / Ns);
+        Ns *= F.wide[i];
+    }
+    const bool quarter = a.kind == Z_ND || a.kind == Z_DN;
+    a.groups = (a.m + 1) / 2;
+    a.tw = P->d_dbl + P->fft_tw;
+    a.t1 = P->d_dbl + (quarter ? P->fft_pre4 : P->fft_twn);
+    a.n1 = quarter ? a.m : a.m / 2 + 1;
+    a.t2 = P->d_dbl + (quarter ? P->fft_post4 : P->fft_post);
+    a.n2 = quarter ? a.m : a.kind == Z_PP ? 0 : a.m + 1;
+    const size_t bytes = F.bytes;
+    const void* fn = wide_fn(wide_form(a.kind, dir));
+    if (bytes > 64 * 1024)
+        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+    const FTile* tl = reinterpret_cast<const FTile*>(tiles);
+    int ntiles = P->fft_ntiles;
+    void* args[] = {&a, &tl, &ntiles, &in, &out, &nonfinite};
+    (void)hipLaunchKernel(fn, dim3(F.grid[dir]), dim3(F.nt), args, bytes, s);
 }
 
 static void run_r2r(const mbp_plan* P, const void* tiles, int dir, const double* in, double* out,
                     int* nonfinite, hipStream_t s) {
+    if (P->fft.W) return run_wide(P, tiles, dir, in, out, nonfinite, s);
     const FFTArgs a = make_args(P);
-    if (P->fft_stream_nt) {
-        switch (P->fft_stream_nt) {
-            case 256: launch_stream<256>(P, a, tiles, dir, in, out, nonfinite, s); break;
-            case 512: launch_stream<512>(P, a, tiles, dir, in, out, nonfinite, s); break;
-            default: launch_stream<1024>(P, a, tiles, dir, in, out, nonfinite, s); break;
-        }
-        return;
-    }
     switch (radix_class(P)) {
         case 0: launch_r2r<0>(P, a, tiles, dir, in, out, nonfinite, s); break;
         case 1: launch_r2r<1>(P, a, tiles, dir, in, out, nonfinite, s); break;

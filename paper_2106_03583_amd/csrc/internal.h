@@ -118,9 +118,17 @@ struct CoarseInfo {
 };
 constexpr int kCoarseInLds = 32;  // coarsest planes up to this many cells have their matrices in LDS
 
+constexpr int kWidePer = 16;  // values a thread of the wide transform holds
+
 struct FFTPlan {
     int n = 0, m = 0;              // real length, complex length n/2
     std::vector<int> radices;      // Stockham stages, product = m
+    // the wide form (fft.hip); W = 0 where it does not apply
+    int W = 0, nt = 0;             // columns of a tile, threads of its workgroup
+    std::vector<int> wide;         // its stages
+    int first8 = 0;                // the first of them runs on the loaded values
+    size_t bytes = 0;              // LDS
+    int grid[2] = {0, 0};          // workgroups, forward and inverse
 };
 
 }  // namespace mbp
@@ -144,7 +152,6 @@ struct mbp_plan {
     mbp::FFTPlan fft;
     int fft_tw = 0, fft_twn = 0, fft_post = 0, fft_pre4 = 0, fft_post4 = 0;  // double-pool offsets
     int fft_ntiles = 0;
-    int fft_stream_nt = 0, fft_grid = 0;  // streaming transform: threads per workgroup, grid (0 = per-tile kernel)
     void* d_ftiles_fwd = nullptr;
     void* d_ftiles_inv = nullptr;
     int64_t lds_limit = 64 * 1024;  // LDS bytes one workgroup may use
@@ -236,7 +243,7 @@ int grid_tanh(int n, double lmin, double lmax, int type, double factor, double* 
 // fft.hip (host helpers)
 int fft_columns_per_wg(const mbp_plan* P);
 int fft_col_stride(const mbp_plan* P);
-int fft_stream_setup(mbp_plan* P);
+int fft_setup_grid(mbp_plan* P);  // the wide form's launch on the current device; after the tiles are known
 void fft_build_tiles(const mbp_plan* P, std::vector<unsigned char>& fwd, std::vector<unsigned char>& inv,
                      int* ntiles);
 

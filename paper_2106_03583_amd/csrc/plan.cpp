@@ -240,6 +240,70 @@ std::vector<int> fft_radices(int m) {
     return r;
 }
 
+// Stage radices of the wide form for half length m: the list of least cost, a
+// stage of radix R taking its register slots (R per butterfly, butterflies per
+// thread rounded up) and eight for its barriers and index arithmetic.
+static bool wide_search(int m, int from, int cost, std::vector<int>& cur, std::vector<int>& best, int& best_cost) {
+    static const int R[12] = {16, 15, 12, 10, 9, 8, 7, 6, 5, 4, 3, 2};
+    if (m == 1) {
+        if (cost < best_cost) best_cost = cost, best = cur;
+        return true;
+    }
+    if (cur.size() == 8) return false;
+    bool any = false;
+    for (int i = from; i < 12; ++i) {
+        if (m % R[i]) continue;
+        cur.push_back(R[i]);
+        any |= wide_search(m / R[i], i, cost + 8 + R[i] * (R[i] >= 8 ? 1 : (8 + R[i] - 1) / R[i]), cur, best, best_cost);
+        cur.pop_back();
+    }
+    return any;
+}
+
+static int wide_threads(int n, int W) { return (n * W / kWidePer + 63) / 64 * 64; }
+
+// LDS of a workgroup: the image, the roots of the stages, and the form's tables
+static int64_t wide_bytes(const mbp_plan* P, int W) {
+    const int m = P->fft.m, kind = P->g.zkind;
+    const bool quarter = kind == Z_ND || kind == Z_DN;
+    return (int64_t(W) * (m | 1) + m + (quarter ? 2 * m : m / 2 + 1 + (kind == Z_PP ? 0 : m + 1))) * 16;
+}
+
+// The wide form runs half lengths of factors 2, 3, 5 and 7 only (the butterflies it
+// has).  W: the widest tile of up to 64 columns with at most 512 threads, as
+// longer row segments and several workgroups a CU beat more threads in one (n = 96:
+// 4.2 / 4.3 / 3.8 TB/s with 64 / 32 / 16 columns; 200: 4.1 with 32, 3.9 with 16;
+// 320: 3.5 with 16, 512 threads' limit); then 16 columns with up to 1024 threads, then
+// 8 (n = 1200: 2.7 against 1.5 TB/s for the per-tile kernel, which takes what
+// needs more LDS than there is).
+static void wide_setup(mbp_plan* P) {
+    FFTPlan& F = P->fft;
+    F.W = 0;
+    std::vector<int> cur, best;
+    int cost = 1 << 30;
+    if (!wide_search(F.m, 0, 0, cur, best, cost)) return;
+    int W = 64;
+    while (W > 16 && (wide_threads(F.n, W) > 512 || wide_bytes(P, W) > P->lds_limit)) W >>= 1;
+    while (W >= 8 && (wide_threads(F.n, W) > 1024 || wide_bytes(P, W) > P->lds_limit)) W >>= 1;
+    if (W < 8) return;
+    F.W = W;
+    F.nt = wide_threads(F.n, W);
+    F.bytes = size_t(wide_bytes(P, W));
+    F.wide = best;
+    F.first8 = 0;
+    // the first stage on the loaded values saves its pass through LDS
+    const bool cosine = P->g.zkind == Z_NN || P->g.zkind == Z_DD;
+    if (!cosine && F.m % 8 == 0 && F.nt / W == F.m / 8) {
+        std::vector<int> rest;
+        int c8 = 1 << 30;
+        if (wide_search(F.m / 8, 0, 8, cur, rest, c8) && c8 < cost && rest.size() < 8) {
+            F.wide.assign(1, 8);
+            F.wide.insert(F.wide.end(), rest.begin(), rest.end());
+            F.first8 = 1;
+        }
+    }
+}
+
 }  // namespace
 
 // Modal shifts of Eq. (9), sigma_q = lambda_q / dz^2 - alpha, with alpha >= 0
@@ -902,6 +966,7 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
     P->fft.n = nz;
     P->fft.m = nz / 2;
     P->fft.radices = fft_radices(P->fft.m);
+    wide_setup(P);
 
     {
         const long double PI = 3.14159265358979323846264338327950288L;
