@@ -314,7 +314,6 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
             break;
         }
         (void)hipEventRecord(t1, s);
-        for (int i : act) ctx_state_readback(cx[i], s);
         if (hipStreamSynchronize(s) != hipSuccess) {
             fail(MBP_ERR_HIP);
             break;

@@ -801,6 +801,8 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
         tabs[k].assign(size_t(ne) * kTab, 0.0);
         const bool transfer = k + 1 < nl;
         std::vector<CRec> byc[4];
+        byc[0].reserve(transfer ? cl.ncell / 2 + nb : cl.ncell);
+        if (transfer) byc[1].reserve(cl.ncell / 2 + nb);
         for (int b = 0; b < nb; ++b) {
             const DBlock& d = P->hblk[F.blk_off + b];
             auto entry = [&](int e, int c, int n, int i, int rw, int pw) {
@@ -820,6 +822,13 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
                     CRec r{};
                     const int self = d.off + j * d.nx + i;
                     r.self = (unsigned short)self;
+                    const bool inner = i > 0 && i < d.nx - 1 && j > 0 && j < d.ny - 1;
+                    if (inner) {
+                        r.n[0] = (unsigned short)(self - 1);
+                        r.n[1] = (unsigned short)(self + 1);
+                        r.n[2] = (unsigned short)(self - d.nx);
+                        r.n[3] = (unsigned short)(self + d.nx);
+                    }
                     auto other = [&](int f, int ii, int jj) {
                         if (ii >= 0 && ii < d.nx && jj >= 0 && jj < d.ny) return d.off + jj * d.nx + ii;
                         const int o = d.nbr[f];
@@ -827,17 +836,19 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
                         const DBlock& e = P->hblk[F.blk_off + o];
                         return e.off + (f == YM ? e.ny - 1 : f == YP ? 0 : j) * e.nx + (f == XM ? e.nx - 1 : f == XP ? 0 : i);
                     };
-                    r.n[0] = (unsigned short)other(XM, i - 1, j);
-                    r.n[1] = (unsigned short)other(XP, i + 1, j);
-                    r.n[2] = (unsigned short)other(YM, i, j - 1);
-                    r.n[3] = (unsigned short)other(YP, i, j + 1);
-                    // a missing neighbour (coupling zero) stands for one that exists, of
-                    // the other colour: the cell itself may not be written yet
-                    int some = self;
-                    for (int k4 = 0; k4 < 4; ++k4)
-                        if (r.n[k4] != self) some = r.n[k4];
-                    for (int k4 = 0; k4 < 4; ++k4)
-                        if (r.n[k4] == self) r.n[k4] = (unsigned short)some;
+                    if (!inner) {
+                        r.n[0] = (unsigned short)other(XM, i - 1, j);
+                        r.n[1] = (unsigned short)other(XP, i + 1, j);
+                        r.n[2] = (unsigned short)other(YM, i, j - 1);
+                        r.n[3] = (unsigned short)other(YP, i, j + 1);
+                        // a missing neighbour (coupling zero) stands for one that exists, of
+                        // the other colour: the cell itself may not be written yet
+                        int some = self;
+                        for (int k4 = 0; k4 < 4; ++k4)
+                            if (r.n[k4] != self) some = r.n[k4];
+                        for (int k4 = 0; k4 < 4; ++k4)
+                            if (r.n[k4] == self) r.n[k4] = (unsigned short)some;
+                    }
                     r.xi = (unsigned short)(xb[b] + i);
                     r.yi = (unsigned short)(yb[b] + j);
                     const int patch = pg[2 * b] + (j / 2) * pg[2 * b + 1] + i / 2;
@@ -845,7 +856,16 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
                     if (transfer) {
                         const Level& C = P->levels[L + k + 1];
                         const int I = P->hint[d.pcx + i], J = P->hint[d.pcy + j];
-                        for (int c = 0; c < 4; ++c) r.c[c] = coarse_ref(P, C, b, I + (c & 1), J + (c >> 1));
+                        const DBlock& e = P->hblk[C.blk_off + b];
+                        if (I >= 0 && I + 1 < e.nx && J >= 0 && J + 1 < e.ny) {
+                            const int at = e.off + J * e.nx + I;
+                            r.c[0] = (unsigned short)at;
+                            r.c[1] = (unsigned short)(at + 1);
+                            r.c[2] = (unsigned short)(at + e.nx);
+                            r.c[3] = (unsigned short)(at + e.nx + 1);
+                        } else {
+                            for (int c = 0; c < 4; ++c) r.c[c] = coarse_ref(P, C, b, I + (c & 1), J + (c >> 1));
+                        }
                     }
                     if (k > 0) {
                         const Level& U = P->levels[L + k - 1];
@@ -868,6 +888,7 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
         cl.n1 = int(byc[1].size());
         cl.n2 = int(byc[2].size());
         cl.n3 = int(byc[3].size());
+        recs[k].reserve(cl.ncell);
         for (const auto& v : byc) recs[k].insert(recs[k].end(), v.begin(), v.end());
         place[k].resize(cl.ncell);
         for (int i = 0; i < cl.ncell; ++i) place[k][recs[k][i].self] = (unsigned short)i;

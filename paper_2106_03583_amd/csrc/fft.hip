@@ -397,9 +397,10 @@ constexpr int kInvBatch = 2;    // inverse cosine kinds: elements per thread rea
 template <int CLASS>
 __global__ void __launch_bounds__(256) k_r2r(FFTArgs a, const FTile* __restrict__ tiles, int ntiles,
                                              int dir, const double* __restrict__ in,
-                                             double* __restrict__ out, int* nonfinite) {
+                                             double* __restrict__ out, int* nonfinite, const int* gate) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double2* z = reinterpret_cast<double2*>(lds_raw);
+    if (gate && *gate) return;  // out is left alone
     const int tix = xcd_remap(blockIdx.x, ntiles);
     const FTile T = tiles[tix];
     const int n = a.n, m = a.m, W = a.W, cs = a.cs;
@@ -722,9 +723,10 @@ __device__ __forceinline__ void wide_load(double (&r)[kWidePer], const double* _
 template <int FORM>
 __global__ void __launch_bounds__(1024) k_wide(SArgs a, const FTile* __restrict__ tiles, int ntiles,
                                                 const double* __restrict__ in, double* __restrict__ out,
-                                                int* nonfinite) {
+                                                int* nonfinite, const int* gate) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double2* z = reinterpret_cast<double2*>(lds_raw);
+    if (gate && *gate) return;  // out is left alone
     const int n = a.n, m = a.m, lw = a.lw, W = 1 << lw, cs = a.cs, nthr = blockDim.x, rpp = nthr >> lw;
     const double sc2 = sqrt(2.0 / n), sc1 = sqrt(1.0 / n);
     double2* tw = z + W * cs;
@@ -1002,13 +1004,13 @@ static int radix_class(const mbp_plan* P) {
 
 template <int CLASS>
 static void launch_r2r(const mbp_plan* P, const FFTArgs& a, const void* tiles, int dir, const double* in,
-                       double* out, int* nonfinite, hipStream_t s) {
+                       double* out, int* nonfinite, const int* gate, hipStream_t s) {
     const size_t bytes = lds_bytes(P);
     if (bytes > 64 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_r2r<CLASS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
     hipLaunchKernelGGL(k_r2r<CLASS>, dim3(P->fft_ntiles), dim3(256), bytes, s, a,
-                       reinterpret_cast<const FTile*>(tiles), P->fft_ntiles, dir, in, out, nonfinite);
+                       reinterpret_cast<const FTile*>(tiles), P->fft_ntiles, dir, in, out, nonfinite, gate);
 }
 
 static const void* wide_fn(int form) {
@@ -1046,7 +1048,7 @@ int fft_setup_grid(mbp_plan* P) {
 }
 
 static void run_wide(const mbp_plan* P, const void* tiles, int dir, const double* in, double* out, int* nonfinite,
-                     hipStream_t s) {
+                     const int* gate, hipStream_t s) {
     const FFTPlan& F = P->fft;
     SArgs a{};
     a.n = F.n;
@@ -1076,28 +1078,28 @@ static void run_wide(const mbp_plan* P, const void* tiles, int dir, const double
         (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
     const FTile* tl = reinterpret_cast<const FTile*>(tiles);
     int ntiles = P->fft_ntiles;
-    void* args[] = {&a, &tl, &ntiles, &in, &out, &nonfinite};
+    void* args[] = {&a, &tl, &ntiles, &in, &out, &nonfinite, &gate};
     (void)hipLaunchKernel(fn, dim3(F.grid[dir]), dim3(F.nt), args, bytes, s);
 }
 
 static void run_r2r(const mbp_plan* P, const void* tiles, int dir, const double* in, double* out,
-                    int* nonfinite, hipStream_t s) {
-    if (P->fft.W) return run_wide(P, tiles, dir, in, out, nonfinite, s);
+                    int* nonfinite, const int* gate, hipStream_t s) {
+    if (P->fft.W) return run_wide(P, tiles, dir, in, out, nonfinite, gate, s);
     const FFTArgs a = make_args(P);
     switch (radix_class(P)) {
-        case 0: launch_r2r<0>(P, a, tiles, dir, in, out, nonfinite, s); break;
-        case 1: launch_r2r<1>(P, a, tiles, dir, in, out, nonfinite, s); break;
-        case 2: launch_r2r<2>(P, a, tiles, dir, in, out, nonfinite, s); break;
-        default: launch_r2r<3>(P, a, tiles, dir, in, out, nonfinite, s); break;
+        case 0: launch_r2r<0>(P, a, tiles, dir, in, out, nonfinite, gate, s); break;
+        case 1: launch_r2r<1>(P, a, tiles, dir, in, out, nonfinite, gate, s); break;
+        case 2: launch_r2r<2>(P, a, tiles, dir, in, out, nonfinite, gate, s); break;
+        default: launch_r2r<3>(P, a, tiles, dir, in, out, nonfinite, gate, s); break;
     }
 }
 
 void launch_forward(const mbp_plan* P, const double* f, double* fhat, int* nonfinite, hipStream_t s) {
-    run_r2r(P, P->d_ftiles_fwd, 0, f, fhat, nonfinite, s);
+    run_r2r(P, P->d_ftiles_fwd, 0, f, fhat, nonfinite, nullptr, s);
 }
 
-void launch_inverse(const mbp_plan* P, const double* phat, double* p, hipStream_t s) {
-    run_r2r(P, P->d_ftiles_inv, 1, phat, p, nullptr, s);
+void launch_inverse(const mbp_plan* P, const double* phat, double* p, hipStream_t s, const int* gate) {
+    run_r2r(P, P->d_ftiles_inv, 1, phat, p, nullptr, gate, s);
 }
 
 }  // namespace mbp

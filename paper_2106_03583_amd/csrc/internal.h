@@ -157,6 +157,7 @@ struct mbp_plan {
     int64_t lds_limit = 64 * 1024;  // LDS bytes one workgroup may use
     int lvinfo = 0;               // int-pool offset: per level {plane, blk_off, tile_off, ntiles}
     int proj_tab = 0;             // int-pool offset: per block {dcx, dcy, gx, gy, rows before, columns before}
+    std::vector<unsigned char> strips, pair_strips;  // host images of the strip descriptors
     std::vector<int> mtile_off, mtile_cnt;  // fused-sweep strips per level (LDS strip form)
     std::vector<int> rtile_off, rtile_cnt;  // taller strips of the register-march form
     std::vector<char> use_rmarch;           // level runs its pre-smoothing as a register march
@@ -214,7 +215,8 @@ struct mbp_plan {
     int* d_flag = nullptr;        // 4 ints: [0] non-finite rhs
     double* d_scal = nullptr;     // 8 doubles of scratch scalars
     void* graph_exec = nullptr;   // cached batched replay (hipGraphExec_t)
-    void* host_pinned = nullptr;  // small pinned buffer for convergence readback
+    void* host_pinned = nullptr;  // pinned buffer that kernels report to
+    void* pinned_dev = nullptr;   //   its device address
     // kernel timing (mbp_profile_*): event pairs around finest-level sweeps
     bool prof = false;
     std::vector<std::array<void*, 2>> prof_ev[2];  // hipEvent_t pairs per kernel class
@@ -250,7 +252,8 @@ void fft_build_tiles(const mbp_plan* P, std::vector<unsigned char>& fwd, std::ve
 // device launchers (fft.hip, mg.hip)
 void launch_forward(const mbp_plan* P, const double* f, double* fhat, int* nonfinite_flag,
                     hipStream_t s);
-void launch_inverse(const mbp_plan* P, const double* phat, double* p, hipStream_t s);
+// gate (device, optional): p is left alone where it is not zero
+void launch_inverse(const mbp_plan* P, const double* phat, double* p, hipStream_t s, const int* gate = nullptr);
 void launch_apply3d(const mbp_plan* P, const double* p, double* out, hipStream_t s);
 // project.hip: staggered velocities (packed face fields) and the projection
 void velocity_offsets(const mbp_plan* P, int64_t* uo, int64_t* vo, int64_t* wo);
@@ -364,10 +367,13 @@ void launch_zero32(float* p, size_t n, hipStream_t s);
 void launch_singular_fix(const mbp_plan* P, double* plane, double* out_mean, hipStream_t s);
 
 // solve.cpp
-size_t plan_device_bytes(const mbp_plan* P);
+size_t plan_device_bytes(mbp_plan* P);  // builds the strip tables, which the device part takes over
 // Device part of a plan.  ext_mem (optional): place the plan in that region
-// of ext_bytes instead of allocating; ext_pinned (optional): a 4 KB pinned
-// host buffer to use for readbacks.
+// of ext_bytes instead of allocating; ext_pinned (optional): a pinned
+// host buffer of kPinBytes to use for readbacks.
+constexpr size_t kPinBytes = 24 * 1024;  // read-back buffer of a plan
+int plan_set_pinned(mbp_plan* P, void* host);  // use that buffer
+double* pin_state(const mbp_plan* P, int slot);  // device view of its state slot, which the convergence test writes
 int plan_device_init(mbp_plan* P, void* ext_mem = nullptr, size_t ext_bytes = 0, void* ext_pinned = nullptr);
 void plan_device_free(mbp_plan* P);
 int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags, hipStream_t s,
@@ -394,13 +400,11 @@ struct SolveCtx {
                              // relaxed are zeroed before the inverse transform
 };
 void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rtol, int flags);
-void ctx_prologue(SolveCtx& c, hipStream_t s);  // ends with an async readback of the checks
-void ctx_check(SolveCtx& c);                    // after that readback synchronised
-void ctx_test(SolveCtx& c, hipStream_t s, double* state_out = nullptr);  // residual norms + convergence
-                                                                        // update (state copied to state_out)
+void ctx_prologue(SolveCtx& c, hipStream_t s);  // ends by writing what ctx_check reads to host memory
+void ctx_check(SolveCtx& c);                    // after the prologue synchronised
+void ctx_test(SolveCtx& c, hipStream_t s, int slot = 0);  // residual norms + convergence, state into the slot
 void ctx_vcycle(SolveCtx& c, hipStream_t s);    // one V-cycle of the active modes
-void ctx_state_readback(SolveCtx& c, hipStream_t s);
-void ctx_state_apply(SolveCtx& c);              // after that readback synchronised
+void ctx_state_apply(SolveCtx& c, int slot = 0);  // after the test synchronised
 void ctx_epilogue(SolveCtx& c, hipStream_t s);
 int ctx_info(SolveCtx& c, hipStream_t s, mbp_solve_info* info);  // synchronises s
 int plan_autotune(mbp_plan* P, const double* rhs, hipStream_t s, mbp_tuning* out);

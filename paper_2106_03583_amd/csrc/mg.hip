@@ -533,6 +533,7 @@ __device__ __forceinline__ void update_body(const UpdJob& J) {
         int c = kept;
         if (!retire) {  // lockstep: done when every mode passes both tests
             scal[1] = double(c);
+            if (c == 0 || stop) *nact = 0;  // what is queued behind has nothing to do
         } else {
             if (stop && c > 0) {
                 state[2] = 1;
@@ -564,12 +565,56 @@ __global__ void k_fill_int(int* p, int n, int v) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
 }
 
-__global__ void k_iota(int* act, int n, int* nact, int* cyc) {
+// Start of a solve: every mode active, no cycle done.  out (optional, host-visible):
+// state[0..3] of the transforms, the singular plane's area sum, mode 0's norm.
+__global__ void k_iota(int* act, int n, int* nact, int* cyc, const int* state, const double* sum, const double* fnorm,
+                       double* out) {
     for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < n; i += blockDim.x * gridDim.x) {
         act[i] = i;
         cyc[i] = 0;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nact = n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *nact = n;
+        if (out) {
+            for (int i = 0; i < 4; ++i) reinterpret_cast<int*>(out)[i] = state[i];
+            out[2] = *sum;
+            out[3] = fnorm[0];
+        }
+    }
+}
+
+// End of a solve, into host-visible memory: out[0] the largest |r|^2 / |f|^2 of all
+// modes, then as ints the most cycles of a mode, and every mode's.
+__global__ void __launch_bounds__(1024) k_report(int n, const int* __restrict__ cyc, const double* __restrict__ rnorm,
+                                                 const double* __restrict__ fnorm, double* __restrict__ out) {
+    __shared__ double mx[16];
+    __shared__ int mc[16];
+    int* oi = reinterpret_cast<int*>(out + 1);
+    double m = 0.0;
+    int c = 0;
+    for (int q = threadIdx.x; q < n; q += blockDim.x) {
+        const double fn = fnorm[q], rn = rnorm[q];
+        m = fmax(m, fn > 0.0 ? rn / fn : (rn > 0.0 ? 1e300 : 0.0));
+        c = max(c, cyc[q]);
+        oi[1 + q] = cyc[q];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        m = fmax(m, __shfl_xor(m, o));
+        c = max(c, __shfl_xor(c, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        mx[threadIdx.x >> 6] = m;
+        mc[threadIdx.x >> 6] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < int(blockDim.x >> 6); ++w) {
+            m = fmax(m, mx[w]);
+            c = max(c, mc[w]);
+        }
+        out[0] = m;
+        oi[0] = c;
+    }
 }
 
 // Zero the planes of the modes that no V-cycle relaxed (cyc[q] == 0: they
@@ -1311,8 +1356,14 @@ void launch_update_active(const mbp_plan* P, double rtol2, double etol2, int ret
     hipLaunchKernelGGL(k_update, dim3(1), dim3(1024), 0, s, J);
 }
 
-void launch_reset_active(const mbp_plan* P, hipStream_t s) {
-    hipLaunchKernelGGL(k_iota, dim3(1), dim3(1024), 0, s, P->d_act, P->g.nz, P->d_nact, P->d_cyc);
+void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out) {
+    hipLaunchKernelGGL(k_iota, dim3(1), dim3(1024), 0, s, P->d_act, P->g.nz, P->d_nact, P->d_cyc, P->d_flag,
+                       P->d_scal + 4, P->d_fnorm, out);
+}
+
+void launch_report(const mbp_plan* P, hipStream_t s, double* out) {
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(P->g.nz <= 256 ? 256 : 1024), 0, s, P->g.nz, P->d_cyc, P->d_rnorm,
+                       P->d_fnorm, out);
 }
 
 void launch_zero_unrelaxed(const mbp_plan* P, double* p, hipStream_t s) {
@@ -1448,7 +1499,7 @@ GStage group_update(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
         const mbp_plan* P = c->P;
         jobs.push_back(UpdJob{P->g.nz, P->d_rnorm, P->d_fnorm, P->d_pnorm, P->d_sabs, c->rtol2, c->etol2,
                               c->retire ? 1 : 0, P->opt.max_cycles, P->d_act, P->d_nact, P->d_cyc, P->d_scal,
-                              P->d_flag});
+                              P->d_flag, pin_state(P, 0)});
         gx.push_back(1);
         gy.push_back(1);
     }

@@ -13,7 +13,7 @@
 // calls hipMalloc or hipFree (hipFree waits for the whole device, which
 // would stall every running request).  The host part of a plan (validation,
 // hierarchy, tables) is built in the submitting thread, so the worker only
-// places the plan and uploads its tables in one copy; readbacks use pinned
+// places the plan and uploads its tables in one copy; solves report into pinned
 // buffers owned by the slots.
 #include <algorithm>
 #include <chrono>
@@ -157,7 +157,7 @@ struct mbp_server {
     std::vector<char> slot_busy;
     void* arena_mem = nullptr;      // the budget, allocated once
     Arena arena;
-    void* pinned = nullptr;         // 4 KB readback buffer per slot
+    void* pinned = nullptr;         // readback buffer per slot
 
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -183,12 +183,12 @@ struct mbp_server {
     }
 
     CachedPlan* acquire_plan(Request* r, int slot) {
-        void* pin = static_cast<unsigned char*>(pinned) + size_t(slot) * 4096;
+        void* pin = static_cast<unsigned char*>(pinned) + size_t(slot) * kPinBytes;
         for (auto& c : cache)
             if (!c->busy && c->key == r->key) {
                 c->busy = true;
                 c->last_use = ++use_clock;
-                c->plan->host_pinned = pin;
+                (void)plan_set_pinned(c->plan, pin);  // a slot's buffer: mapped before
                 return c.get();
             }
         // make room: drop idle plans, least recently used first, until a
@@ -262,7 +262,6 @@ struct mbp_server {
                     ctx_test(c, s);
                     ctx_vcycle(c, s);
                 }
-                ctx_state_readback(c, s);
                 (void)hipEventRecord(r->ev, s);
                 r->stage = kCycles;
                 return true;
@@ -388,7 +387,7 @@ int mbp_server_create(size_t hbm_budget, int slots, const mbp_options* opt, mbp_
         return MBP_ERR_NOMEM;
     }
     S->arena.init(hbm_budget);
-    if (hipHostMalloc(&S->pinned, size_t(slots) * 4096, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&S->pinned, size_t(slots) * kPinBytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipFree(S->arena_mem);
         delete S;
         return MBP_ERR_NOMEM;

@@ -8,7 +8,8 @@
 
 namespace mbp {
 
-void launch_reset_active(const mbp_plan* P, hipStream_t s);
+void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out);
+void launch_report(const mbp_plan* P, hipStream_t s, double* out);
 void launch_area_dot(const mbp_plan* P, const double* plane, double* out_sum, hipStream_t s);
 void launch_fill_int(int* p, int n, int v, hipStream_t s);
 
@@ -96,7 +97,10 @@ constexpr int kMarchSeg = 26;  // rows per fused-sweep strip (the LDS tile heigh
 // register march; both live in one descriptor array.
 constexpr int kRMarchSeg = 128;  // rows per register-march strip
 
-void plan_march_tables(mbp_plan* P, std::vector<unsigned char>& bytes, std::vector<unsigned char>& pbytes) {
+static void plan_march_tables(mbp_plan* P) {
+    if (!P->march_ok.empty()) return;
+    std::vector<unsigned char>& bytes = P->strips;
+    std::vector<unsigned char>& pbytes = P->pair_strips;
     P->march_ok.assign(P->nlev, 0);
     P->mtile_off.assign(P->nlev, 0);
     P->mtile_cnt.assign(P->nlev, 0);
@@ -142,21 +146,20 @@ static int partial_count(const mbp_plan* P) {
     return std::max({4 * P->mtile_cnt[0], P->rtile_cnt[0], pair_max_strips(P, 0)});
 }
 
-size_t plan_device_bytes(const mbp_plan* P) {
-    mbp_plan tmp = *P;
-    std::vector<unsigned char> mt, pt;
-    plan_march_tables(&tmp, mt, pt);
+size_t plan_device_bytes(mbp_plan* P) {
+    plan_march_tables(P);
     const int W = fft_columns_per_wg(P);
     size_t nt = 0;
     for (int b = 0; b < P->g.nb; ++b) nt += (size_t(P->g.nx[b]) * P->g.ny[b] + W - 1) / W;
-    return layout(&tmp, nt * 32, mt.size(), pt.size(), partial_count(&tmp)).total;
+    return layout(P, nt * 32, P->strips.size(), P->pair_strips.size(), partial_count(P)).total;
 }
 
 int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pinned) {
-    std::vector<unsigned char> ftf, fti, mt, pt;
+    std::vector<unsigned char> ftf, fti;
     fft_build_tiles(P, ftf, fti, &P->fft_ntiles);
     if (const int st = fft_setup_grid(P)) return st;
-    plan_march_tables(P, mt, pt);
+    plan_march_tables(P);
+    const std::vector<unsigned char>&mt = P->strips, &pt = P->pair_strips;
     Layout L = layout(P, ftf.size(), mt.size(), pt.size(), partial_count(P));
     void* mem = ext_mem;
     if (ext_mem) {
@@ -241,15 +244,18 @@ int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pin
         hipSuccess)
         return MBP_ERR_HIP;
     if (ext_pinned) {
-        P->host_pinned = ext_pinned;
         P->owns_pinned = false;
-        return MBP_OK;
+        return plan_set_pinned(P, ext_pinned);
     }
     void* hp = nullptr;
-    if (hipHostMalloc(&hp, 4096, hipHostMallocDefault) != hipSuccess) return MBP_ERR_NOMEM;
-    P->host_pinned = hp;
+    if (hipHostMalloc(&hp, kPinBytes, hipHostMallocDefault) != hipSuccess) return MBP_ERR_NOMEM;
     P->owns_pinned = true;
-    return MBP_OK;
+    return plan_set_pinned(P, hp);
+}
+
+int plan_set_pinned(mbp_plan* P, void* host) {
+    P->host_pinned = host;
+    return hipHostGetDevicePointer(&P->pinned_dev, host, 0) == hipSuccess ? MBP_OK : MBP_ERR_HIP;
 }
 
 // Event pairs around a finest-level sweep launch (only while profiling).
@@ -302,14 +308,20 @@ void plan_device_free(mbp_plan* P) {
 // ---------------------------------------------------------------------------
 
 namespace {
-// layout of the plan's pinned readback buffer
-constexpr int kPinScal = 0;     // doubles 0..7: d_scal
-constexpr int kPinSum = 8;      // double: singular-plane area sum
-constexpr int kPinInts = 32;    // ints (byte offset 256): flag[0..3], nact
-constexpr int kPinSlots = 64;   // doubles from byte 512: state slots of the pipelined loop
+// layout (doubles) of the plan's pinned buffer, which kernels write directly: a copy
+// is a dispatch of its own between two kernels
+constexpr int kPinStart = 0;    // after the prologue: ints flag[0..3], area sum, mode 0's norm
+constexpr int kPinSlots = 64;   // state slots of the tests
 constexpr int kSlotDoubles = 8; //   each scal[0..1], then ints flag[0..3], nact
 constexpr int kSlots = 3;
+constexpr int kPinReport = 128; // at the end: max ratio, then ints most cycles, cycles per mode
+static_assert(kPinReport * 8 + 8 + 4 * (1 + 4096) <= kPinBytes, "one int a mode");
+
+double* pin_host(const mbp_plan* P, int at) { return static_cast<double*>(P->host_pinned) + at; }
+double* pin_dev(const mbp_plan* P, int at) { return static_cast<double*>(P->pinned_dev) + at; }
 }  // namespace
+
+double* pin_state(const mbp_plan* P, int slot) { return pin_dev(P, kPinSlots + slot * kSlotDoubles); }
 
 void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rtol, int flags) {
     c = SolveCtx{};
@@ -328,9 +340,6 @@ void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rto
     c.nitems = P->g.nz;
 }
 
-static double* pin_d(const mbp_plan* P) { return static_cast<double*>(P->host_pinned); }
-static int* pin_i(const mbp_plan* P) { return reinterpret_cast<int*>(pin_d(P) + kPinInts); }
-
 void ctx_prologue(SolveCtx& c, hipStream_t s) {
     mbp_plan* P = c.P;
     const int nz = P->g.nz;
@@ -343,23 +352,20 @@ void ctx_prologue(SolveCtx& c, hipStream_t s) {
     launch_plane_norm(P, P->fhat, P->d_fnorm, s);
     if (c.warm) launch_forward(P, c.p, P->phat, nullptr, s);
     else if (!c.lazy_zero) launch_zero(P->phat, size_t(nz) * P->plane0, s);
-    launch_reset_active(P, s);
-    (void)hipMemcpyAsync(pin_i(P), P->d_flag, 4 * sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(pin_d(P) + kPinSum, P->d_scal + 4, sizeof(double), hipMemcpyDeviceToHost, s);
+    launch_reset_active(P, s, pin_dev(P, kPinStart));
 }
 
 void ctx_check(SolveCtx& c) {
     mbp_plan* P = c.P;
     const int nz = P->g.nz;
-    if (pin_i(P)[0]) c.status = MBP_ERR_NONFINITE;
+    const double* start = pin_host(P, kPinStart);
+    if (reinterpret_cast<const int*>(start)[0]) c.status = MBP_ERR_NONFINITE;
     if (c.status == MBP_OK && P->g.singular) {
-        const double mean_q0 = pin_d(P)[kPinSum] / P->area_sum;  // area-weighted mean of fhat_0
+        const double mean_q0 = start[2] / P->area_sum;  // area-weighted mean of fhat_0
         c.removed = mean_q0 / std::sqrt(double(nz));               // volume-weighted mean of f
         if (!(c.flags & MBP_PROJECT_RHS)) {
             // compatible if the mean is at rounding level of the plane's rms
-            double fn0 = 0.0;
-            (void)hipMemcpy(&fn0, P->d_fnorm, sizeof(double), hipMemcpyDeviceToHost);
-            const double rms = std::sqrt(fn0 / double(P->plane0));
+            const double rms = std::sqrt(start[3] / double(P->plane0));
             if (std::fabs(mean_q0) > 1e-12 * (rms + 1e-300)) c.status = MBP_ERR_INCOMPATIBLE;
             c.removed = 0.0;
         }
@@ -369,7 +375,7 @@ void ctx_check(SolveCtx& c) {
 
 // Convergence test of the current iterate (Sec. 3's per-mode systems each
 // stop on their own when retiring).
-void ctx_test(SolveCtx& c, hipStream_t s, double* state_out) {
+void ctx_test(SolveCtx& c, hipStream_t s, int slot) {
     mbp_plan* P = c.P;
     const bool zero = c.cycles == 0 && !c.warm;  // p = 0: the residual is f itself
     if (c.mixed)
@@ -381,7 +387,7 @@ void ctx_test(SolveCtx& c, hipStream_t s, double* state_out) {
         launch_finish(P, c.fused_parts, c.flip ? P->d_flag + 3 : nullptr, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
     else
         launch_residual_norm(P, P->phat, P->fhat, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
-    launch_update_active(P, c.rtol2, c.etol2, c.retire ? 1 : 0, P->opt.max_cycles, s, state_out);
+    launch_update_active(P, c.rtol2, c.etol2, c.retire ? 1 : 0, P->opt.max_cycles, s, pin_state(P, slot));
 }
 
 void ctx_vcycle(SolveCtx& c, hipStream_t s) {
@@ -415,24 +421,18 @@ void ctx_vcycle(SolveCtx& c, hipStream_t s) {
     ++c.cycles;
 }
 
-void ctx_state_readback(SolveCtx& c, hipStream_t s) {
-    mbp_plan* P = c.P;
-    (void)hipMemcpyAsync(pin_d(P) + kPinScal, P->d_scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(pin_i(P), P->d_flag, 4 * sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(pin_i(P) + 4, P->d_nact, sizeof(int), hipMemcpyDeviceToHost, s);
-}
-
-// After the readback synchronised: stop when every mode retired (retiring
-// form) or every mode passed (lockstep), or when the cycle budget ran out.
-// hi: flag[0..3], nact; scal1: the lockstep count of unconverged modes.
-static void state_apply(SolveCtx& c, const int* hi, double scal1) {
+// After the test synchronised: stop when every mode retired (retiring form) or
+// every mode passed (lockstep), or when the cycle budget ran out.
+void ctx_state_apply(SolveCtx& c, int slot) {
+    const double* sl = pin_host(c.P, kPinSlots + slot * kSlotDoubles);
+    const int* hi = reinterpret_cast<const int*>(sl + 2);  // flag[0..3], nact
     const bool hitmax = hi[2] != 0;
     bool converged;
     if (c.retire) {
         c.nitems = hi[4];
         converged = c.nitems == 0 && !hitmax;
     } else {
-        converged = scal1 == 0.0;
+        converged = sl[1] == 0.0;  // modes that have not passed
     }
     if (converged) {
         c.done = true;
@@ -442,49 +442,47 @@ static void state_apply(SolveCtx& c, const int* hi, double scal1) {
     }
 }
 
-void ctx_state_apply(SolveCtx& c) { state_apply(c, pin_i(c.P), pin_d(c.P)[kPinScal + 1]); }
-
-void ctx_epilogue(SolveCtx& c, hipStream_t s) {
+// gate (device, optional): p is left alone where it is not zero.
+static void ctx_finish(SolveCtx& c, hipStream_t s, const int* gate) {
     mbp_plan* P = c.P;
     if (c.status == MBP_OK || c.status == MBP_ERR_NOT_CONVERGED) {
         if (c.lazy_zero) launch_zero_unrelaxed(P, P->phat, s);
         if (c.flip) launch_take_odd(P, P->phat, P->phatB, s);
         if (P->g.singular) launch_singular_fix(P, P->phat, P->d_scal + 5, s);
-        launch_inverse(P, P->phat, c.p, s);
+        launch_inverse(P, P->phat, c.p, s, gate);
     }
+    launch_report(P, s, pin_dev(P, kPinReport));
 }
+
+void ctx_epilogue(SolveCtx& c, hipStream_t s) { ctx_finish(c, s, nullptr); }
 
 // Host-side result record; synchronises the stream.
 int ctx_info(SolveCtx& c, hipStream_t s, mbp_solve_info* info) {
     mbp_plan* P = c.P;
-    const int nz = P->g.nz;
-    std::vector<int> cyc(nz, 0);
-    std::vector<double> rn(nz, 0.0), fn(nz, 0.0);
-    (void)hipMemcpyAsync(cyc.data(), P->d_cyc, nz * sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(rn.data(), P->d_rnorm, nz * sizeof(double), hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(fn.data(), P->d_fnorm, nz * sizeof(double), hipMemcpyDeviceToHost, s);
     if (hipStreamSynchronize(s) != hipSuccess) return MBP_ERR_HIP;
     if (hipGetLastError() != hipSuccess) return MBP_ERR_HIP;
-    double maxratio = 0.0;
-    int cycles = 0;
-    for (int q = 0; q < nz; ++q) {
-        maxratio = std::max(maxratio, fn[q] > 0 ? rn[q] / fn[q] : (rn[q] > 0 ? 1e300 : 0.0));
-        cycles = std::max(cycles, cyc[q]);
-    }
+    const double maxratio = *pin_host(P, kPinReport);
+    const int* cyc = reinterpret_cast<const int*>(pin_host(P, kPinReport + 1));
     if (c.status == MBP_OK && c.full_lds && maxratio > c.rtol2) c.status = MBP_ERR_NOT_CONVERGED;
     if (info) {
         info->status = c.status;
-        info->cycles = cycles;
+        info->cycles = cyc[0];
         info->rel_residual = std::sqrt(maxratio);
         info->removed_mean = c.status == MBP_ERR_NONFINITE ? 0.0 : c.removed;
-        if (info->cycles_per_mode) std::memcpy(info->cycles_per_mode, cyc.data(), nz * sizeof(int));
+        if (info->cycles_per_mode) std::memcpy(info->cycles_per_mode, cyc + 1, P->g.nz * sizeof(int));
     }
     return MBP_OK;
 }
 
 // Algorithm 1 for one problem: forward transform, per-mode multigrid to the
-// tolerance, inverse transform.  Host-driven: the convergence state is read
-// back once per cycle (the batched form replays captured cycles instead).
+// tolerance, inverse transform.  Host-driven, but the host reads the state of a test
+// only after the next V-cycle and test are queued, and the checks of the rhs with
+// the first of them, so the device never waits for the host (the batched form
+// replays captured cycles instead).  Once every mode has retired or, in lockstep, passed,
+// the queued work runs on an empty active list (no-op launches).  State reaches the
+// host through memory that kernels write: with a copy kernel per item and a wait per
+// cycle, a lockstep solve of 203 x 157 x 90 took 2.53 ms (now 2.30) and one of 32^3
+// 246 us (now 199).
 int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags, hipStream_t s,
               mbp_solve_info* info) {
     SolveCtx c;
@@ -499,58 +497,44 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
     ctx_prologue(c, s);
     (void)hipEventRecord(ev[1], s);
     int st = MBP_OK;
-    if (hipStreamSynchronize(s) != hipSuccess) st = MBP_ERR_HIP;
-    if (st == MBP_OK) {
-        ctx_check(c);
-        if (!c.done && c.full_lds) {
-            launch_lds_full(P, P->phat, P->fhat, P->d_act, P->d_nact, P->g.nz, P->opt.max_cycles, c.rtol2,
-                            c.etol2, P->d_cyc, P->d_rnorm, P->d_fnorm, s);
-        } else if (c.retire) {
-            // Pipelined: the next V-cycle and test are queued before the host
-            // reads the state of the previous test, so the device never waits
-            // for the host.  Once every mode has retired the queued work runs
-            // on an empty active list (no-op launches).
-            double* slots = pin_d(P) + kPinSlots;
-            double* dslots = nullptr;
-            if (hipHostGetDevicePointer(reinterpret_cast<void**>(&dslots), slots, 0) != hipSuccess) {
-                st = MBP_ERR_HIP;
-            } else {
-                hipEvent_t sev[kSlots];
-                for (auto& e : sev) (void)hipEventCreateWithFlags(&e, hipEventDisableTiming);
-                auto test = [&](int k) {
-                    ctx_test(c, s, dslots + (k % kSlots) * kSlotDoubles);
-                    (void)hipEventRecord(sev[k % kSlots], s);
-                };
-                test(0);
-                for (int k = 0;; ++k) {
-                    ctx_vcycle(c, s);
-                    test(k + 1);
-                    if (hipEventSynchronize(sev[k % kSlots]) != hipSuccess) {
-                        st = MBP_ERR_HIP;
-                        break;
-                    }
-                    const double* sl = slots + (k % kSlots) * kSlotDoubles;
-                    state_apply(c, reinterpret_cast<const int*>(sl + 2), sl[1]);
-                    if (c.done) break;
-                }
-                for (auto& e : sev) (void)hipEventDestroy(e);
-            }
-        } else {
-            while (!c.done) {
-                ctx_test(c, s);
-                ctx_state_readback(c, s);
-                if (hipStreamSynchronize(s) != hipSuccess) {
-                    st = MBP_ERR_HIP;
-                    break;
-                }
-                ctx_state_apply(c);
-                if (c.done) break;
-                ctx_vcycle(c, s);
-            }
+    bool finished = false;  // epilogue queued
+    if (c.full_lds) {
+        launch_lds_full(P, P->phat, P->fhat, P->d_act, P->d_nact, P->g.nz, P->opt.max_cycles, c.rtol2, c.etol2,
+                        P->d_cyc, P->d_rnorm, P->d_fnorm, s);
+        if (!P->g.singular || (flags & MBP_PROJECT_RHS)) {
+            // only a value that is not finite can stop this solve, which the
+            // inverse transform can see for itself
+            (void)hipEventRecord(ev[2], s);
+            ctx_finish(c, s, P->d_flag);
+            finished = true;
         }
+        if (hipStreamSynchronize(s) != hipSuccess) st = MBP_ERR_HIP;
+        else ctx_check(c);
+    } else {
+        hipEvent_t sev[kSlots];
+        for (auto& e : sev) (void)hipEventCreateWithFlags(&e, hipEventDisableTiming);
+        auto test = [&](int k) {
+            ctx_test(c, s, k % kSlots);
+            (void)hipEventRecord(sev[k % kSlots], s);
+        };
+        test(0);
+        for (int k = 0;; ++k) {
+            ctx_vcycle(c, s);
+            test(k + 1);
+            if (hipEventSynchronize(sev[k % kSlots]) != hipSuccess) {
+                st = MBP_ERR_HIP;
+                break;
+            }
+            if (k == 0) ctx_check(c);
+            if (!c.done) ctx_state_apply(c, k % kSlots);
+            if (c.done) break;
+        }
+        for (auto& e : sev) (void)hipEventDestroy(e);
     }
-    (void)hipEventRecord(ev[2], s);
-    if (st == MBP_OK) ctx_epilogue(c, s);
+    if (!finished) {
+        (void)hipEventRecord(ev[2], s);
+        if (st == MBP_OK) ctx_finish(c, s, nullptr);
+    }
     (void)hipEventRecord(ev[3], s);
     if (st == MBP_OK) st = ctx_info(c, s, info);
     if (st == MBP_OK && info) {
