@@ -290,6 +290,10 @@ struct VcycleArgs {
     bool ready = false;  // in / out: the next level's rhs already holds the restricted
                          // residual of the pre-smoothed p (the pair march leaves it there)
     bool flipped = false;  // out
+    // FP32: add the result to this FP64 iterate (first: zero so far) where the last
+    // sweep can do so (out: added; p and pB are then undefined)
+    double* sum = nullptr;
+    bool first = false, added = false;
 };
 template <typename T>
 int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s);
@@ -343,6 +347,8 @@ void pair_pre(const mbp_plan* P, int l, const T* p, const T* f, T* fc, const int
 template <typename T>
 void pair_post(const mbp_plan* P, int l, const T* p, T* pnew, const T* f, const T* ec, const int* act, const int* nact,
                int nitems, hipStream_t s);
+void pair_post_add(const mbp_plan* P, const float* p, double* sum, bool first, const float* f, const float* ec,
+                   const int* act, const int* nact, int nitems, hipStream_t s);
 template <typename T>
 void pair_cycle(const mbp_plan* P, int l, T* pa, T* pb, const int* cycle, const T* f, const T* ec, T* fc, bool zero,
                 const int* act, const int* nact, int nitems, hipStream_t s);
@@ -418,7 +424,7 @@ struct GEnt {
 enum GKind {
     G_RES32 = 0, G_FINISH, G_UPDATE, G_PRE32, G_LDS32, G_POST32, G_ADDCORR,
     G_COARSE0, G_COARSE1, G_COARSE2,
-    G_PAIR_PRE, G_PAIR_POST0, G_PAIR_POST, G_PAIR_CYCLE0, G_PAIR_CYCLE  // (0: from a zero iterate)
+    G_PAIR_PRE, G_PAIR_POST0, G_PAIR_ADD0, G_PAIR_ADD, G_PAIR_CYCLE0, G_PAIR_CYCLE  // (0: from a zero iterate)
 };
 struct GStage {
     int kind = 0;

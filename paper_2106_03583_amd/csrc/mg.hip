@@ -1235,7 +1235,11 @@ int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s) {
                 continue;
             }
             prof_begin(P, 1, s, double(Lf.plane) * nitems);
-            if (v.last)
+            if (v.last && v.sum) {
+                if constexpr (sizeof(T) == 4)
+                    pair_post_add(P, v.zero ? nullptr : v.p, v.sum, v.first, v.f, P_(1), act, nact, nitems, s);
+                v.added = true;
+            } else if (v.last)
                 pair_post<T>(P, 0, v.zero ? nullptr : v.p, v.pB, v.f, P_(1), act, nact, nitems, s);
             else
                 pair_cycle<T>(P, 0, v.p, v.pB, v.cycle, v.f, P_(1), F_(1), v.zero, act, nact, nitems, s);
@@ -1514,9 +1518,8 @@ GStage group_addcorr(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     for (const SolveCtx* c : cs) {
         const mbp_plan* P = c->P;
         const Level& L = P->levels[0];
-        // the pair march leaves the correction of an odd cycle count in the second buffer
-        const float* e = P->lds_level32 > 0 && P->pair_ok[0] && (P->opt.inner & 1) ? P->p32B[0] : P->p32[0];
-        jobs.push_back(AddJob{P->phat, e, (long long)L.plane, P->d_act, P->d_nact});
+        if (P->lds_level32 > 0 && P->pair_ok[0]) continue;  // the pair march's last sweep adds it
+        jobs.push_back(AddJob{P->phat, P->p32[0], (long long)L.plane, P->d_act, P->d_nact});
         gx.push_back(add_chunks(L.plane));
         gy.push_back(c->nitems);
     }

@@ -28,6 +28,11 @@
 // branches: a missing cell has zero couplings and a huge diagonal and stays 0.
 // Loads are buffer loads whose out-of-range lanes return 0.
 //
+// The last sweep of an FP32 correction solve (ADD) adds its rows to the FP64 iterate:
+// 25 B a cell instead of 13 B and a pass of 20 B that read them again (eight-block
+// obstacle: 94 + 41 -> 106 us a refinement step).  Four FP64 rows ahead, and six of p
+// and f instead of eight, as eight of both spilled: 7 % slower than two passes.
+//
 // What bounds it: memory.  512 x 512 x 1024 box, FP64, all 1024 modes: the first
 // cycle launch moves 20 B per cell in 1.32 ms (4.1 TB/s; a device copy reaches
 // 4.9), the later ones 28 B at 4.3 TB/s; the two strip launches they replace
@@ -95,6 +100,8 @@ struct PArgs {
     const int* nact;
     double* part;       // per (mode, strip) squared residual and solution
     int* nparts;        // strips of this launch, for the reduction
+    double* sum;        // ADD: the FP64 iterate that takes the result (its plane as of p)
+    int first;          // ADD: it is zero so far and need not be read
 };
 
 namespace {
@@ -140,11 +147,13 @@ __device__ __forceinline__ void store_one(__amdgpu_buffer_rsrc_t r, unsigned o, 
 // The march of one wave.  FORM bits: see the file comment.
 enum { kPre = 0, kPost = 1, kCycle = 2 };
 
-template <typename T, int FORM, bool ZIN, bool NRM>
+// ADD (FP32, the last sweep of a correction solve): the result is added to the FP64
+// iterate instead of being stored; the iterate's rows are loaded kSum steps ahead.
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
 struct March {
     static constexpr bool C = FORM != kPre, R = FORM != kPost;
     // rows loaded ahead: the ring minus the rows the last stage still reads
-    static constexpr int kAhead = FORM == kCycle ? 6 : 8;
+    static constexpr int kAhead = FORM == kCycle || ADD ? 6 : 8;
 
     // strip constants
     int lane, y0, y1, bny, ncy, kend;
@@ -165,6 +174,10 @@ struct March {
     unsigned co, cs, co1, cs1, co2, cs2;  // coarse rows
     T acc;
     double nrm, pnr;
+    static constexpr int kSum = 4;
+    __amdgpu_buffer_rsrc_t rsl, rss;      // ADD: the FP64 plane, for loads and stores
+    unsigned out_s, row_s;
+    Pr<double> sum[kSum];
 
     static __device__ __forceinline__ unsigned pick(bool c, unsigned a, unsigned b) { return c ? a : b; }
     __device__ __forceinline__ bool inside(int r) const { return (r >= y0) & (r < y1); }
@@ -262,7 +275,17 @@ struct March {
                 constexpr int i = (U - 5) & M;
                 const int r = k - 5;
                 const bool in = inside(r);
-                store_pair(rq, pick(in, out_p + unsigned(max(r, 0)) * row_p, kDead), p[i]);
+                if constexpr (ADD) {
+                    constexpr int w = (U - 5) & (kSum - 1);
+                    Pr<double> v = sum[w];
+                    v.v[0] += double(p[i].v[0]);
+                    v.v[1] += double(p[i].v[1]);
+                    store_pair(rss, pick(in, out_s + unsigned(max(r, 0)) * row_s, kDead), v);
+                    const int n = r + kSum;
+                    sum[w] = load_pair(rsl, pick(inside(n), out_s + unsigned(max(n, 0)) * row_s, kDead), 0.0);
+                } else {
+                    store_pair(rq, pick(in, out_p + unsigned(max(r, 0)) * row_p, kDead), p[i]);
+                }
                 if (NRM) {
                     const T a = p[i].v[0], b = p[i].v[1];
                     const T sum = a * a + b * b;
@@ -348,7 +371,7 @@ __host__ __device__ constexpr size_t pair_lds_bytes(int rows, bool corr) {
     return (size_t(kXw + kXd + (corr ? kXp : 0)) + 3 * size_t(rows + kUp + kDown) * kYw) * sizeof(T);
 }
 
-template <typename T, int FORM, bool ZIN, bool NRM>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
 __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nact = *a.nact;
@@ -375,7 +398,7 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     if (mi >= nact) return;
     const int q = __builtin_amdgcn_readfirstlane(a.act[mi]);
 
-    March<T, FORM, ZIN, NRM> m;
+    March<T, FORM, ZIN, NRM, ADD> m;
     m.lane = lane;
     m.y0 = t.y0;
     m.y1 = t.y1;
@@ -404,10 +427,19 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     const bool swap = a.cycle ? ((*a.cycle - 1) & 1) != 0 : false;
     const long long qo = q * a.plane, qc = q * a.plane_c;
     if (!ZIN) m.rp = plane_rsrc((swap ? a.pb : a.pa) + qo, pbytes);
-    if (C) m.rq = plane_rsrc((swap ? a.pa : a.pb) + qo, pbytes);
+    if (C && !ADD) m.rq = plane_rsrc((swap ? a.pa : a.pb) + qo, pbytes);
     m.rf = plane_rsrc(a.f + qo, pbytes);
     if (C) m.re = plane_rsrc(a.ec + qc, cbytes);
     if (FORM != kPost) m.rc = plane_rsrc(a.fc + qc, cbytes);
+    if constexpr (ADD) {
+        // (the first rows are loaded by the steps before the strip's first)
+        m.rsl = plane_rsrc(a.sum + qo, a.first ? 0u : unsigned(a.plane) * 8u);
+        m.rss = plane_rsrc(a.sum + qo, unsigned(a.plane) * 8u);
+        m.out_s = m.outl ? unsigned(t.off + c0) * 8u : kDead;
+        m.row_s = unsigned(t.bnx) * 8u;
+#pragma unroll
+        for (int i = 0; i < m.kSum; ++i) m.sum[i] = Pr<double>{{0.0, 0.0}};
+    }
     // row offsets of the lane in each row region
     {
         const int4* ot = reinterpret_cast<const int4*>(a.ip + t.ot);
@@ -459,21 +491,21 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
 
 // Register budgets: the FP64 forms run two waves per SIMD (the cycle form
 // holds a 16-row ring of p and f), FP32 three.
-template <typename T, int FORM, bool ZIN, bool NRM>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
 k_pair(const PArgs<T> args) {
     // strips fastest, each XCD a contiguous range: neighbouring strips share an L2
     const int n = gridDim.x, x = blockIdx.x & 7, l = blockIdx.x >> 3;
     const int id = x * (n >> 3) + min(x, n & 7) + l;
-    pair_body<T, FORM, ZIN, NRM>(args, id % args.ntiles, id / args.ntiles);
+    pair_body<T, FORM, ZIN, NRM, ADD>(args, id % args.ntiles, id / args.ntiles);
 }
 
-template <int FORM, bool ZIN>
+template <int FORM, bool ZIN, bool ADD = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_pair_group(const GEnt* __restrict__ e, int n, const PArgs<float>* __restrict__ jobs) {
     int bx, by;
     const int j = group_locate(e, n, bx, by);
-    pair_body<float, FORM, ZIN, false>(jobs[j], bx, by);
+    pair_body<float, FORM, ZIN, false, ADD>(jobs[j], bx, by);
 }
 
 // ------------------------------- host side -------------------------------
@@ -727,13 +759,16 @@ static PArgs<T> pair_args(const mbp_plan* P, int l, const PairSet& set, const T*
     return a;
 }
 
-template <typename T, int FORM, bool ZIN, bool NRM>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
 static void launch_pair(const mbp_plan* P, int l, const T* f, const T* ec, T* fc, T* pa, T* pb, const int* cycle,
-                        const int* act, const int* nact, int nitems, hipStream_t s) {
-    const void* fn = reinterpret_cast<const void*>(k_pair<T, FORM, ZIN, NRM>);
+                        const int* act, const int* nact, int nitems, hipStream_t s, double* sum = nullptr,
+                        bool first = false) {
+    const void* fn = reinterpret_cast<const void*>(k_pair<T, FORM, ZIN, NRM, ADD>);
     const PairSet& set = pair_choose<T>(P, l, nitems, fn, FORM != kPre);
-    const PArgs<T> a = pair_args<T>(P, l, set, f, ec, fc, pa, pb, cycle, act, nact, NRM);
-    hipLaunchKernelGGL((k_pair<T, FORM, ZIN, NRM>), dim3(set.cnt * ((nitems + 3) / 4)), dim3(256),
+    PArgs<T> a = pair_args<T>(P, l, set, f, ec, fc, pa, pb, cycle, act, nact, NRM);
+    a.sum = sum;
+    a.first = first ? 1 : 0;
+    hipLaunchKernelGGL((k_pair<T, FORM, ZIN, NRM, ADD>), dim3(set.cnt * ((nitems + 3) / 4)), dim3(256),
                        pair_lds_bytes<T>(set.rows, FORM != kPre), s, a);
 }
 
@@ -755,7 +790,15 @@ void pair_post(const mbp_plan* P, int l, const T* p, T* pnew, const T* f, const 
     else launch_pair<T, kPost, true, false>(P, l, f, ec, nullptr, nullptr, pnew, nullptr, act, nact, nitems, s);
 }
 
-// The same, then the next cycle's pre-smoothing and restriction.  zero: p is
+// The same on the finest level, added to the FP64 iterate sum (first: zero so far).
+void pair_post_add(const mbp_plan* P, const float* p, double* sum, bool first, const float* f, const float* ec,
+                   const int* act, const int* nact, int nitems, hipStream_t s) {
+    float* pp = const_cast<float*>(p);
+    if (p) launch_pair<float, kPost, false, false, true>(P, 0, f, ec, nullptr, pp, nullptr, nullptr, act, nact, nitems, s, sum, first);
+    else launch_pair<float, kPost, true, false, true>(P, 0, f, ec, nullptr, nullptr, nullptr, nullptr, act, nact, nitems, s, sum, first);
+}
+
+// The same as pair_post, then the next cycle's pre-smoothing and restriction.  zero: p is
 // zero.  FP64: per-strip squared residual and solution sums too.  cycle:
 // device count of convergence tests that picks the buffers (see PArgs).
 template <typename T>
@@ -806,13 +849,14 @@ GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, 
         if (l < c->P->lds_level32 && c->P->pair_ok[l] && !(down && l == 0 && k > 0)) in.push_back(c);
     const int kind = down ? G_PAIR_PRE
                           : l > 0 ? G_PAIR_POST0
-                                  : last ? (k == 0 ? G_PAIR_POST0 : G_PAIR_POST) : (k == 0 ? G_PAIR_CYCLE0 : G_PAIR_CYCLE);
+                                  : last ? (k == 0 ? G_PAIR_ADD0 : G_PAIR_ADD) : (k == 0 ? G_PAIR_CYCLE0 : G_PAIR_CYCLE);
     GStage none;
     none.kind = kind;
     if (in.empty()) return none;
     const void* fn = down ? reinterpret_cast<const void*>(k_pair_group<kPre, true>)
                      : kind == G_PAIR_POST0 ? reinterpret_cast<const void*>(k_pair_group<kPost, true>)
-                     : kind == G_PAIR_POST  ? reinterpret_cast<const void*>(k_pair_group<kPost, false>)
+                     : kind == G_PAIR_ADD0  ? reinterpret_cast<const void*>(k_pair_group<kPost, true, true>)
+                     : kind == G_PAIR_ADD   ? reinterpret_cast<const void*>(k_pair_group<kPost, false, true>)
                      : kind == G_PAIR_CYCLE0 ? reinterpret_cast<const void*>(k_pair_group<kCycle, true>)
                                              : reinterpret_cast<const void*>(k_pair_group<kCycle, false>);
     auto set = [&](const SolveCtx* c, size_t t) -> const PairSet& {
@@ -846,6 +890,7 @@ GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, 
         float* pb = l == 0 ? ((k & 1) ? P->p32[0] : P->p32B[0]) : P->p32[l];
         jobs.push_back(pair_args<float>(P, l, ps, P->f32[l], down ? nullptr : P->p32[l + 1], P->f32[l + 1], pa, pb, nullptr,
                                         P->d_act, P->d_nact, false));
+        jobs.back().sum = P->phat;
         gx.push_back(ps.cnt);
         gy.push_back((c->nitems + 3) / 4);
     }
@@ -862,7 +907,8 @@ void group_launch_pair(const GStage& st, const unsigned char* dev, hipStream_t s
     switch (st.kind) {
         case G_PAIR_PRE: go(k_pair_group<kPre, true>); break;
         case G_PAIR_POST0: go(k_pair_group<kPost, true>); break;
-        case G_PAIR_POST: go(k_pair_group<kPost, false>); break;
+        case G_PAIR_ADD0: go(k_pair_group<kPost, true, true>); break;
+        case G_PAIR_ADD: go(k_pair_group<kPost, false, true>); break;
         case G_PAIR_CYCLE0: go(k_pair_group<kCycle, true>); break;
         case G_PAIR_CYCLE: go(k_pair_group<kCycle, false>); break;
         default: break;

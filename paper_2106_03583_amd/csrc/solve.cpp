@@ -404,11 +404,13 @@ void ctx_vcycle(SolveCtx& c, hipStream_t s) {
             v.zero = k == 0;
             v.last = k + 1 == inner;
             v.ready = ready;
+            v.sum = v.last ? P->phat : nullptr;
+            v.first = zero;
             launch_vcycle<float>(P, v, s);
             ready = v.ready;
             if (v.flipped) std::swap(v.p, v.pB);
         }
-        launch_add_correction(P, P->phat, v.p, P->d_act, P->d_nact, c.nitems, s, zero);
+        if (!v.added) launch_add_correction(P, P->phat, v.p, P->d_act, P->d_nact, c.nitems, s, zero);
     } else {
         VcycleArgs<double> v{P->phat, P->phatB, P->fhat, P->d_act, P->d_nact, c.nitems};
         v.cycle = P->d_flag + 1;
