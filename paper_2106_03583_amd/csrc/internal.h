@@ -297,17 +297,16 @@ struct VcycleArgs {
 };
 template <typename T>
 int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s);
-// dyn (optional): device count of the partials, read instead of nparts
-void launch_finish(const mbp_plan* P, int nparts, const int* dyn, double* out, const int* act, const int* nact,
-                   int nitems, hipStream_t s);
+// The test of a cycle from nparts partial sums a mode (dyn: their count on the device;
+// nparts 0: p is zero, the residual is the rhs itself), its state and seq into out.
+void launch_test(const mbp_plan* P, int nparts, const int* dyn, double rtol2, double etol2, int retire, int nitems,
+                 hipStream_t s, unsigned long long* out, unsigned seq);
 // Copy the planes of the modes that took an odd number of V-cycles from pB to p.
 void launch_take_odd(const mbp_plan* P, double* p, const double* pB, hipStream_t s);
 // Whole solve of every mode for plans whose hierarchy fits in LDS.
 void launch_lds_full(const mbp_plan* P, double* p, const double* f, const int* act, const int* nact,
                      int nitems, int maxc, double rtol2, double etol2, int* cyc, double* rnorm,
                      double* fnorm, hipStream_t s);
-// First cycle from a zero guess: residual norms are the rhs norms.
-void launch_norm_from_rhs(const mbp_plan* P, int nitems, hipStream_t s);
 
 // kernel timing helpers (solve.cpp)
 void prof_begin(const mbp_plan* P, int cls, hipStream_t s, double cells);
@@ -352,11 +351,12 @@ void pair_post_add(const mbp_plan* P, const float* p, double* sum, bool first, c
 template <typename T>
 void pair_cycle(const mbp_plan* P, int l, T* pa, T* pb, const int* cycle, const T* f, const T* ec, T* fc, bool zero,
                 const int* act, const int* nact, int nitems, hipStream_t s);
-void launch_residual_norm(const mbp_plan* P, const double* p, const double* f, double* rnorm,
-                          const int* act, const int* nact, int nitems, hipStream_t s);
+// partial sums of the squared residual and iterate of the active modes
+void launch_residual_norm(const mbp_plan* P, const double* p, const double* f, const int* act, const int* nact,
+                          int nitems, hipStream_t s);
 // pzero: p is zero (the first refinement step), r = f without reading p
 void launch_residual_to32(const mbp_plan* P, const double* p, const double* f, float* r32,
-                          float* e32, double* rnorm, const int* act, const int* nact, int nitems,
+                          float* e32, const int* act, const int* nact, int nitems,
                           hipStream_t s, bool pzero = false);
 // FP32 finest guess the refinement residual must zero (nullptr: none).
 float* fp32_guess_to_zero(const mbp_plan* P);
@@ -364,8 +364,6 @@ float* fp32_guess_to_zero(const mbp_plan* P);
 void launch_add_correction(const mbp_plan* P, double* p, const float* e32, const int* act,
                            const int* nact, int nitems, hipStream_t s, bool first = false);
 void launch_plane_norm(const mbp_plan* P, const double* f, double* out, hipStream_t s);
-void launch_update_active(const mbp_plan* P, double rtol2, double etol2, int retire, int maxc,
-                          hipStream_t s, double* out = nullptr);
 void launch_zero(double* p, size_t n, hipStream_t s);
 void launch_zero_unrelaxed(const mbp_plan* P, double* p, hipStream_t s);  // modes with cyc == 0
 bool vcycle_zero_start_reads_none(const mbp_plan* P);
@@ -379,7 +377,7 @@ size_t plan_device_bytes(mbp_plan* P);  // builds the strip tables, which the de
 // host buffer of kPinBytes to use for readbacks.
 constexpr size_t kPinBytes = 24 * 1024;  // read-back buffer of a plan
 int plan_set_pinned(mbp_plan* P, void* host);  // use that buffer
-double* pin_state(const mbp_plan* P, int slot);  // device view of its state slot, which the convergence test writes
+unsigned long long* pin_state(const mbp_plan* P, int slot);  // device view of its state slot, which the convergence test writes
 int plan_device_init(mbp_plan* P, void* ext_mem = nullptr, size_t ext_bytes = 0, void* ext_pinned = nullptr);
 void plan_device_free(mbp_plan* P);
 int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags, hipStream_t s,
@@ -408,7 +406,9 @@ struct SolveCtx {
 void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rtol, int flags);
 void ctx_prologue(SolveCtx& c, hipStream_t s);  // ends by writing what ctx_check reads to host memory
 void ctx_check(SolveCtx& c);                    // after the prologue synchronised
-void ctx_test(SolveCtx& c, hipStream_t s, int slot = 0);  // residual norms + convergence, state into the slot
+unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot = 0);  // residual norms + convergence, state into the
+                                                              // slot; its number
+bool ctx_tested(const SolveCtx& c, int slot, unsigned seq);   // that state has arrived
 void ctx_vcycle(SolveCtx& c, hipStream_t s);    // one V-cycle of the active modes
 void ctx_state_apply(SolveCtx& c, int slot = 0);  // after the test synchronised
 void ctx_epilogue(SolveCtx& c, hipStream_t s);

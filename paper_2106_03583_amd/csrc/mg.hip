@@ -16,6 +16,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "wave.h"
 
 namespace mbp {
 
@@ -403,6 +404,7 @@ struct FinJob {
     double* out;
     double* out2;
     const int* dyn = nullptr;  // device count of the partials (optional, instead of ntiles)
+    const double* src = nullptr;  // without partials: the sums themselves (out2 is zero)
 };
 
 __device__ __forceinline__ void finish_body(const FinJob& J, int item) {
@@ -410,6 +412,13 @@ __device__ __forceinline__ void finish_body(const FinJob& J, int item) {
     if (J.act && item >= *J.nact) return;
     const int q = J.act ? J.act[item] : item;
     const int ntiles = J.dyn ? *J.dyn : J.ntiles;
+    if (!J.part) {
+        if (threadIdx.x == 0) {
+            J.out[q] = J.src[q];
+            if (J.out2) J.out2[q] = 0.0;
+        }
+        return;
+    }
     double acc = 0.0, acc2 = 0.0;
     for (int t = threadIdx.x; t < ntiles; t += blockDim.x) {
         acc += J.part[2 * ((long long)q * ntiles + t)];
@@ -469,7 +478,9 @@ struct UpdJob {
     int* cyc;
     double* scal;
     int* state;
-    double* out;  // optional (host-visible): scal[0..1], state[0..3], nact after the update
+    unsigned long long* out;  // optional (host-visible): seq << 32 | modes that have not passed << 8 |
+                              // 1 where the cycles are used up
+    unsigned seq;
 };
 
 __device__ __forceinline__ void update_body(const UpdJob& J) {
@@ -543,17 +554,56 @@ __device__ __forceinline__ void update_body(const UpdJob& J) {
         }
         if (stop && !retire && c > 0) state[2] = 1;
         state[1] = cycle + 1;
-        if (J.out) {
-            J.out[0] = scal[0];
-            J.out[1] = scal[1];
-            int* oi = reinterpret_cast<int*>(J.out + 2);
-            for (int i = 0; i < 4; ++i) oi[i] = state[i];
-            oi[4] = *nact;
-        }
+        // one store, so that no fence (3 us across PCIe) stands between state and number
+        if (J.out)
+            __hip_atomic_store(J.out, (unsigned long long)J.seq << 32 | (unsigned)c << 8 | (state[2] ? 1u : 0u),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
 __global__ void __launch_bounds__(1024) k_update(const UpdJob J) { update_body(J); }
+
+// Both steps of a test in one workgroup, a wave per mode (four at a time, to have
+// their loads in flight together), where there are few partial sums.
+__global__ void __launch_bounds__(1024) k_test(const FinJob F, const UpdJob U) {
+    const int n = *F.nact, ntiles = F.dyn ? *F.dyn : F.ntiles;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    constexpr int B = 4;
+    for (int i0 = wave; i0 < n; i0 += B * nw) {
+        int q[B];
+        double s[B], s2[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            q[b] = F.act[min(i0 + b * nw, n - 1)];
+            s[b] = s2[b] = 0.0;
+        }
+        if (F.part) {
+            for (int t = lane; t < ntiles; t += 64)
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const double2 v = reinterpret_cast<const double2*>(F.part)[(long long)q[b] * ntiles + t];
+                    s[b] += v.x;
+                    s2[b] += v.y;
+                }
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                s[b] = wave_sum63(s[b]);
+                s2[b] = wave_sum63(s2[b]);
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < B; ++b) s[b] = F.src[q[b]];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (lane == 63 && i0 + b * nw < n) {
+                F.out[q[b]] = s[b];
+                F.out2[q[b]] = s2[b];
+            }
+    }
+    __syncthreads();
+    update_body(U);
+}
 
 __global__ void k_zero64(double* p, long long n) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
@@ -1278,27 +1328,6 @@ int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s) {
 template int launch_vcycle<double>(const mbp_plan*, VcycleArgs<double>&, hipStream_t);
 template int launch_vcycle<float>(const mbp_plan*, VcycleArgs<float>&, hipStream_t);
 
-__global__ void k_norm_from_rhs(const double* __restrict__ fnorm, double* __restrict__ rnorm,
-                                double* __restrict__ pnorm, const int* __restrict__ act,
-                                const int* __restrict__ nact) {
-    const int item = blockIdx.x * blockDim.x + threadIdx.x;
-    if (item >= *nact) return;
-    const int q = act[item];
-    rnorm[q] = fnorm[q];
-    pnorm[q] = 0.0;
-}
-
-void launch_norm_from_rhs(const mbp_plan* P, int nitems, hipStream_t s) {
-    hipLaunchKernelGGL(k_norm_from_rhs, dim3((nitems + 255) / 256), dim3(256), 0, s, P->d_fnorm, P->d_rnorm,
-                       P->d_pnorm, P->d_act, P->d_nact);
-}
-
-void launch_finish(const mbp_plan* P, int nparts, const int* dyn, double* out, const int* act, const int* nact,
-                   int nitems, hipStream_t s) {
-    const FinJob F{P->d_part, nparts, act, nact, out, P->d_pnorm, dyn};
-    hipLaunchKernelGGL(k_finish, dim3(nitems), dim3(256), 0, s, F);
-}
-
 void launch_lds_full(const mbp_plan* P, double* p, const double* f, const int* act, const int* nact,
                      int nitems, int maxc, double rtol2, double etol2, int* cyc, double* rnorm,
                      double* fnorm, hipStream_t s) {
@@ -1314,27 +1343,22 @@ void launch_lds_full(const mbp_plan* P, double* p, const double* f, const int* a
                        rnorm, fnorm);
 }
 
-void launch_residual_norm(const mbp_plan* P, const double* p, const double* f, double* rnorm,
-                          const int* act, const int* nact, int nitems, hipStream_t s) {
+void launch_residual_norm(const mbp_plan* P, const double* p, const double* f, const int* act, const int* nact,
+                          int nitems, hipStream_t s) {
     const Level& L = P->levels[0];
     const int per = res_per(L.ntiles, nitems);
     const ResJob J{P->d_blk + L.blk_off, P->d_tiles + L.tile_off, L.ntiles, P->d_dbl, p, f,
                    (long long)L.plane, P->d_shift, act, nact, P->d_part, nullptr, nullptr, per};
     hipLaunchKernelGGL(k_residual<0>, dim3(L.ntiles, (nitems + per - 1) / per), dim3(kTileX, kRowsPerPass), 0, s, J);
-    const FinJob F{P->d_part, L.ntiles, act, nact, rnorm, P->d_pnorm};
-    hipLaunchKernelGGL(k_finish, dim3(nitems), dim3(256), 0, s, F);
 }
 
 void launch_residual_to32(const mbp_plan* P, const double* p, const double* f, float* r32, float* e32,
-                          double* rnorm, const int* act, const int* nact, int nitems, hipStream_t s,
-                          bool pzero) {
+                          const int* act, const int* nact, int nitems, hipStream_t s, bool pzero) {
     const Level& L = P->levels[0];
     const int per = res_per(L.ntiles, nitems);
     const ResJob J{P->d_blk + L.blk_off, P->d_tiles + L.tile_off, L.ntiles, P->d_dbl, p, f,
                    (long long)L.plane, P->d_shift, act, nact, P->d_part, r32, e32, per, pzero ? 1 : 0};
     hipLaunchKernelGGL(k_residual<1>, dim3(L.ntiles, (nitems + per - 1) / per), dim3(kTileX, kRowsPerPass), 0, s, J);
-    const FinJob F{P->d_part, L.ntiles, act, nact, rnorm, P->d_pnorm};
-    hipLaunchKernelGGL(k_finish, dim3(nitems), dim3(256), 0, s, F);
 }
 
 void launch_add_correction(const mbp_plan* P, double* p, const float* e32, const int* act,
@@ -1353,11 +1377,30 @@ void launch_plane_norm(const mbp_plan* P, const double* f, double* out, hipStrea
     hipLaunchKernelGGL(k_finish, dim3(P->g.nz), dim3(256), 0, s, F);
 }
 
-void launch_update_active(const mbp_plan* P, double rtol2, double etol2, int retire, int maxc,
-                          hipStream_t s, double* out) {
-    const UpdJob J{P->g.nz, P->d_rnorm, P->d_fnorm, P->d_pnorm, P->d_sabs, rtol2, etol2,
-                   retire, maxc, P->d_act, P->d_nact, P->d_cyc, P->d_scal, P->d_flag, out};
-    hipLaunchKernelGGL(k_update, dim3(1), dim3(1024), 0, s, J);
+static FinJob fin_job(const mbp_plan* P, int nparts, const int* dyn) {
+    return FinJob{nparts ? P->d_part : nullptr, nparts, P->d_act, P->d_nact, P->d_rnorm, P->d_pnorm, dyn, P->d_fnorm};
+}
+
+static UpdJob upd_job(const mbp_plan* P, double rtol2, double etol2, int retire, unsigned long long* out, unsigned seq) {
+    return UpdJob{P->g.nz, P->d_rnorm, P->d_fnorm, P->d_pnorm, P->d_sabs, rtol2, etol2, retire, P->opt.max_cycles,
+                  P->d_act, P->d_nact, P->d_cyc, P->d_scal, P->d_flag, out, seq};
+}
+
+// One launch up to this many partial pairs: 1,500 pairs take 8.0 us (two launches
+// 9.2), 5,800 9.8 (9.5), 30,000 18 (9.5).
+constexpr long long kTestPairs = 4096;
+
+void launch_test(const mbp_plan* P, int nparts, const int* dyn, double rtol2, double etol2, int retire, int nitems,
+                 hipStream_t s, unsigned long long* out, unsigned seq) {
+    const FinJob F = fin_job(P, nparts, dyn);
+    const UpdJob U = upd_job(P, rtol2, etol2, retire, out, seq);
+    const long long pairs = (long long)nitems * std::max(1, dyn ? pair_max_strips(P, 0) : nparts);
+    if (pairs <= kTestPairs) {
+        hipLaunchKernelGGL(k_test, dim3(1), dim3(1024), 0, s, F, U);
+        return;
+    }
+    hipLaunchKernelGGL(k_finish, dim3(nitems), dim3(256), 0, s, F);
+    hipLaunchKernelGGL(k_update, dim3(1), dim3(1024), 0, s, U);
 }
 
 void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out) {
@@ -1488,8 +1531,7 @@ GStage group_finish(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     std::vector<FinJob> jobs;
     std::vector<int> gx, gy;
     for (const SolveCtx* c : cs) {
-        const mbp_plan* P = c->P;
-        jobs.push_back(FinJob{P->d_part, P->levels[0].ntiles, P->d_act, P->d_nact, P->d_rnorm, P->d_pnorm});
+        jobs.push_back(fin_job(c->P, c->P->levels[0].ntiles, nullptr));
         gx.push_back(c->nitems);
         gy.push_back(1);
     }
@@ -1500,16 +1542,11 @@ GStage group_update(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     std::vector<UpdJob> jobs;
     std::vector<int> gx, gy;
     for (const SolveCtx* c : cs) {
-        const mbp_plan* P = c->P;
-        jobs.push_back(UpdJob{P->g.nz, P->d_rnorm, P->d_fnorm, P->d_pnorm, P->d_sabs, c->rtol2, c->etol2,
-                              c->retire ? 1 : 0, P->opt.max_cycles, P->d_act, P->d_nact, P->d_cyc, P->d_scal,
-                              P->d_flag, pin_state(P, 0)});
+        jobs.push_back(upd_job(c->P, c->rtol2, c->etol2, c->retire ? 1 : 0, pin_state(c->P, 0), 0));
         gx.push_back(1);
         gy.push_back(1);
     }
-    GStage st = group_build(gb, G_UPDATE, jobs, gx, gy);
-    st.threads = 1024;
-    return st;
+    return group_build(gb, G_UPDATE, jobs, gx, gy);
 }
 
 GStage group_addcorr(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {

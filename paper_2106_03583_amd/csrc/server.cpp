@@ -106,6 +106,9 @@ struct Request {
     Stage stage = kQueued;
     SolveCtx ctx;
     hipEvent_t ev = nullptr;
+    unsigned seq = 0;            // the last test queued
+    bool checked = true;         // the rhs passed its checks
+    Clock::time_point t_issue;   // when its cycles were queued, or the stream last asked
     std::unique_ptr<mbp_plan> host;  // host plan built at submission (none when cached)
     // result
     int status = MBP_OK;
@@ -223,6 +226,17 @@ struct mbp_server {
         return cache.back().get();
     }
 
+    // Queue the next cycles of a request.
+    void cycles(Request* r) {
+        hipStream_t s = streams[r->slot];
+        for (int k = 0; k < kCyclesPerStep; ++k) {
+            r->seq = ctx_test(r->ctx, s);
+            ctx_vcycle(r->ctx, s);
+        }
+        r->t_issue = Clock::now();
+        r->stage = kCycles;
+    }
+
     // Start (or move on) one request; returns true if it made progress.
     bool step(Request* r) {
         hipStream_t s = streams[r->slot];
@@ -231,12 +245,26 @@ struct mbp_server {
             case kQueued:
                 ctx_init(c, r->cp->plan, r->rhs, r->p, r->rtol, r->flags | opt.flags | MBP_RETIRE);
                 ctx_prologue(c, s);
+                if (!c.full_lds) {  // its checks are read with the first state
+                    cycles(r);
+                    r->checked = false;
+                    return true;
+                }
                 (void)hipEventRecord(r->ev, s);
                 r->stage = kPrologue;
                 return true;
             case kPrologue:
             case kCycles: {
-                const hipError_t q = hipEventQuery(r->ev);
+                // the state of a test arrives while the V-cycle behind it runs; the
+                // stream is asked for errors only when none has come for a while
+                hipError_t q = hipErrorNotReady;
+                if (r->stage == kPrologue) q = hipEventQuery(r->ev);
+                else if (ctx_tested(c, 0, r->seq)) q = hipSuccess;
+                else if (Clock::now() - r->t_issue > std::chrono::milliseconds(5)) {
+                    r->t_issue = Clock::now();
+                    q = hipStreamQuery(s);
+                    if (q == hipSuccess && !ctx_tested(c, 0, r->seq)) q = hipErrorUnknown;
+                }
                 if (q == hipErrorNotReady) return false;
                 if (q != hipSuccess) {
                     c.status = MBP_ERR_HIP;
@@ -250,7 +278,9 @@ struct mbp_server {
                         c.done = true;
                     }
                 } else {
-                    ctx_state_apply(c);
+                    if (!r->checked) ctx_check(c);
+                    r->checked = true;
+                    if (!c.done) ctx_state_apply(c);
                 }
                 if (c.done) {
                     ctx_epilogue(c, s);
@@ -258,12 +288,7 @@ struct mbp_server {
                     r->stage = kEpilogue;
                     return true;
                 }
-                for (int k = 0; k < kCyclesPerStep; ++k) {
-                    ctx_test(c, s);
-                    ctx_vcycle(c, s);
-                }
-                (void)hipEventRecord(r->ev, s);
-                r->stage = kCycles;
+                cycles(r);
                 return true;
             }
             case kEpilogue: {
@@ -387,7 +412,7 @@ int mbp_server_create(size_t hbm_budget, int slots, const mbp_options* opt, mbp_
         return MBP_ERR_NOMEM;
     }
     S->arena.init(hbm_budget);
-    if (hipHostMalloc(&S->pinned, size_t(slots) * kPinBytes, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&S->pinned, size_t(slots) * kPinBytes, hipHostMallocCoherent) != hipSuccess) {
         (void)hipFree(S->arena_mem);
         delete S;
         return MBP_ERR_NOMEM;

@@ -1,5 +1,6 @@
 // Device workspace and the solve drivers (Algorithm 1 on one plan).
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -248,7 +249,7 @@ int plan_device_init(mbp_plan* P, void* ext_mem, size_t ext_bytes, void* ext_pin
         return plan_set_pinned(P, ext_pinned);
     }
     void* hp = nullptr;
-    if (hipHostMalloc(&hp, kPinBytes, hipHostMallocDefault) != hipSuccess) return MBP_ERR_NOMEM;
+    if (hipHostMalloc(&hp, kPinBytes, hipHostMallocCoherent) != hipSuccess) return MBP_ERR_NOMEM;
     P->owns_pinned = true;
     return plan_set_pinned(P, hp);
 }
@@ -311,8 +312,7 @@ namespace {
 // layout (doubles) of the plan's pinned buffer, which kernels write directly: a copy
 // is a dispatch of its own between two kernels
 constexpr int kPinStart = 0;    // after the prologue: ints flag[0..3], area sum, mode 0's norm
-constexpr int kPinSlots = 64;   // state slots of the tests
-constexpr int kSlotDoubles = 8; //   each scal[0..1], then ints flag[0..3], nact
+constexpr int kPinSlots = 64;   // state slots of the tests, a 64-bit word each (mg.hip: UpdJob)
 constexpr int kSlots = 3;
 constexpr int kPinReport = 128; // at the end: max ratio, then ints most cycles, cycles per mode
 static_assert(kPinReport * 8 + 8 + 4 * (1 + 4096) <= kPinBytes, "one int a mode");
@@ -321,7 +321,12 @@ double* pin_host(const mbp_plan* P, int at) { return static_cast<double*>(P->hos
 double* pin_dev(const mbp_plan* P, int at) { return static_cast<double*>(P->pinned_dev) + at; }
 }  // namespace
 
-double* pin_state(const mbp_plan* P, int slot) { return pin_dev(P, kPinSlots + slot * kSlotDoubles); }
+unsigned long long* pin_state(const mbp_plan* P, int slot) {
+    return reinterpret_cast<unsigned long long*>(pin_dev(P, kPinSlots + slot));
+}
+static uint64_t state_word(const SolveCtx& c, int slot) {
+    return __atomic_load_n(reinterpret_cast<const uint64_t*>(pin_host(c.P, kPinSlots + slot)), __ATOMIC_ACQUIRE);
+}
 
 void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rtol, int flags) {
     c = SolveCtx{};
@@ -375,19 +380,41 @@ void ctx_check(SolveCtx& c) {
 
 // Convergence test of the current iterate (Sec. 3's per-mode systems each
 // stop on their own when retiring).
-void ctx_test(SolveCtx& c, hipStream_t s, int slot) {
+unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot) {
     mbp_plan* P = c.P;
     const bool zero = c.cycles == 0 && !c.warm;  // p = 0: the residual is f itself
     if (c.mixed)
-        launch_residual_to32(P, P->phat, P->fhat, P->f32[0], fp32_guess_to_zero(P), P->d_rnorm, P->d_act, P->d_nact,
+        launch_residual_to32(P, P->phat, P->fhat, P->f32[0], fp32_guess_to_zero(P), P->d_act, P->d_nact,
                              c.nitems, s, zero);
-    else if (zero)
-        launch_norm_from_rhs(P, c.nitems, s);
-    else if (c.fused_parts > 0)
-        launch_finish(P, c.fused_parts, c.flip ? P->d_flag + 3 : nullptr, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
-    else
-        launch_residual_norm(P, P->phat, P->fhat, P->d_rnorm, P->d_act, P->d_nact, c.nitems, s);
-    launch_update_active(P, c.rtol2, c.etol2, c.retire ? 1 : 0, P->opt.max_cycles, s, pin_state(P, slot));
+    else if (!zero && c.fused_parts == 0)
+        launch_residual_norm(P, P->phat, P->fhat, P->d_act, P->d_nact, c.nitems, s);
+    // a number no other test has: buffers pass from plan to plan in a server
+    static std::atomic<unsigned> tests{0};
+    const unsigned seq = ++tests;
+    const bool fused = !c.mixed && c.fused_parts > 0;
+    const int parts = !c.mixed && zero ? 0 : fused ? c.fused_parts : P->levels[0].ntiles;
+    launch_test(P, parts, fused && c.flip ? P->d_flag + 3 : nullptr, c.rtol2, c.etol2, c.retire ? 1 : 0, c.nitems, s,
+                pin_state(P, slot), seq);
+    return seq;
+}
+
+bool ctx_tested(const SolveCtx& c, int slot, unsigned seq) { return unsigned(state_word(c, slot) >> 32) == seq; }
+
+// Wait for the state of a test.  An event behind each test would do, but its
+// packet holds the queue for 6 us a cycle; the stream is only asked (for
+// errors) when nothing has come for some milliseconds.
+static int wait_test(const SolveCtx& c, hipStream_t s, int slot, unsigned seq) {
+    auto t0 = std::chrono::steady_clock::now();
+    for (unsigned i = 1; !ctx_tested(c, slot, seq); ++i) {
+        if (i & 1023) continue;
+        const auto t = std::chrono::steady_clock::now();
+        if (t - t0 < std::chrono::milliseconds(5)) continue;
+        t0 = t;
+        const hipError_t q = hipStreamQuery(s);
+        if (q == hipSuccess) return ctx_tested(c, slot, seq) ? MBP_OK : MBP_ERR_HIP;
+        if (q != hipErrorNotReady) return MBP_ERR_HIP;
+    }
+    return MBP_OK;
 }
 
 void ctx_vcycle(SolveCtx& c, hipStream_t s) {
@@ -426,16 +453,10 @@ void ctx_vcycle(SolveCtx& c, hipStream_t s) {
 // After the test synchronised: stop when every mode retired (retiring form) or
 // every mode passed (lockstep), or when the cycle budget ran out.
 void ctx_state_apply(SolveCtx& c, int slot) {
-    const double* sl = pin_host(c.P, kPinSlots + slot * kSlotDoubles);
-    const int* hi = reinterpret_cast<const int*>(sl + 2);  // flag[0..3], nact
-    const bool hitmax = hi[2] != 0;
-    bool converged;
-    if (c.retire) {
-        c.nitems = hi[4];
-        converged = c.nitems == 0 && !hitmax;
-    } else {
-        converged = sl[1] == 0.0;  // modes that have not passed
-    }
+    const uint64_t w = state_word(c, slot);
+    const int left = int(w >> 8 & 0xffffff);  // modes that have not passed
+    const bool hitmax = (w & 1) != 0, converged = left == 0 && !hitmax;
+    if (c.retire) c.nitems = left;
     if (converged) {
         c.done = true;
     } else if (hitmax) {
@@ -513,25 +534,17 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
         if (hipStreamSynchronize(s) != hipSuccess) st = MBP_ERR_HIP;
         else ctx_check(c);
     } else {
-        hipEvent_t sev[kSlots];
-        for (auto& e : sev) (void)hipEventCreateWithFlags(&e, hipEventDisableTiming);
-        auto test = [&](int k) {
-            ctx_test(c, s, k % kSlots);
-            (void)hipEventRecord(sev[k % kSlots], s);
-        };
-        test(0);
+        unsigned seq = ctx_test(c, s, 0);
         for (int k = 0;; ++k) {
             ctx_vcycle(c, s);
-            test(k + 1);
-            if (hipEventSynchronize(sev[k % kSlots]) != hipSuccess) {
-                st = MBP_ERR_HIP;
-                break;
-            }
+            const unsigned next = ctx_test(c, s, (k + 1) % kSlots);
+            st = wait_test(c, s, k % kSlots, seq);
+            if (st != MBP_OK) break;
+            seq = next;
             if (k == 0) ctx_check(c);
             if (!c.done) ctx_state_apply(c, k % kSlots);
             if (c.done) break;
         }
-        for (auto& e : sev) (void)hipEventDestroy(e);
     }
     if (!finished) {
         (void)hipEventRecord(ev[2], s);
