@@ -434,6 +434,7 @@ struct GStage {
     size_t job_off = 0;
     size_t lds = 0;         // dynamic LDS bytes (LDS-resident stage)
     int threads = 256;
+    bool odd = false;       // pair march: some plane is odd
 };
 // Host image of the tables of every stage; uploaded once per capture.
 struct GroupBlob {

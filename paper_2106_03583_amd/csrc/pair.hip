@@ -42,9 +42,14 @@
 // eight-block obstacle (mixed) 12.5 -> 7.0 ms, 24 uneven boxes in one mixed batch
 // 31.8 -> 18.7 ms.
 //
-// Levels qualify when every block is even in x and y and at least 8 cells
-// both ways (pairs and coarse cells then align in every block, and the halo
-// stays inside the neighbour); the strip kernels of march.hip run the others.
+// Levels qualify when every block has at least 8 cells both ways and odd counts end
+// at walls (pairs and coarse cells then align in every block, and the halo stays
+// inside the neighbour); the strip kernels of march.hip run the others.  An odd
+// count leaves one cell alone in the last lane, or row, as the third child of the
+// last coarse cell: forms of their own (ODD), since what they add (a masked store a
+// row, a shift in the restriction, a select in the interpolation) costs even planes
+// registers.  203 x 157, 90 modes: 34 + 41 us of strip sweeps a cycle -> 40 us, a
+// lockstep solve 2.20 -> 1.51 ms.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -149,11 +154,14 @@ enum { kPre = 0, kPost = 1, kCycle = 2 };
 
 // ADD (FP32, the last sweep of a correction solve): the result is added to the FP64
 // iterate instead of being stored; the iterate's rows are loaded kSum steps ahead.
-template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false, bool ODD = false>
 struct March {
     static constexpr bool C = FORM != kPre, R = FORM != kPost;
-    // rows loaded ahead: the ring minus the rows the last stage still reads
-    static constexpr int kAhead = FORM == kCycle || ADD ? 6 : 8;
+    // rows loaded ahead: at most the ring minus the rows the last stage still reads.  Six
+    // in the odd forms too: with eight, hipcc 7.2 gave a register of a row still to be
+    // relaxed to a diagonal in the FP32 PRE form (seen in its assembly), and two of
+    // eight restricted rows were wrong.
+    static constexpr int kAhead = FORM == kCycle || ADD || ODD ? 6 : 8;
 
     // strip constants
     int lane, y0, y1, bny, ncy, kend;
@@ -165,6 +173,10 @@ struct March {
     T sig, wr0, wr1;
     __amdgpu_buffer_rsrc_t rp, rq, rf, re, rc;
     bool outl;
+    // ODD (some block's count is odd): the last coarse cell of such a row or column
+    // has three children, the third alone in its lane (row)
+    bool oy, out1, lastc;   // odd rows; both cells of the lane are output; lane of the last coarse cell
+    unsigned out_1;         // the lone cell
     // moving state
     int kc;                               // row of ring slot 0
     Pr<T> p[kRing], f[kRing];
@@ -255,10 +267,15 @@ struct March {
                 const int j = (k - 2) >> 1;
                 const T* w = sW + (region(j, ncy) * 64 + lane) * 4;
                 const Pr<T> w0 = *reinterpret_cast<const Pr<T>*>(w), w1 = *reinterpret_cast<const Pr<T>*>(w + 2);
-                const T l = from_left(e[ie]), r = from_right(e[ie]);
-                xlo = xhi;
-                xhi.v[0] = w0.v[0] * l + w0.v[1] * e[ie];
-                xhi.v[1] = w1.v[0] * e[ie] + w1.v[1] * r;
+                const T l = from_left(e[ie]);
+                T r = from_right(e[ie]);
+                if (ODD) r = lastc ? l : r;
+                // (the last two rows of an odd count lie between the last two coarse rows)
+                if (!ODD || !(oy & (j >= ncy))) {
+                    xlo = xhi;
+                    xhi.v[0] = w0.v[0] * l + w0.v[1] * e[ie];
+                    xhi.v[1] = w1.v[0] * e[ie] + w1.v[1] * r;
+                }
                 unsigned o;
                 advance_coarse(j + 4, o);
                 e[ie] = load_one(re, o, T(0));
@@ -280,15 +297,21 @@ struct March {
                     Pr<double> v = sum[w];
                     v.v[0] += double(p[i].v[0]);
                     v.v[1] += double(p[i].v[1]);
-                    store_pair(rss, pick(in, out_s + unsigned(max(r, 0)) * row_s, kDead), v);
+                    if (ODD) {
+                        store_pair(rss, pick(in & out1, out_s + unsigned(max(r, 0)) * row_s, kDead), v);
+                        store_one(rss, pick(in & (out_1 != kDead), out_s + unsigned(max(r, 0)) * row_s, kDead), v.v[0]);
+                    } else {
+                        store_pair(rss, pick(in, out_s + unsigned(max(r, 0)) * row_s, kDead), v);
+                    }
                     const int n = r + kSum;
                     sum[w] = load_pair(rsl, pick(inside(n), out_s + unsigned(max(n, 0)) * row_s, kDead), 0.0);
                 } else {
                     store_pair(rq, pick(in, out_p + unsigned(max(r, 0)) * row_p, kDead), p[i]);
+                    if (ODD) store_one(rq, pick(in, out_1 + unsigned(max(r, 0)) * row_p, kDead), p[i].v[0]);
                 }
                 if (NRM) {
                     const T a = p[i].v[0], b = p[i].v[1];
-                    const T sum = a * a + b * b;
+                    const T sum = a * a + (ODD && !out1 ? T(0) : b * b);
                     pnr += double((in & outl) ? sum : T(0));
                 }
             }
@@ -306,7 +329,7 @@ struct March {
                     const int r = k - 6;
                     const T res = t - d * p[i].v[S0];
                     const T sq = res * res;
-                    nrm += double((inside(r) & outl) ? sq : T(0));
+                    nrm += double((inside(r) & (ODD && S0 == 1 ? out1 : outl)) ? sq : T(0));
                 }
                 p[i].v[S0] = div_nr(t, d);
             }
@@ -320,13 +343,21 @@ struct March {
             constexpr int i = (U - LAG) & M;
             T d;
             const T o = around<U, LAG, S>(d);
-            const T w = (f[i].v[S] - o - d * p[i].v[S]) * (S == 0 ? wr0 : wr1) * (yb + kYw * (U - LAG) + z)[3];
+            T w = (f[i].v[S] - o - d * p[i].v[S]) * (S == 0 ? wr0 : wr1) * (yb + kYw * (U - LAG) + z)[3];
+            const int r = k - LAG;
+            const bool in = inside(r);
             if constexpr (S == 0) {
+                if (ODD) {
+                    const T third = from_right(w);
+                    w += lastc ? third : T(0);
+                    const bool end = oy & (r == bny - 1);  // third row of the last coarse cell
+                    store_one(rc, pick(in & end, out_c + unsigned(max((r >> 1) - 1, 0)) * row_c, kDead), acc + w);
+                }
                 acc = w;  // even row: the coarse cell's first
             } else {
-                const int r = k - LAG;
-                const bool in = inside(r);
-                store_one(rc, pick(in, out_c + unsigned(max(r >> 1, 0)) * row_c, kDead), acc + w);
+                acc += w;
+                const bool more = ODD && (oy & (r == bny - 2));
+                store_one(rc, pick(in & !more, out_c + unsigned(max(r >> 1, 0)) * row_c, kDead), acc);
             }
         }
         // row k + kAhead takes the slot of a row no stage reads any more
@@ -371,7 +402,7 @@ __host__ __device__ constexpr size_t pair_lds_bytes(int rows, bool corr) {
     return (size_t(kXw + kXd + (corr ? kXp : 0)) + 3 * size_t(rows + kUp + kDown) * kYw) * sizeof(T);
 }
 
-template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false, bool ODD = false>
 __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nact = *a.nact;
@@ -398,7 +429,7 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     if (mi >= nact) return;
     const int q = __builtin_amdgcn_readfirstlane(a.act[mi]);
 
-    March<T, FORM, ZIN, NRM, ADD> m;
+    March<T, FORM, ZIN, NRM, ADD, ODD> m;
     m.lane = lane;
     m.y0 = t.y0;
     m.y1 = t.y1;
@@ -422,6 +453,15 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
     m.out_p = m.outl ? unsigned(t.off + c0) * sz : kDead;
     m.out_c = m.outl ? unsigned(t.coff + (c0 >> 1)) * sz : kDead;
     m.row_p = unsigned(t.bnx) * sz;
+    if (ODD) {
+        const bool ox = t.bnx & 1, lone = ox & (c0 == t.bnx - 1);
+        m.oy = t.bny & 1;
+        m.out1 = m.outl & !lone;
+        m.lastc = ox & (c0 == t.bnx - 3);
+        m.out_1 = m.outl & lone ? m.out_p : kDead;
+        m.out_p = lone ? kDead : m.out_p;
+        m.out_c = lone ? kDead : m.out_c;
+    }
     m.row_c = unsigned(t.ncx) * sz;
     const unsigned pbytes = unsigned(a.plane) * sz, cbytes = unsigned(a.plane_c) * sz;
     const bool swap = a.cycle ? ((*a.cycle - 1) & 1) != 0 : false;
@@ -491,21 +531,21 @@ __device__ __forceinline__ void pair_body(const PArgs<T>& a, int bx, int by) {
 
 // Register budgets: the FP64 forms run two waves per SIMD (the cycle form
 // holds a 16-row ring of p and f), FP32 three.
-template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false, bool ODD = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3)))
 k_pair(const PArgs<T> args) {
     // strips fastest, each XCD a contiguous range: neighbouring strips share an L2
     const int n = gridDim.x, x = blockIdx.x & 7, l = blockIdx.x >> 3;
     const int id = x * (n >> 3) + min(x, n & 7) + l;
-    pair_body<T, FORM, ZIN, NRM, ADD>(args, id % args.ntiles, id / args.ntiles);
+    pair_body<T, FORM, ZIN, NRM, ADD, ODD>(args, id % args.ntiles, id / args.ntiles);
 }
 
-template <int FORM, bool ZIN, bool ADD = false>
+template <int FORM, bool ZIN, bool ADD = false, bool ODD = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_pair_group(const GEnt* __restrict__ e, int n, const PArgs<float>* __restrict__ jobs) {
     int bx, by;
     const int j = group_locate(e, n, bx, by);
-    pair_body<float, FORM, ZIN, false, ADD>(jobs[j], bx, by);
+    pair_body<float, FORM, ZIN, false, ADD, ODD>(jobs[j], bx, by);
 }
 
 // ------------------------------- host side -------------------------------
@@ -532,20 +572,40 @@ int block_beyond(const Geometry& g, int b, int rr, int cr) {
 
 }  // namespace
 
-// Every block even and at least 8 x 8 with the aligned 2 : 1 transfer the
-// march assumes (fine cells 2I, 2I + 1 between coarse I - 1, I, I + 1), one
-// sweep before and after the correction, no extra colours.
+static bool pair_odd(const mbp_plan* P, int l) {
+    for (int b = 0; b < P->levels[l].nb; ++b)
+        if ((P->levels[l].nx[b] | P->levels[l].ny[b]) & 1) return true;
+    return false;
+}
+
+// Every block at least 8 x 8, with the aligned 2 : 1 transfer the march assumes
+// (fine cells 2I, 2I + 1 between coarse I - 1, I, I + 1), one sweep before and after
+// the correction, no extra colours.  An odd count (whose last coarse cell I has the
+// children 2I .. 2I + 2, the second between I - 1 and I or beyond I) only where a
+// wall ends it: beyond a joined face the pairs of the two blocks would not align.
 bool pair_level_ok(const mbp_plan* P, int l) {
     if (P->opt.nu1 != 1 || P->opt.nu2 != 1 || l + 1 >= P->nlev) return false;
     const Level& L = P->levels[l];
     if (!L.cx || !L.cy || !march_level_ok(P, l) || L.plane >= (int64_t(1) << 27)) return false;
     for (int b = 0; b < L.nb; ++b) {
         const DBlock& d = P->hblk[L.blk_off + b];
-        if ((d.nx & 1) || (d.ny & 1) || d.nx < 8 || d.ny < 8 || d.par != 0) return false;
-        for (int i = 0; i < d.nx; ++i)
-            if (P->hint[d.pcx + i] != ((i & 1) ? i / 2 : i / 2 - 1)) return false;
-        for (int j = 0; j < d.ny; ++j)
-            if (P->hint[d.pcy + j] != ((j & 1) ? j / 2 : j / 2 - 1)) return false;
+        if (d.nx < 8 || d.ny < 8 || d.par != 0) return false;
+        if (((d.nx & 1) && d.nbr[XP] >= 0) || ((d.ny & 1) && d.nbr[YP] >= 0)) return false;
+        auto aligned = [&](int at, int n) {
+            const int I = n / 2 - 1;  // last coarse cell
+            for (int i = 0; i < n; ++i) {
+                const int c = P->hint[at + i];
+                if ((n & 1) && i == n - 2) {
+                    if (c != I - 1 && c != I) return false;
+                } else if ((n & 1) && i == n - 1) {
+                    if (c != I) return false;
+                } else if (c != ((i & 1) ? i / 2 : i / 2 - 1)) {
+                    return false;
+                }
+            }
+            return true;
+        };
+        if (!aligned(d.pcx, d.nx) || !aligned(d.pcy, d.ny)) return false;
     }
     return true;
 }
@@ -587,18 +647,25 @@ void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes,
                     hi += sign(k, YM) * lo;
                     lo = 0.0;
                 }
-                if (j == e.ny - 1 && g.nbr[k][YP] < 0) {
+                if ((e.ny & 1) && j >= e.ny - 2) {
+                    // the last two rows of an odd count, between the last two coarse rows
+                    if (P->hint[e.pcy + j] == e.ny / 2 - 1) {
+                        hi = lo + sign(k, YP) * hi;
+                        lo = 0.0;
+                    }
+                } else if (j == e.ny - 1 && g.nbr[k][YP] < 0) {
                     lo += sign(k, YP) * hi;
                     hi = 0.0;
                 }
                 y[4] = lo;
                 y[5] = hi;
             }
-        const int ns = (d.nx + wmax - 1) / wmax;
+        const int ns = (d.nx + (d.nx & 1) + wmax - 1) / wmax;
         for (int s = 0; s < ns; ++s) {
             PTile t{};
             t.x0 = 2 * int((long long)(d.nx / 2) * s / ns);
             t.w = 2 * int((long long)(d.nx / 2) * (s + 1) / ns) - t.x0;
+            if (s + 1 == ns) t.w = d.nx - t.x0;
             t.bnx = d.nx;
             t.bny = d.ny;
             t.off = d.off;
@@ -630,15 +697,35 @@ void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes,
                     }
                     const DBlock e = blk(k);
                     const int ci = cr == 0 ? e.nx + c : (cr == 2 ? c - d.nx : c);
+                    const bool lone = ci + 1 == e.nx;  // the last cell of an odd count
                     for (int sl = 0; sl < 2; ++sl) {
+                        if (sl && lone) {
+                            xd[(rr * 2 + sl) * 64 + lane] = 1e30;
+                            continue;
+                        }
                         xw[((rr * 2 + sl) * 64 + lane) * 2] = P->hdbl[e.cx + ci + sl];
                         xw[((rr * 2 + sl) * 64 + lane) * 2 + 1] = P->hdbl[e.cx + e.nx + ci + sl];
                         xd[(rr * 2 + sl) * 64 + lane] = P->hdbl[e.cx + 2 * e.nx + ci + sl];
                     }
-                    double wl = P->hdbl[e.pwx + ci], w0e = 1.0 - wl, w0o = P->hdbl[e.pwx + ci + 1], wr = 1.0 - w0o;
+                    double wl = P->hdbl[e.pwx + ci], w0e = 1.0 - wl;
+                    double w0o = lone ? 0.0 : P->hdbl[e.pwx + ci + 1], wr = lone ? 0.0 : 1.0 - w0o;
                     if (ci == 0 && g.nbr[k][XM] < 0) {
                         w0e += sign(k, XM) * wl;
                         wl = 0.0;
+                    }
+                    if (lone) {  // its lower coarse cell is the left lane's, beyond is the wall
+                        wl += sign(k, XP) * w0e;
+                        w0e = 0.0;
+                    }
+                    if ((e.nx & 1) && ci == e.nx - 3) {
+                        // the middle child of the last coarse cell: the third weight goes with
+                        // the coarse cell to the left (March::lastc)
+                        if (P->hint[e.pcx + ci + 1] == e.nx / 2 - 1) {
+                            w0o += sign(k, XP) * wr;
+                            wr = 0.0;
+                        } else {
+                            std::swap(w0o, wr);
+                        }
                     }
                     if (ci == e.nx - 2 && g.nbr[k][XP] < 0) {
                         w0o += sign(k, XP) * wr;
@@ -651,7 +738,7 @@ void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes,
                     w4[3] = wr;
                     if (rr == 1 && c >= t.x0 && c < t.x0 + t.w) {
                         xr[2 * lane] = P->hdbl[e.rwx + ci];
-                        xr[2 * lane + 1] = P->hdbl[e.rwx + ci + 1];
+                        xr[2 * lane + 1] = lone ? 0.0 : P->hdbl[e.rwx + ci + 1];
                     }
                     const int up = rr == 0 ? e.ny : (rr == 2 ? -d.ny : 0);  // row of the neighbour's row 0
                     const int cup = rr == 0 ? Lc.ny[k] : (rr == 2 ? -Lc.ny[b] : 0);
@@ -677,7 +764,7 @@ void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes,
                 for (size_t s = s0; s < s1; ++s) {
                     PTile t = strips[s];
                     t.y0 = 2 * int((long long)(ny / 2) * y / nseg);
-                    t.y1 = 2 * int((long long)(ny / 2) * (y + 1) / nseg);
+                    t.y1 = y + 1 == nseg ? ny : 2 * int((long long)(ny / 2) * (y + 1) / nseg);
                     ps.rows = std::max(ps.rows, t.y1 - t.y0);
                     out.push_back(t);
                 }
@@ -759,16 +846,21 @@ static PArgs<T> pair_args(const mbp_plan* P, int l, const PairSet& set, const T*
     return a;
 }
 
-template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false>
+template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false, bool ODD = false>
 static void launch_pair(const mbp_plan* P, int l, const T* f, const T* ec, T* fc, T* pa, T* pb, const int* cycle,
                         const int* act, const int* nact, int nitems, hipStream_t s, double* sum = nullptr,
                         bool first = false) {
-    const void* fn = reinterpret_cast<const void*>(k_pair<T, FORM, ZIN, NRM, ADD>);
+    if constexpr (!ODD)
+        if (pair_odd(P, l)) {
+            launch_pair<T, FORM, ZIN, NRM, ADD, true>(P, l, f, ec, fc, pa, pb, cycle, act, nact, nitems, s, sum, first);
+            return;
+        }
+    const void* fn = reinterpret_cast<const void*>(k_pair<T, FORM, ZIN, NRM, ADD, ODD>);
     const PairSet& set = pair_choose<T>(P, l, nitems, fn, FORM != kPre);
     PArgs<T> a = pair_args<T>(P, l, set, f, ec, fc, pa, pb, cycle, act, nact, NRM);
     a.sum = sum;
     a.first = first ? 1 : 0;
-    hipLaunchKernelGGL((k_pair<T, FORM, ZIN, NRM, ADD>), dim3(set.cnt * ((nitems + 3) / 4)), dim3(256),
+    hipLaunchKernelGGL((k_pair<T, FORM, ZIN, NRM, ADD, ODD>), dim3(set.cnt * ((nitems + 3) / 4)), dim3(256),
                        pair_lds_bytes<T>(set.rows, FORM != kPre), s, a);
 }
 
@@ -834,6 +926,18 @@ template void pair_cycle<double>(const mbp_plan*, int, double*, double*, const i
 template void pair_cycle<float>(const mbp_plan*, int, float*, float*, const int*, const float*, const float*, float*,
                                 bool, const int*, const int*, int, hipStream_t);
 
+template <bool ODD>
+static const void* group_kernel(int kind) {
+    switch (kind) {
+        case G_PAIR_PRE: return reinterpret_cast<const void*>(k_pair_group<kPre, true, false, ODD>);
+        case G_PAIR_POST0: return reinterpret_cast<const void*>(k_pair_group<kPost, true, false, ODD>);
+        case G_PAIR_ADD0: return reinterpret_cast<const void*>(k_pair_group<kPost, true, true, ODD>);
+        case G_PAIR_ADD: return reinterpret_cast<const void*>(k_pair_group<kPost, false, true, ODD>);
+        case G_PAIR_CYCLE0: return reinterpret_cast<const void*>(k_pair_group<kCycle, true, false, ODD>);
+        default: return reinterpret_cast<const void*>(k_pair_group<kCycle, false, false, ODD>);
+    }
+}
+
 // Level `level` of every problem whose level the pair march takes, for inner
 // cycle k of the FP32 correction solve: on the way down the pre-smoothing and
 // restriction (the finest level's only in cycle 0: later ones were done by
@@ -853,12 +957,10 @@ GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, 
     GStage none;
     none.kind = kind;
     if (in.empty()) return none;
-    const void* fn = down ? reinterpret_cast<const void*>(k_pair_group<kPre, true>)
-                     : kind == G_PAIR_POST0 ? reinterpret_cast<const void*>(k_pair_group<kPost, true>)
-                     : kind == G_PAIR_ADD0  ? reinterpret_cast<const void*>(k_pair_group<kPost, true, true>)
-                     : kind == G_PAIR_ADD   ? reinterpret_cast<const void*>(k_pair_group<kPost, false, true>)
-                     : kind == G_PAIR_CYCLE0 ? reinterpret_cast<const void*>(k_pair_group<kCycle, true>)
-                                             : reinterpret_cast<const void*>(k_pair_group<kCycle, false>);
+    // one launch for all: where one plane is odd, the form that can do both
+    bool odd = false;
+    for (const SolveCtx* c : in) odd = odd || pair_odd(c->P, l);
+    const void* fn = odd ? group_kernel<true>(kind) : group_kernel<false>(kind);
     auto set = [&](const SolveCtx* c, size_t t) -> const PairSet& {
         const std::vector<PairSet>& v = c->P->pair_sets[l];
         return v[std::min(t, v.size() - 1)];
@@ -896,6 +998,7 @@ GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, 
     }
     GStage st = group_build(gb, kind, jobs, gx, gy);
     st.lds = lds;
+    st.odd = odd;
     return st;
 }
 
@@ -903,16 +1006,10 @@ void group_launch_pair(const GStage& st, const unsigned char* dev, hipStream_t s
     if (st.wgs <= 0) return;
     const GEnt* e = reinterpret_cast<const GEnt*>(dev + st.ent_off);
     const PArgs<float>* j = reinterpret_cast<const PArgs<float>*>(dev + st.job_off);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(st.wgs), dim3(256), st.lds, s, e, st.nent, j); };
-    switch (st.kind) {
-        case G_PAIR_PRE: go(k_pair_group<kPre, true>); break;
-        case G_PAIR_POST0: go(k_pair_group<kPost, true>); break;
-        case G_PAIR_ADD0: go(k_pair_group<kPost, true, true>); break;
-        case G_PAIR_ADD: go(k_pair_group<kPost, false, true>); break;
-        case G_PAIR_CYCLE0: go(k_pair_group<kCycle, true>); break;
-        case G_PAIR_CYCLE: go(k_pair_group<kCycle, false>); break;
-        default: break;
-    }
+    const void* fn = st.odd ? group_kernel<true>(st.kind) : group_kernel<false>(st.kind);
+    int n = st.nent;
+    void* args[] = {&e, &n, &j};
+    (void)hipLaunchKernel(fn, dim3(st.wgs), dim3(256), args, st.lds, s);
 }
 
 }  // namespace mbp
