@@ -61,15 +61,13 @@ def _workload(name: str):
 # ---------------------------------------------------------------------------
 
 def _bytes_per_cell(precision: str) -> float:
-    """Method bytes of one finest-level fused launch per plane cell and mode.
-
-    Each launch does one red-black smoothing sweep (read p and f, write p:
-    3 words) plus either the residual with its restriction (read p and f,
-    write a quarter-size coarse rhs: 2.25 words) or the prolongation with its
-    correction (2.25 words), so 5.25 words per cell.
+    """Bytes that one finest-level launch of the pair march has to move per plane
+    cell and mode: it reads p, f and the quarter-size coarse correction and writes p
+    and the quarter-size coarse rhs, 3.5 words (the first launch of a solve reads
+    no p; the last FP32 one writes no coarse rhs and adds to the FP64 iterate).
     """
     w = 8.0 if precision == "fp64" else 4.0
-    return 5.25 * w
+    return 3.5 * w
 
 
 def _vcycle_bytes_per_point(w: float, nu1: int = 1, nu2: int = 1) -> float:
@@ -107,7 +105,7 @@ _PROFILE_NAMES = {"lshape3x256^2x512_stretch1.5": "lshape_256x3x512", "box512x51
 
 def _kernel_source_hash() -> str:
     import hashlib
-    path = os.path.join(HERE, "paper_2106_03583_amd", "csrc", "march.hip")
+    path = os.path.join(HERE, "paper_2106_03583_amd", "csrc", "pair.hip")
     return hashlib.sha256(open(path, "rb").read()).hexdigest()
 
 
@@ -238,10 +236,11 @@ def _roofline(prob, precision, prof, lockstep):
         traffic = tr.get("bytes_per_launch")
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-            "kernel": ["k_tile (pre-smoothing sweep + residual + restriction, finest level)",
-                       "k_tile_corr (correction + post-smoothing sweep + residual norm, finest level)"][cls],
+            "kernel": ["k_pair PRE (first pre-smoothing sweep + residual + restriction, finest level)",
+                       "k_pair CYCLE (correction + post-smoothing + residual norm + next pre-smoothing + "
+                       "restriction, finest level)"][cls],
             "avg_launch_ms": round(avg_ms, 4), "launches": launches, "bytes_per_launch": bpc * cells,
-            "bytes_model": "42 B per plane cell and mode (FP64): sweep 3 words + transfer 2.25 words"}
+            "bytes_model": "28 B per plane cell and mode (FP64): p, f, correction / 4 in; p, coarse rhs / 4 out"}
     if traffic:
         roof["traffic_GBs"] = round(traffic / (avg_ms * 1e-3) / 1e9, 1)
         roof["traffic_frac"] = round(roof["traffic_GBs"] / HBM_PEAK_GBS, 4)
