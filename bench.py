@@ -70,9 +70,12 @@ def _bytes_per_cell(precision: str) -> float:
     return 3.5 * w
 
 
-def _vcycle_bytes_per_point(w: float, nu1: int = 1, nu2: int = 1) -> float:
-    """Method bytes of one V-cycle per fine point: (sweeps*3 + 4.5) words x 4/3."""
-    return ((nu1 + nu2) * 3.0 + 4.5) * w * 4.0 / 3.0
+def _vcycle_bytes_per_point(w: float) -> float:
+    """Bytes one V-cycle has to move per fine point: 3.5 words a cell on every
+    level (finest: p, f, correction / 4 in, p, coarse rhs / 4 out in one launch;
+    coarse ones: f in, rhs / 4 out on the way down, f and correction / 4 in, p out
+    on the way up, 3.5 words too), x 4/3."""
+    return 3.5 * w * 4.0 / 3.0
 
 
 MIXED_INNER = 4  # FP32 V-cycles per refinement step (the library's default)
@@ -82,10 +85,11 @@ SERVE_INNER = 2  # the same inside a server (its default)
 def _mode_cycle_bytes(precision: str, inner: int = MIXED_INNER) -> float:
     """Method bytes per plane point and convergence step of one mode.
     FP64: one V-cycle.  Mixed: FP64 residual to FP32 (read p, f; write r:
-    20 B), `inner` FP32 V-cycles, FP64 accumulation (read e, p; write p: 20 B)."""
+    20 B), `inner` FP32 V-cycles, the last of which adds to p (read and write p
+    instead of writing e: 12 B more)."""
     if precision == "fp64":
         return _vcycle_bytes_per_point(8.0)
-    return 20.0 + inner * _vcycle_bytes_per_point(4.0) + 20.0
+    return 20.0 + inner * _vcycle_bytes_per_point(4.0) + 12.0
 
 
 TRANSFORM_BYTES = 32.0  # forward + inverse z transform, FP64 read + write
