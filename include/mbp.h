@@ -117,9 +117,11 @@ typedef struct {
  *   inner      MBP_MIXED: FP32 V-cycles per FP64 refinement step
  *              (residual in FP64, correction solved in FP32, added in
  *              FP64); 0 = default                [4; 2 in a server]
- *   march      pre-smoothing form of the fused levels: 0 LDS strip
- *              tiles, 1 register march (mbp_plan_autotune may change
- *              it per level)                                     [0]
+ *   march      pre-smoothing form of the levels that run the strip
+ *              kernels (odd sides at joined faces or rings, other
+ *              sweep counts than one and one): 0 LDS strip tiles, 1
+ *              register march (mbp_plan_autotune may change it per
+ *              level); the pair march of the others has one form  [0]
  *   smoother   MBP_SMOOTHER_DEFAULT | _RBGS (FFT path) | _JACOBI (mbp3_*)
  *                                                                [DEFAULT]
  *   helmholtz  alpha >= 0: solve (L_h - alpha) p = f, the Helmholtz
@@ -251,8 +253,8 @@ int mbp_solve(mbp_plan* plan, const double* rhs_dev, double* p_dev, double rtol,
  * Returns MBP_OK if every item converged, else the first failing item's
  * status; infos (optional, count entries) hold the per-item reports.
  * Grouped form: when every unfinished item is a mixed-precision plan whose
- * levels above the LDS-resident ones all run the strip kernels (one pre- and
- * one post-smoothing sweep) with the same inner cycle count, each stage of
+ * levels above the LDS-resident ones all run the pair march or the strip
+ * kernels (one pre- and one post-smoothing sweep) with the same inner cycle count, each stage of
  * the refinement step is one launch across all items (the stream count is
  * then unused). */
 int mbp_solve_batch(mbp_plan* const* plans, const double* const* rhs_dev, double* const* p_dev,
@@ -367,7 +369,8 @@ int mbp_profile_read(mbp_plan* plan, mbp_profile_info* out);
  * number of workgroups a strip-form launch aims at (which sets how many
  * modes one workgroup runs in turn) and, per fused multigrid level, the
  * pre-smoothing form (LDS strip tiles of 26 x 58 cells, or a register
- * march down strips of 128 x 58 cells).  All candidates run the same
+ * march down strips of 128 x 58 cells); levels of the pair march have one
+ * form.  All candidates run the same
  * red-black sweeps.  Blocking; the plan must be idle.  out (optional):
  *   wg_target  chosen workgroups per launch
  *   levels     multigrid levels reported in form[] (at most 16)
