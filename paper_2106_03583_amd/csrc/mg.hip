@@ -689,15 +689,17 @@ k_zero_active(T* __restrict__ p, long long plane, const int* __restrict__ act, c
         pq[i] = T(0);
 }
 
-// Planes of the modes that took an odd number of V-cycles: from pB to p.
+// Planes of the modes that took an odd number of V-cycles: from pB to p.  In pairs
+// where the plane has an even number of cells (every plane then begins on 16 bytes).
+template <typename V>
 __global__ void __launch_bounds__(256)
 k_take_odd(double* __restrict__ p, const double* __restrict__ pB, long long plane, const int* __restrict__ cyc) {
     const int q = blockIdx.y;
     if (!(cyc[q] & 1)) return;
-    const double2* s = reinterpret_cast<const double2*>(pB + q * plane);  // even planes only (pair march)
-    double2* d = reinterpret_cast<double2*>(p + q * plane);
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < plane / 2;
-         i += (long long)gridDim.x * blockDim.x)
+    const V* s = reinterpret_cast<const V*>(pB + q * plane);
+    V* d = reinterpret_cast<V*>(p + q * plane);
+    const long long n = plane / (long long)(sizeof(V) / sizeof(double));
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
         d[i] = s[i];
 }
 
@@ -1421,7 +1423,8 @@ void launch_zero_unrelaxed(const mbp_plan* P, double* p, hipStream_t s) {
 
 void launch_take_odd(const mbp_plan* P, double* p, const double* pB, hipStream_t s) {
     const int chunks = int(std::min<long long>(64, (P->plane0 + 2047) / 2048));
-    hipLaunchKernelGGL(k_take_odd, dim3(chunks, P->g.nz), dim3(256), 0, s, p, pB, (long long)P->plane0, P->d_cyc);
+    const auto fn = (P->plane0 & 1) ? k_take_odd<double> : k_take_odd<double2>;
+    hipLaunchKernelGGL(fn, dim3(chunks, P->g.nz), dim3(256), 0, s, p, pB, (long long)P->plane0, P->d_cyc);
 }
 
 // The first V-cycle from a zero iterate reads no finest-level p: its first
