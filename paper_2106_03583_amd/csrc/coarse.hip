@@ -53,7 +53,6 @@ struct CRec {
 };
 static_assert(sizeof(CRec) == 32, "eight words a record");
 
-constexpr int kThreads = 512;  // most threads of a workgroup: 256 registers each hold a level's cells without spills
 constexpr int kTab = 6;  // x / y table entry: lower and upper coupling, diagonal, restriction weight, lower prolongation weight
 
 // One level as the kernel reads it (in the int pool).
@@ -724,12 +723,12 @@ __device__ __forceinline__ void coarse_body(const CArgs<T>& a, int first, int st
 }  // namespace
 
 template <typename T, int NC, int KEEP, bool ODD, bool FULL>
-__global__ void __launch_bounds__(kThreads) k_coarse(const CArgs<T> a) {
+__global__ void __launch_bounds__(kCoarseThreads) k_coarse(const CArgs<T> a) {
     coarse_body<T, NC, KEEP, ODD, FULL>(a, blockIdx.x, gridDim.x);
 }
 
 template <int NC, int KEEP, bool ODD>
-__global__ void __launch_bounds__(kThreads) k_coarse_group(const GEnt* __restrict__ e, int n,
+__global__ void __launch_bounds__(kCoarseThreads) k_coarse_group(const GEnt* __restrict__ e, int n,
                                                        const CArgs<float>* __restrict__ jobs) {
     int bx, by;
     const int j = group_locate(e, n, bx, by);
@@ -765,12 +764,12 @@ unsigned short coarse_ref(const mbp_plan* P, const Level& C, int b, int I, int J
 
 }  // namespace
 
-// Records and tables of levels L .. of the plan, appended to the pools.  L must
-// pass coarse_levels_ok.
+// Records and tables of levels L .. of the plan, appended to the pools; nothing
+// where the levels do not fit the form.
 void coarse_build(mbp_plan* P, int L, int64_t elem) {
     CoarseInfo& ci = P->coarse;
     ci = CoarseInfo{};
-    if (!coarse_levels_ok(P, L)) return;
+    if (!coarse_fits(P, L, elem)) return;
     const Geometry& g = P->g;
     const int nl = P->nlev - L, nb = g.nb;
     std::vector<CLev> lev(nl);
@@ -902,10 +901,10 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
             if (k + 1 < nl)
                 for (unsigned short& o : r.c) o = (unsigned short)((o & 0x8000) | place[k + 1][o & 0x7fff]);
         }
-    // threads: two cells of each colour each, or as many as kThreads threads need
+    // threads: two cells of each colour each, or as many as kCoarseThreads threads need
     const int n = std::max(lev[0].n0, lev[0].n1);
     ci.ncell = n;
-    ci.nthr = int(std::min<int64_t>(kThreads, std::max<int64_t>(64, ((n + 1) / 2 + 63) / 64 * 64)));
+    ci.nthr = coarse_threads(n);
     ci.per = n <= 2 * ci.nthr ? 2 : 4;
     for (const CLev& c : lev) ci.odd |= c.odd;
     ci.oS = elems;
@@ -924,7 +923,7 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
     while (P->hint.size() & 3) P->hint.push_back(0);
     // records in LDS from the second level on where that costs no workgroup of
     // the CU (its 8 waves of this kernel), else from the third
-    const int64_t share = P->lds_limit / std::max(1, kThreads / ci.nthr);
+    const int64_t share = P->lds_limit / std::max(1, kCoarseThreads / ci.nthr);
     const int first_rec = coarse_lds_need(P, L, elem) + int64_t(lev[1].ncell) * 32 <= share ? 1 : 2;
     for (int k = 0; k < nl; ++k) {
         if (k == first_rec) ci.rec0 = int(P->hint.size());

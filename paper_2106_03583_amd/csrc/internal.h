@@ -313,7 +313,10 @@ void prof_begin(const mbp_plan* P, int cls, hipStream_t s, double cells);
 void prof_end(const mbp_plan* P, int cls, hipStream_t s);
 
 // coarse.hip (plan.cpp: the rule and the LDS size)
+constexpr int kCoarseThreads = 512;  // most threads of a workgroup: 256 registers each hold a level's cells without spills
+int coarse_threads(int cells);  // for that many cells of a colour on the top level
 bool coarse_levels_ok(const mbp_plan* P, int L);
+bool coarse_fits(const mbp_plan* P, int L, int64_t elem);  // and the LDS image fits
 int64_t coarse_lds_need(const mbp_plan* P, int L, int64_t elem);
 void coarse_build(mbp_plan* P, int L, int64_t elem);
 // ncyc V-cycles from zero on levels L .. of every active mode

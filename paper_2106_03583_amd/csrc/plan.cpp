@@ -330,9 +330,33 @@ void plan_set_shifts(mbp_plan* P) {
     P->g.singular = !g.dirichlet_xy && !zd && alpha == 0.0;
 }
 
+// Most cells of one of the two colours on level l (without those an odd ring puts in
+// colours of their own): joined blocks of odd counts can leave the colours uneven.
+static int widest_colour(const mbp_plan* P, int l) {
+    const Level& L = P->levels[l];
+    int64_t n[2] = {0, 0};
+    for (int b = 0; b < L.nb; ++b) {
+        const DBlock& d = P->hblk[L.blk_off + b];
+        const int kx = d.nbr[XP], ky = d.nbr[YP];
+        const bool ox = kx >= 0 && ((d.par + d.nx + P->hblk[L.blk_off + kx].par) & 1);
+        const bool oy = ky >= 0 && ((d.par + d.ny + P->hblk[L.blk_off + ky].par) & 1);
+        const int64_t cells = int64_t(d.nx - (ox ? 1 : 0)) * (d.ny - (oy ? 1 : 0));
+        n[d.par] += (cells + 1) / 2;
+        n[d.par ^ 1] += cells / 2;
+    }
+    return int(std::max(n[0], n[1]));
+}
+
+int coarse_threads(int cells) {
+    return std::min(kCoarseThreads, std::max(64, ((cells + 1) / 2 + 63) / 64 * 64));
+}
+
 // The form of coarse.hip takes levels L .. when every step below L halves
 // every block both ways, with one sweep before and after the correction, and
-// level L has at most 4096 cells: its 512 threads hold four of each colour.
+// level L has at most 4096 cells: its 512 threads hold four of each colour, and on
+// each level below one of each.  Uneven colours can ask for more (a T of even blocks
+// with 4096 cells has 513 and 511 cells on its second level): refused.  Levels with odd
+// rings are looped over.
 // (A form with 1024 threads for up to 8192 cells spilled half of its state: 65 us
 // a V-cycle on 101 x 78 cells against 52 us in the generic kernel.)
 bool coarse_levels_ok(const mbp_plan* P, int L) {
@@ -341,7 +365,16 @@ bool coarse_levels_ok(const mbp_plan* P, int L) {
         if (!P->levels[l].cx || !P->levels[l].cy) return false;
     int64_t e = 0;
     for (int b = 0; b < P->g.nb; ++b) e += P->levels[L].nx[b] + P->levels[L].ny[b];
-    return e < 60000;
+    if (e >= 60000) return false;
+    const int top = widest_colour(P, L), nthr = coarse_threads(top);
+    if (!P->levels[L].odd && top > 4 * nthr) return false;
+    for (int l = L + 1; l + 1 < P->nlev; ++l)
+        if (!P->levels[l].odd && widest_colour(P, l) > nthr) return false;
+    return true;
+}
+
+bool coarse_fits(const mbp_plan* P, int L, int64_t elem) {
+    return coarse_levels_ok(P, L) && coarse_lds_need(P, L, elem) <= P->lds_limit;
 }
 
 int64_t coarse_lds_need(const mbp_plan* P, int L, int64_t elem) {
@@ -875,7 +908,7 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
         auto pick = [&](int generic, int64_t elem) {
             int best = generic;
             for (int l = P->nlev - 2; l >= 0; --l)
-                if (l < best && coarse_levels_ok(P, l) && coarse_lds_need(P, l, elem) <= budget) best = l;
+                if (l < best && coarse_fits(P, l, elem)) best = l;
             return best;
         };
         P->lds_level = pick(P->lds_level, 8);
@@ -896,7 +929,7 @@ int build_plan_host_limits(const mbp_block_desc* blocks, int nblocks, const mbp_
                 P->lds_bytes64 -= fbytes;
             }
         }
-        if (P->lds_bytes64 > budget && !coarse_levels_ok(P, P->lds_level)) {
+        if (P->lds_bytes64 > budget && !coarse_fits(P, P->lds_level, 8)) {
             if (err) *err = "coarsest plane does not fit the LDS budget";
             return MBP_ERR_INVALID;
         }
