@@ -238,32 +238,32 @@ int mbp_plan_layout(const mbp_plan* plan, int64_t* block_offsets, size_t* worksp
 int mbp_solve(mbp_plan* plan, const double* rhs_dev, double* p_dev, double rtol, int flags,
               void* stream, mbp_solve_info* info);
 
-/* Many independent solves in one call (Algorithm 1 for each).  After the
- * forward transforms and one eager cycle, the cycles of every unfinished
- * problem are captured into one HIP graph (one branch per internal stream)
- * and replayed, a few cycles per replay; inside a replay the device tests
- * every mode and retires converged ones, so finished problems cost only
- * empty launches until the host, reading the active counts after each
- * replay, captures a smaller graph.  Plans may differ in size, conditions
- * and precision and must be distinct; each must be idle.  Every item runs
- * with per-mode retirement.  The stream count and cycles per replay come
- * from a cache keyed by the plan set, filled when a call passes
- * MBP_AUTOTUNE (default 4 streams, 4 cycles).  Stream-ordered on `stream`
- * at entry and exit; the call returns after the results are read back.
- * Returns MBP_OK if every item converged, else the first failing item's
- * status; infos (optional, count entries) hold the per-item reports.
- * Grouped form: when every unfinished item is a mixed-precision plan whose
- * levels above the LDS-resident ones all run the pair march or the strip
- * kernels (one pre- and one post-smoothing sweep) with the same inner cycle count, each stage of
- * the refinement step is one launch across all items (the stream count is
- * then unused). */
+/* Many independent solves in one call (Algorithm 1 for each).  Plans may differ
+ * in size, conditions and precision and must be distinct; each must be idle.
+ * Every item runs with per-mode retirement.
+ * Grouped form: of the mixed-precision plans whose levels above the
+ * LDS-resident ones all run the pair march or the strip kernels (one pre- and
+ * one post-smoothing sweep; the inner cycle count of the first of them), each
+ * stage of the refinement step is one launch for all.  A few cycles are captured
+ * into one HIP graph and replayed; inside a replay the device tests every mode
+ * and retires converged ones, so finished problems cost only empty workgroups
+ * until the host, reading the active counts after each replay, captures a
+ * smaller graph.
+ * Per-problem form: the other items are dealt to a few internal streams, and
+ * the host queues a cycle and a test of each ahead of the states it reads.
+ * The stream count and cycles per replay come from a cache keyed by the plan
+ * set, filled when a call passes MBP_AUTOTUNE (default 4 streams, 4 cycles).
+ * Stream-ordered on `stream` at entry and exit; the call returns after the
+ * results are read back.  Returns MBP_OK if every item converged, else the
+ * first failing item's status; infos (optional, count entries) hold the
+ * per-item reports. */
 int mbp_solve_batch(mbp_plan* const* plans, const double* const* rhs_dev, double* const* p_dev,
                     int count, double rtol, int flags, void* stream, mbp_solve_info* infos);
 
 /* Schedule the batch autotuner chose for this plan set (the batched form is
  * this library's; the paper solves one problem at a time): MBP_OK with the
  * stream count and cycles per replay, or MBP_PENDING if none is cached.
- * streams is 0 when every replay of the last batch of this plan set ran in
+ * streams is 0 when every cycle of the last batch of this plan set ran in
  * the grouped form. */
 int mbp_batch_schedule(mbp_plan* const* plans, int count, int* streams, int* cycles_per_replay);
 

@@ -1,14 +1,24 @@
 // Batched solves: many independent problems (each with all of its modes)
-// driven together.  After the prologue (and, unless the grouped form runs,
-// one eager cycle), the cycles of every unfinished problem are captured into
-// one HIP graph and replayed chunk by chunk: inside a replay the device runs
-// the convergence test and retires converged modes (and so finished
-// problems, whose kernels then exit at once); the host reads the active
-// counts after each replay and re-captures when the set has shrunk enough to
-// pay off.  Two graph shapes: the grouped form (mixed precision, strip
-// levels only) launches each stage of the refinement step once for all
-// problems; otherwise each problem's kernels form one branch per stream.
-// The number of streams and the cycles per replay come from a small online
+// driven together, in two forms side by side.
+//
+// Grouped (mixed-precision problems on the pair march or the strip kernels): each
+// stage of the refinement step is one launch for all of them.  A few steps are
+// captured into one HIP graph and replayed; inside a replay the device runs the
+// convergence test and retires converged modes (and so finished problems, whose
+// workgroups then exit at once); the host reads the active counts after each replay
+// and re-captures when the set has shrunk enough to pay off.
+//
+// Per problem (all others, FP64 among them): problems are dealt to a few streams
+// and the host queues a V-cycle and a test of every unfinished one before it looks
+// at the states of the tests before, as for a single solve, so the streams do not
+// wait for the host.  Nothing is captured: replayed graphs of one branch per stream
+// (13 FP64 boxes) ended a process once with a corrupted heap, cause unknown; that
+// form made its kernels' first occupancy queries inside a capture, and destroyed
+// graphs the moment their last replay had ended.  24 FP64 boxes of 64 to 384 cells:
+// 44.0 ms a batch in branches over strip kernels, 26.8 here; 32 of 32 to 96 cells
+// 14.0 and 6.2.
+//
+// The number of streams and the steps per replay come from a small online
 // autotuner, cached per batch signature; streams and events are pooled.
 #include <algorithm>
 #include <chrono>
@@ -25,9 +35,9 @@ namespace mbp {
 namespace {
 
 struct BatchTune {
-    int streams = 4;
-    int chunk = 4;
-    bool grouped = false;  // every replay of the set's last batch ran in the grouped form
+    int streams = 4;       // per-problem form
+    int chunk = 4;         // grouped form: cycles a replay
+    bool grouped = false;  // every problem of the set's last batch ran in the grouped form
 };
 
 std::mutex g_tune_mu;
@@ -70,6 +80,7 @@ struct Graph {
 struct StreamSet {
     int dev = -1;
     hipStream_t st[kMaxStreams] = {};
+    hipStream_t cap = nullptr;  // captures graphs, runs nothing
     hipEvent_t ev_join[kMaxStreams] = {};
     hipEvent_t ev_fork = nullptr, t0 = nullptr, t1 = nullptr;
 };
@@ -95,6 +106,7 @@ StreamSet* acquire_streams() {
         ok = ok && hipStreamCreateWithFlags(&p->st[k], hipStreamNonBlocking) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&p->ev_join[k], hipEventDisableTiming) == hipSuccess;
     }
+    ok = ok && hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreate(&p->t0) == hipSuccess && hipEventCreate(&p->t1) == hipSuccess;
     if (!ok) {
@@ -102,6 +114,7 @@ StreamSet* acquire_streams() {
             if (p->st[k]) (void)hipStreamDestroy(p->st[k]);
             if (p->ev_join[k]) (void)hipEventDestroy(p->ev_join[k]);
         }
+        if (p->cap) (void)hipStreamDestroy(p->cap);
         if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
         if (p->t0) (void)hipEventDestroy(p->t0);
         if (p->t1) (void)hipEventDestroy(p->t1);
@@ -135,11 +148,8 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
             have = true;
         }
     }
-    std::vector<BatchTune> trials;
-    if ((flags & MBP_AUTOTUNE) && !have)
-        trials = {{4, 4}, {1, 4}, {8, 4}, {2, 4}, {4, 2}, {4, 8}};
 
-    // streams: [0] is the capture origin; all of them are forked from s
+    // all of the streams are forked from s
     StreamSet* ss = acquire_streams();
     if (!ss) return MBP_ERR_HIP;
     hipStream_t* st = ss->st;
@@ -163,24 +173,17 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
     };
 
     // prologue of every problem, then the checks that need the host
-    int S = std::min(std::max(1, tune.streams), std::min(count, kMaxStreams));
+    const int S = std::min(std::max(1, tune.streams), std::min(count, kMaxStreams));
     fork(s, S);
     for (int i = 0; i < count; ++i) ctx_prologue(cx[i], st[i % S]);
     join(s, S);
     if (hipStreamSynchronize(s) != hipSuccess) fail(MBP_ERR_HIP);
     for (int i = 0; i < count && status == MBP_OK; ++i) ctx_check(cx[i]);
 
-    // problems whose whole hierarchy fits in LDS: one launch each; the
-    // others run their first cycle (from zero) eagerly, unless they all take
-    // the grouped form, whose captured cycles do not depend on the iterate
-    bool all_grouped = true;
-    int inner0 = -1;
-    for (int i = 0; i < count; ++i) {
-        const SolveCtx& c = cx[i];
-        if (c.done || c.full_lds) continue;
-        if (inner0 < 0) inner0 = c.P->opt.inner;
-        all_grouped = all_grouped && group_ok(c) && c.P->opt.inner == inner0;
-    }
+    // problems whose whole hierarchy fits in LDS: one launch each; the others join
+    // the group or run on their own
+    std::vector<int> group, single;
+    int inner = -1;  // of the group
     if (status == MBP_OK) {
         fork(s, S);
         for (int i = 0; i < count; ++i) {
@@ -193,119 +196,153 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                 c.done = true;
                 continue;
             }
-            if (all_grouped) continue;
-            ctx_test(c, st[i % S]);
-            ctx_vcycle(c, st[i % S]);
+            const bool in = group_ok(c) && (inner < 0 || c.P->opt.inner == inner);
+            if (in) inner = c.P->opt.inner;
+            (in ? group : single).push_back(i);
         }
         join(s, S);
     }
-
-    // captured cycles, replayed until every problem is done
-    Graph G;
-    int captures = 0, grouped_captures = 0;
-    void* table = nullptr;  // stage tables of the grouped form
-    size_t table_bytes = 0;
-    size_t trial = 0;
-    BatchTune cur = trials.empty() ? tune : trials[0];
-    double best_cost = 1e300;
-    BatchTune best = cur;
-    while (status == MBP_OK) {
-        std::vector<int> act;
-        long long modes = 0;
-        for (int i = 0; i < count; ++i)
-            if (!cx[i].done) {
-                act.push_back(i);
-                modes += cx[i].nitems;
+    const bool all_grouped = !group.empty() && single.empty();
+    const bool retuning = (flags & MBP_AUTOTUNE) && !have;
+    auto drop_done = [&](std::vector<int>& v) {
+        v.erase(std::remove_if(v.begin(), v.end(), [&](int i) { return cx[i].done; }), v.end());
+    };
+    // candidates of one form: cost per active mode-cell and cycle between t0 and t1
+    struct Trials {
+        std::vector<int> value;
+        size_t at = 0;
+        double best_cost = 1e300;
+        int best = 0;
+        bool open() const { return at < value.size(); }
+        void note(double cost) {
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = value[at];
             }
-        if (act.empty()) break;
-        const bool retune = trial < trials.size();
-        if (retune) cur = trials[trial];
-        const int Sc = std::min(std::max(1, cur.streams), std::min(int(act.size()), kMaxStreams));
-        bool recapture = G.e == nullptr || retune || act.size() < G.members.size() ||
-                         modes * 4 < G.modes * 3;
-        if (recapture) {
-            G.reset();
-            // grouped form: every unfinished problem is a mixed strip V-cycle
-            // with the same inner cycle count
-            bool grouped = true;
-            for (int i : act)
-                grouped = grouped && group_ok(cx[i]) && cx[i].P->opt.inner == cx[act[0]].P->opt.inner;
+            ++at;
+        }
+    };
+    auto cost_of = [&](const std::vector<int>& v, int cycles) {
+        float ms = 0.0f;
+        (void)hipEventElapsedTime(&ms, t0, t1);
+        double work = 0.0;
+        for (int i : v) work += double(cx[i].nitems) * double(cx[i].P->plane0);
+        return ms / std::max(1.0, work * cycles);
+    };
+
+    // ---- per-problem form ----
+    struct Test {
+        unsigned seq = 0;
+        int slot = 0;
+        bool open = false;  // its state has not been looked at
+    };
+    std::vector<Test> test(count);
+    std::vector<int> on(count);  // stream of each problem
+    int dealt = 0;
+    auto deal = [&](int streams) {
+        dealt = std::min(std::max(1, streams), std::min(int(single.size()), kMaxStreams));
+        for (size_t a = 0; a < single.size(); ++a) on[single[a]] = int(a) % dealt;
+        fork(s, dealt);
+    };
+    auto queue_cycle = [&](int i) {  // V-cycle and test; the test before it
+        const Test t = test[i];
+        ctx_vcycle(cx[i], st[on[i]]);
+        const int slot = (t.slot + 1) % kStateSlots;
+        test[i] = Test{ctx_test(cx[i], st[on[i]], slot), slot, true};
+        return t;
+    };
+    std::vector<Test> before;
+    auto round = [&] {  // a cycle of every problem, then the states before it
+        before.clear();
+        for (int i : single) before.push_back(queue_cycle(i));
+        for (size_t a = 0; a < single.size(); ++a) {
+            SolveCtx& c = cx[single[a]];
+            if (!before[a].open) continue;
+            const int r = ctx_wait(c, st[on[single[a]]], before[a].slot, before[a].seq);
+            if (r != MBP_OK) fail(r);
+            else ctx_state_apply(c, before[a].slot);
+        }
+        drop_done(single);
+    };
+    if (status == MBP_OK && !single.empty()) {
+        deal(tune.streams);
+        for (int i : single) test[i] = Test{ctx_test(cx[i], st[on[i]], 0), 0, true};
+    }
+
+    // ---- grouped form, with rounds of the others beside each replay ----
+    Graph G, last;          // a graph replaced by a smaller one is destroyed a replay later
+    void* table = nullptr;  // stage tables
+    size_t table_bytes = 0;
+    Trials chunks;
+    if (retuning && !group.empty()) chunks.value = {4, 2, 8};
+    while (status == MBP_OK && !group.empty()) {
+        long long modes = 0;
+        for (int i : group) modes += cx[i].nitems;
+        const bool retune = chunks.open();
+        if (retune) tune.chunk = chunks.value[chunks.at];
+        if (G.e == nullptr || retune || group.size() < G.members.size() || modes * 4 < G.modes * 3) {
+            last.reset();
+            std::swap(last, G);
             std::vector<GStage> stages;
-            if (grouped) {
-                std::vector<SolveCtx*> cs;
-                int maxL = 0;
-                for (int i : act) {
-                    cs.push_back(&cx[i]);
-                    maxL = std::max(maxL, cx[i].P->lds_level32);
+            std::vector<SolveCtx*> cs;
+            int maxL = 0;
+            for (int i : group) {
+                cs.push_back(&cx[i]);
+                maxL = std::max(maxL, cx[i].P->lds_level32);
+            }
+            GroupBlob gb;
+            stages.push_back(group_res32(gb, cs));
+            stages.push_back(group_finish(gb, cs));
+            stages.push_back(group_update(gb, cs));
+            for (int k = 0; k < inner; ++k) {
+                // each level's problems: those of the pair march, then the strip kernels'
+                for (int l = 0; l < maxL; ++l) {
+                    stages.push_back(group_pair32(gb, cs, l, true, k, inner));
+                    stages.push_back(group_march32(gb, cs, l, false, k == 0));
                 }
-                GroupBlob gb;
-                stages.push_back(group_res32(gb, cs));
-                stages.push_back(group_finish(gb, cs));
-                stages.push_back(group_update(gb, cs));
-                const int inner = cx[act[0]].P->opt.inner;
-                for (int k = 0; k < inner; ++k) {
-                    // each level's problems: those of the pair march, then the strip kernels'
-                    for (int l = 0; l < maxL; ++l) {
-                        stages.push_back(group_pair32(gb, cs, l, true, k, inner));
-                        stages.push_back(group_march32(gb, cs, l, false, k == 0));
-                    }
-                    for (int form = 0; form < 3; ++form) stages.push_back(group_coarse32(gb, cs, form));
-                    stages.push_back(group_lds32(gb, cs));
-                    for (int l = maxL - 1; l >= 0; --l) {
-                        stages.push_back(group_pair32(gb, cs, l, false, k, inner));
-                        stages.push_back(group_march32(gb, cs, l, true, false));
-                    }
+                for (int form = 0; form < 3; ++form) stages.push_back(group_coarse32(gb, cs, form));
+                stages.push_back(group_lds32(gb, cs));
+                for (int l = maxL - 1; l >= 0; --l) {
+                    stages.push_back(group_pair32(gb, cs, l, false, k, inner));
+                    stages.push_back(group_march32(gb, cs, l, true, false));
                 }
-                stages.push_back(group_addcorr(gb, cs));
-                if (gb.host.size() > table_bytes) {
-                    if (table) (void)hipFree(table);
-                    table = nullptr;
-                    table_bytes = 0;
-                    if (hipMalloc(&table, gb.host.size()) != hipSuccess) {
-                        fail(MBP_ERR_NOMEM);
-                        break;
-                    }
-                    table_bytes = gb.host.size();
-                }
-                if (hipMemcpy(table, gb.host.data(), gb.host.size(), hipMemcpyHostToDevice) != hipSuccess) {
-                    fail(MBP_ERR_HIP);
+            }
+            stages.push_back(group_addcorr(gb, cs));
+            if (gb.host.size() > table_bytes) {
+                if (table) (void)hipFree(table);
+                table = nullptr;
+                table_bytes = 0;
+                if (hipMalloc(&table, gb.host.size()) != hipSuccess) {
+                    fail(MBP_ERR_NOMEM);
                     break;
                 }
+                table_bytes = gb.host.size();
             }
-            if (hipStreamBeginCapture(st[0], hipStreamCaptureModeThreadLocal) != hipSuccess) {
+            if (hipMemcpy(table, gb.host.data(), gb.host.size(), hipMemcpyHostToDevice) != hipSuccess) {
                 fail(MBP_ERR_HIP);
                 break;
             }
-            ++captures;
-            if (grouped) {
-                ++grouped_captures;
-                const unsigned char* dev = static_cast<const unsigned char*>(table);
-                for (int it = 0; it < cur.chunk; ++it)
-                    for (const GStage& g : stages) {
-                        if (g.kind == G_PRE32 || g.kind == G_POST32) group_launch_march(g, dev, st[0]);
-                        else if (g.kind >= G_PAIR_PRE) group_launch_pair(g, dev, st[0]);
-                        else if (g.kind >= G_COARSE0) group_launch_coarse(g, dev, st[0]);
-                        else group_launch_mg(g, dev, st[0]);
-                    }
-                for (int i : act) cx[i].cycles += cur.chunk;
-            } else {
-                fork(st[0], Sc);
-                for (int it = 0; it < cur.chunk; ++it)
-                    for (size_t a = 0; a < act.size(); ++a) {
-                        SolveCtx& c = cx[act[a]];
-                        ctx_test(c, st[a % Sc]);
-                        ctx_vcycle(c, st[a % Sc]);
-                    }
-                join(st[0], Sc);
+            // (every kernel's occupancy and LDS limit were settled with its stage)
+            if (hipStreamBeginCapture(ss->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+                fail(MBP_ERR_HIP);
+                break;
             }
-            if (hipStreamEndCapture(st[0], &G.g) != hipSuccess ||
+            const unsigned char* dev = static_cast<const unsigned char*>(table);
+            for (int it = 0; it < tune.chunk; ++it)
+                for (const GStage& g : stages) {
+                    if (g.kind == G_PRE32 || g.kind == G_POST32) group_launch_march(g, dev, ss->cap);
+                    else if (g.kind >= G_PAIR_PRE) group_launch_pair(g, dev, ss->cap);
+                    else if (g.kind >= G_COARSE0) group_launch_coarse(g, dev, ss->cap);
+                    else group_launch_mg(g, dev, ss->cap);
+                }
+            if (hipStreamEndCapture(ss->cap, &G.g) != hipSuccess ||
                 hipGraphInstantiate(&G.e, G.g, nullptr, nullptr, 0) != hipSuccess) {
                 (void)hipGetLastError();
                 G.reset();
                 fail(MBP_ERR_HIP);
                 break;
             }
-            G.members = act;
+            G.members = group;
             G.modes = modes;
         }
         (void)hipEventRecord(t0, s);
@@ -314,39 +351,54 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
             break;
         }
         (void)hipEventRecord(t1, s);
+        for (int k = 0; k < tune.chunk && !retuning && !single.empty() && status == MBP_OK; ++k) round();
         if (hipStreamSynchronize(s) != hipSuccess) {
             fail(MBP_ERR_HIP);
             break;
         }
         if (retune) {
-            // cost per active mode-cell and cycle of this replay
-            float ms = 0.0f;
-            (void)hipEventElapsedTime(&ms, t0, t1);
-            double work = 0.0;
-            for (int i : act) work += double(cx[i].nitems) * double(cx[i].P->plane0);
-            const double cost = ms / std::max(1.0, work * cur.chunk);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best = cur;
-            }
-            if (++trial == trials.size()) {
-                std::lock_guard<std::mutex> lk(g_tune_mu);
-                g_tune[sig] = best;
-                tune = best;
-                cur = best;
-                G.reset();
-            }
+            chunks.note(cost_of(group, tune.chunk));
+            if (!chunks.open()) tune.chunk = chunks.best;
         }
-        for (int i : act) ctx_state_apply(cx[i]);
+        for (int i : group) ctx_state_apply(cx[i]);
+        drop_done(group);
     }
-    G.reset();
-    if (table) (void)hipFree(table);
+    if (chunks.at > 0) tune.chunk = chunks.best;  // (the batch may have finished before every candidate ran)
+
+    // ---- what is left of the others ----
+    Trials streams;
+    if (retuning && !single.empty()) streams.value = {4, 1, 8, 2};
+    while (status == MBP_OK && !single.empty()) {
+        if (!streams.open()) {
+            round();
+            continue;
+        }
+        // one cycle of every problem alone on this candidate's streams
+        join(s, dealt);
+        (void)hipEventRecord(t0, s);
+        deal(streams.value[streams.at]);
+        for (int i : single) (void)queue_cycle(i);
+        join(s, dealt);
+        (void)hipEventRecord(t1, s);
+        if (hipStreamSynchronize(s) != hipSuccess) {
+            fail(MBP_ERR_HIP);
+            break;
+        }
+        streams.note(cost_of(single, 1));
+        for (int i : single) {
+            ctx_state_apply(cx[i], test[i].slot);
+            test[i].open = false;
+        }
+        drop_done(single);
+        if (!streams.open() && !single.empty()) deal(streams.best);
+    }
+    if (streams.at > 0) tune.streams = streams.best;
+    join(s, dealt);  // finished problems have a cycle and a test queued that do nothing
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        // the batch finished before every candidate ran: keep the best seen
-        if (trial > 0 && trial < trials.size()) g_tune[sig] = best;
+        if (chunks.at + streams.at > 0) g_tune[sig] = tune;
         auto it = g_tune.find(sig);
-        if (it != g_tune.end()) it->second.grouped = captures > 0 && grouped_captures == captures;
+        if (it != g_tune.end()) it->second.grouped = all_grouped;
     }
 
     // epilogue and results
@@ -358,6 +410,9 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
         if (r != MBP_OK) fail(r);
         else if (cx[i].status != MBP_OK) fail(cx[i].status);
     }
+    G.reset();
+    last.reset();
+    if (table) (void)hipFree(table);
     release_streams(ss);
     return status;
 }

@@ -411,7 +411,9 @@ void ctx_prologue(SolveCtx& c, hipStream_t s);  // ends by writing what ctx_chec
 void ctx_check(SolveCtx& c);                    // after the prologue synchronised
 unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot = 0);  // residual norms + convergence, state into the
                                                               // slot; its number
+constexpr int kStateSlots = 3;
 bool ctx_tested(const SolveCtx& c, int slot, unsigned seq);   // that state has arrived
+int ctx_wait(const SolveCtx& c, hipStream_t s, int slot, unsigned seq);  // until it has
 void ctx_vcycle(SolveCtx& c, hipStream_t s);    // one V-cycle of the active modes
 void ctx_state_apply(SolveCtx& c, int slot = 0);  // after the test synchronised
 void ctx_epilogue(SolveCtx& c, hipStream_t s);

@@ -313,7 +313,6 @@ namespace {
 // is a dispatch of its own between two kernels
 constexpr int kPinStart = 0;    // after the prologue: ints flag[0..3], area sum, mode 0's norm
 constexpr int kPinSlots = 64;   // state slots of the tests, a 64-bit word each (mg.hip: UpdJob)
-constexpr int kSlots = 3;
 constexpr int kPinReport = 128; // at the end: max ratio, then ints most cycles, cycles per mode
 static_assert(kPinReport * 8 + 8 + 4 * (1 + 4096) <= kPinBytes, "one int a mode");
 
@@ -403,7 +402,7 @@ bool ctx_tested(const SolveCtx& c, int slot, unsigned seq) { return unsigned(sta
 // Wait for the state of a test.  An event behind each test would do, but its
 // packet holds the queue for 6 us a cycle; the stream is only asked (for
 // errors) when nothing has come for some milliseconds.
-static int wait_test(const SolveCtx& c, hipStream_t s, int slot, unsigned seq) {
+int ctx_wait(const SolveCtx& c, hipStream_t s, int slot, unsigned seq) {
     auto t0 = std::chrono::steady_clock::now();
     for (unsigned i = 1; !ctx_tested(c, slot, seq); ++i) {
         if (i & 1023) continue;
@@ -537,12 +536,12 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
         unsigned seq = ctx_test(c, s, 0);
         for (int k = 0;; ++k) {
             ctx_vcycle(c, s);
-            const unsigned next = ctx_test(c, s, (k + 1) % kSlots);
-            st = wait_test(c, s, k % kSlots, seq);
+            const unsigned next = ctx_test(c, s, (k + 1) % kStateSlots);
+            st = ctx_wait(c, s, k % kStateSlots, seq);
             if (st != MBP_OK) break;
             seq = next;
             if (k == 0) ctx_check(c);
-            if (!c.done) ctx_state_apply(c, k % kSlots);
+            if (!c.done) ctx_state_apply(c, k % kStateSlots);
             if (c.done) break;
         }
     }
