@@ -299,8 +299,9 @@ template <typename T>
 int launch_vcycle(const mbp_plan* P, VcycleArgs<T>& v, hipStream_t s);
 // The test of a cycle from nparts partial sums a mode (dyn: their count on the device;
 // nparts 0: p is zero, the residual is the rhs itself), its state and seq into out.
+// release: what kernels before it wrote to host memory is there once out is.
 void launch_test(const mbp_plan* P, int nparts, const int* dyn, double rtol2, double etol2, int retire, int nitems,
-                 hipStream_t s, unsigned long long* out, unsigned seq);
+                 hipStream_t s, unsigned long long* out, unsigned seq, bool release);
 // Copy the planes of the modes that took an odd number of V-cycles from pB to p.
 void launch_take_odd(const mbp_plan* P, double* p, const double* pB, hipStream_t s);
 // Whole solve of every mode for plans whose hierarchy fits in LDS.
@@ -408,9 +409,9 @@ struct SolveCtx {
 };
 void ctx_init(SolveCtx& c, mbp_plan* P, const double* rhs, double* p, double rtol, int flags);
 void ctx_prologue(SolveCtx& c, hipStream_t s);  // ends by writing what ctx_check reads to host memory
-void ctx_check(SolveCtx& c);                    // after the prologue synchronised
-unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot = 0);  // residual norms + convergence, state into the
-                                                              // slot; its number
+void ctx_check(SolveCtx& c);  // after the stream synchronised, or a test with checks arrived
+// residual norms + convergence, state into the slot; its number
+unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot = 0, bool checks = false);
 constexpr int kStateSlots = 3;
 bool ctx_tested(const SolveCtx& c, int slot, unsigned seq);   // that state has arrived
 int ctx_wait(const SolveCtx& c, hipStream_t s, int slot, unsigned seq);  // until it has

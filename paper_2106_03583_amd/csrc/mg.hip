@@ -481,6 +481,7 @@ struct UpdJob {
     unsigned long long* out;  // optional (host-visible): seq << 32 | modes that have not passed << 8 |
                               // 1 where the cycles are used up
     unsigned seq;
+    int release;  // the host reads what earlier kernels wrote (k_iota) once it sees out
 };
 
 __device__ __forceinline__ void update_body(const UpdJob& J) {
@@ -554,10 +555,13 @@ __device__ __forceinline__ void update_body(const UpdJob& J) {
         }
         if (stop && !retire && c > 0) state[2] = 1;
         state[1] = cycle + 1;
-        // one store, so that no fence (3 us across PCIe) stands between state and number
-        if (J.out)
-            __hip_atomic_store(J.out, (unsigned long long)J.seq << 32 | (unsigned)c << 8 | (state[2] ? 1u : 0u),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        // one store, so that no fence (3 us across PCIe) stands between state and number;
+        // only the test that the host's checks of the rhs wait for releases what came before
+        if (J.out) {
+            const unsigned long long w = (unsigned long long)J.seq << 32 | (unsigned)c << 8 | (state[2] ? 1u : 0u);
+            if (J.release) __hip_atomic_store(J.out, w, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            else __hip_atomic_store(J.out, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
@@ -1383,9 +1387,10 @@ static FinJob fin_job(const mbp_plan* P, int nparts, const int* dyn) {
     return FinJob{nparts ? P->d_part : nullptr, nparts, P->d_act, P->d_nact, P->d_rnorm, P->d_pnorm, dyn, P->d_fnorm};
 }
 
-static UpdJob upd_job(const mbp_plan* P, double rtol2, double etol2, int retire, unsigned long long* out, unsigned seq) {
+static UpdJob upd_job(const mbp_plan* P, double rtol2, double etol2, int retire, unsigned long long* out, unsigned seq,
+                      bool release) {
     return UpdJob{P->g.nz, P->d_rnorm, P->d_fnorm, P->d_pnorm, P->d_sabs, rtol2, etol2, retire, P->opt.max_cycles,
-                  P->d_act, P->d_nact, P->d_cyc, P->d_scal, P->d_flag, out, seq};
+                  P->d_act, P->d_nact, P->d_cyc, P->d_scal, P->d_flag, out, seq, release ? 1 : 0};
 }
 
 // One launch up to this many partial pairs: 1,500 pairs take 8.0 us (two launches
@@ -1393,9 +1398,9 @@ static UpdJob upd_job(const mbp_plan* P, double rtol2, double etol2, int retire,
 constexpr long long kTestPairs = 4096;
 
 void launch_test(const mbp_plan* P, int nparts, const int* dyn, double rtol2, double etol2, int retire, int nitems,
-                 hipStream_t s, unsigned long long* out, unsigned seq) {
+                 hipStream_t s, unsigned long long* out, unsigned seq, bool release) {
     const FinJob F = fin_job(P, nparts, dyn);
-    const UpdJob U = upd_job(P, rtol2, etol2, retire, out, seq);
+    const UpdJob U = upd_job(P, rtol2, etol2, retire, out, seq, release);
     const long long pairs = (long long)nitems * std::max(1, dyn ? pair_max_strips(P, 0) : nparts);
     if (pairs <= kTestPairs) {
         hipLaunchKernelGGL(k_test, dim3(1), dim3(1024), 0, s, F, U);
@@ -1545,7 +1550,7 @@ GStage group_update(GroupBlob& gb, const std::vector<SolveCtx*>& cs) {
     std::vector<UpdJob> jobs;
     std::vector<int> gx, gy;
     for (const SolveCtx* c : cs) {
-        jobs.push_back(upd_job(c->P, c->rtol2, c->etol2, c->retire ? 1 : 0, pin_state(c->P, 0), 0));
+        jobs.push_back(upd_job(c->P, c->rtol2, c->etol2, c->retire ? 1 : 0, pin_state(c->P, 0), 0, false));
         gx.push_back(1);
         gy.push_back(1);
     }

@@ -230,7 +230,7 @@ struct mbp_server {
     void cycles(Request* r) {
         hipStream_t s = streams[r->slot];
         for (int k = 0; k < kCyclesPerStep; ++k) {
-            r->seq = ctx_test(r->ctx, s);
+            r->seq = ctx_test(r->ctx, s, 0, !r->checked && k + 1 == kCyclesPerStep);
             ctx_vcycle(r->ctx, s);
         }
         r->t_issue = Clock::now();
@@ -246,8 +246,8 @@ struct mbp_server {
                 ctx_init(c, r->cp->plan, r->rhs, r->p, r->rtol, r->flags | opt.flags | MBP_RETIRE);
                 ctx_prologue(c, s);
                 if (!c.full_lds) {  // its checks are read with the first state
-                    cycles(r);
                     r->checked = false;
+                    cycles(r);
                     return true;
                 }
                 (void)hipEventRecord(r->ev, s);

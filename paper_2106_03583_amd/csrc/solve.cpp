@@ -379,7 +379,7 @@ void ctx_check(SolveCtx& c) {
 
 // Convergence test of the current iterate (Sec. 3's per-mode systems each
 // stop on their own when retiring).
-unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot) {
+unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot, bool checks) {
     mbp_plan* P = c.P;
     const bool zero = c.cycles == 0 && !c.warm;  // p = 0: the residual is f itself
     if (c.mixed)
@@ -393,7 +393,7 @@ unsigned ctx_test(SolveCtx& c, hipStream_t s, int slot) {
     const bool fused = !c.mixed && c.fused_parts > 0;
     const int parts = !c.mixed && zero ? 0 : fused ? c.fused_parts : P->levels[0].ntiles;
     launch_test(P, parts, fused && c.flip ? P->d_flag + 3 : nullptr, c.rtol2, c.etol2, c.retire ? 1 : 0, c.nitems, s,
-                pin_state(P, slot), seq);
+                pin_state(P, slot), seq, checks);
     return seq;
 }
 
@@ -533,7 +533,7 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
         if (hipStreamSynchronize(s) != hipSuccess) st = MBP_ERR_HIP;
         else ctx_check(c);
     } else {
-        unsigned seq = ctx_test(c, s, 0);
+        unsigned seq = ctx_test(c, s, 0, true);
         for (int k = 0;; ++k) {
             ctx_vcycle(c, s);
             const unsigned next = ctx_test(c, s, (k + 1) % kStateSlots);
