@@ -496,7 +496,7 @@ __device__ __forceinline__ void update_body(const UpdJob& J) {
     int* __restrict__ cyc = J.cyc;
     double* __restrict__ scal = J.scal;
     int* __restrict__ state = J.state;
-    // state[0]: non-finite rhs, state[1]: cycle counter, state[2]: max cycles reached
+    // state[0]: rhs refused, state[1]: cycle counter, state[2]: max cycles reached
     __shared__ int keep[4096];
     __shared__ double mx[16];
     const int n = *nact;
@@ -619,20 +619,23 @@ __global__ void k_fill_int(int* p, int n, int v) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
 }
 
-// Start of a solve: every mode active, no cycle done.  out (optional, host-visible):
-// state[0..3] of the transforms, the singular plane's area sum, mode 0's norm.
-__global__ void k_iota(int* act, int n, int* nact, int* cyc, const int* state, const double* sum, const double* fnorm,
-                       double* out) {
+// Start of a solve: every mode active, no cycle done.  A rhs that is refused leaves
+// none: what is queued behind finds nothing to do.  state[0]: bit 0, a value that is not
+// finite (set by the transform); bit 1, here, where area is not zero and the singular
+// plane's mean (its area sum over area) is above the rounding level of its rms.
+// out (optional, host-visible): state[0..3], the area sum.
+__global__ void k_iota(int* act, int n, int* nact, int* cyc, int* state, const double* sum, const double* fnorm,
+                       double area, double cells, double* out) {
     for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < n; i += blockDim.x * gridDim.x) {
         act[i] = i;
         cyc[i] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *nact = n;
+        if (area != 0.0 && fabs(*sum / area) > 1e-12 * (sqrt(fnorm[0] / cells) + 1e-300)) state[0] |= 2;
+        *nact = state[0] ? 0 : n;
         if (out) {
             for (int i = 0; i < 4; ++i) reinterpret_cast<int*>(out)[i] = state[i];
             out[2] = *sum;
-            out[3] = fnorm[0];
         }
     }
 }
@@ -1410,9 +1413,9 @@ void launch_test(const mbp_plan* P, int nparts, const int* dyn, double rtol2, do
     hipLaunchKernelGGL(k_update, dim3(1), dim3(1024), 0, s, U);
 }
 
-void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out) {
+void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out, bool compatible) {
     hipLaunchKernelGGL(k_iota, dim3(1), dim3(1024), 0, s, P->d_act, P->g.nz, P->d_nact, P->d_cyc, P->d_flag,
-                       P->d_scal + 4, P->d_fnorm, out);
+                       P->d_scal + 4, P->d_fnorm, compatible ? P->area_sum : 0.0, double(P->plane0), out);
 }
 
 void launch_report(const mbp_plan* P, hipStream_t s, double* out) {

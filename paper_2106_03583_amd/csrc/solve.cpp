@@ -9,7 +9,7 @@
 
 namespace mbp {
 
-void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out);
+void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out, bool compatible);
 void launch_report(const mbp_plan* P, hipStream_t s, double* out);
 void launch_area_dot(const mbp_plan* P, const double* plane, double* out_sum, hipStream_t s);
 void launch_fill_int(int* p, int n, int v, hipStream_t s);
@@ -311,7 +311,7 @@ void plan_device_free(mbp_plan* P) {
 namespace {
 // layout (doubles) of the plan's pinned buffer, which kernels write directly: a copy
 // is a dispatch of its own between two kernels
-constexpr int kPinStart = 0;    // after the prologue: ints flag[0..3], area sum, mode 0's norm
+constexpr int kPinStart = 0;    // after the prologue: ints flag[0..3], area sum
 constexpr int kPinSlots = 64;   // state slots of the tests, a 64-bit word each (mg.hip: UpdJob)
 constexpr int kPinReport = 128; // at the end: max ratio, then ints most cycles, cycles per mode
 static_assert(kPinReport * 8 + 8 + 4 * (1 + 4096) <= kPinBytes, "one int a mode");
@@ -356,24 +356,18 @@ void ctx_prologue(SolveCtx& c, hipStream_t s) {
     launch_plane_norm(P, P->fhat, P->d_fnorm, s);
     if (c.warm) launch_forward(P, c.p, P->phat, nullptr, s);
     else if (!c.lazy_zero) launch_zero(P->phat, size_t(nz) * P->plane0, s);
-    launch_reset_active(P, s, pin_dev(P, kPinStart));
+    launch_reset_active(P, s, pin_dev(P, kPinStart), P->g.singular && !(c.flags & MBP_PROJECT_RHS));
 }
 
 void ctx_check(SolveCtx& c) {
-    mbp_plan* P = c.P;
-    const int nz = P->g.nz;
+    const mbp_plan* P = c.P;
     const double* start = pin_host(P, kPinStart);
-    if (reinterpret_cast<const int*>(start)[0]) c.status = MBP_ERR_NONFINITE;
-    if (c.status == MBP_OK && P->g.singular) {
-        const double mean_q0 = start[2] / P->area_sum;  // area-weighted mean of fhat_0
-        c.removed = mean_q0 / std::sqrt(double(nz));               // volume-weighted mean of f
-        if (!(c.flags & MBP_PROJECT_RHS)) {
-            // compatible if the mean is at rounding level of the plane's rms
-            const double rms = std::sqrt(start[3] / double(P->plane0));
-            if (std::fabs(mean_q0) > 1e-12 * (rms + 1e-300)) c.status = MBP_ERR_INCOMPATIBLE;
-            c.removed = 0.0;
-        }
-    }
+    const int refused = reinterpret_cast<const int*>(start)[0];
+    if (refused & 1) c.status = MBP_ERR_NONFINITE;
+    else if (refused) c.status = MBP_ERR_INCOMPATIBLE;
+    else if (P->g.singular && (c.flags & MBP_PROJECT_RHS))
+        // the area-weighted mean of fhat_0, as the volume-weighted mean of f
+        c.removed = start[2] / P->area_sum / std::sqrt(double(P->g.nz));
     if (c.status != MBP_OK) c.done = true;
 }
 
@@ -519,17 +513,12 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
     ctx_prologue(c, s);
     (void)hipEventRecord(ev[1], s);
     int st = MBP_OK;
-    bool finished = false;  // epilogue queued
     if (c.full_lds) {
+        // one wait for all: a refused rhs leaves no mode to solve, and p alone
         launch_lds_full(P, P->phat, P->fhat, P->d_act, P->d_nact, P->g.nz, P->opt.max_cycles, c.rtol2, c.etol2,
                         P->d_cyc, P->d_rnorm, P->d_fnorm, s);
-        if (!P->g.singular || (flags & MBP_PROJECT_RHS)) {
-            // only a value that is not finite can stop this solve, which the
-            // inverse transform can see for itself
-            (void)hipEventRecord(ev[2], s);
-            ctx_finish(c, s, P->d_flag);
-            finished = true;
-        }
+        (void)hipEventRecord(ev[2], s);
+        ctx_finish(c, s, P->d_flag);
         if (hipStreamSynchronize(s) != hipSuccess) st = MBP_ERR_HIP;
         else ctx_check(c);
     } else {
@@ -544,8 +533,6 @@ int solve_one(mbp_plan* P, const double* rhs, double* p, double rtol, int flags,
             if (!c.done) ctx_state_apply(c, k % kStateSlots);
             if (c.done) break;
         }
-    }
-    if (!finished) {
         (void)hipEventRecord(ev[2], s);
         if (st == MBP_OK) ctx_finish(c, s, nullptr);
     }

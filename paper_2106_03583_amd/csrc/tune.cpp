@@ -14,14 +14,14 @@
 
 namespace mbp {
 
-void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out);
+void launch_reset_active(const mbp_plan* P, hipStream_t s, double* out, bool compatible);
 
 namespace {
 
 // Mean time of `reps` V-cycles over all modes (after one untimed cycle).
 float time_cycles(SolveCtx& c, hipStream_t s, hipEvent_t a, hipEvent_t b, int reps) {
     mbp_plan* P = c.P;
-    launch_reset_active(P, s, nullptr);
+    launch_reset_active(P, s, nullptr, false);
     c.nitems = P->g.nz;
     ctx_vcycle(c, s);
     (void)hipEventRecord(a, s);
