@@ -212,7 +212,8 @@ struct mbp_plan {
     int* d_act = nullptr;         // active mode list (nz)
     int* d_nact = nullptr;        // 1 int
     int* d_cyc = nullptr;         // nz: cycles per mode
-    int* d_flag = nullptr;        // 4 ints: [0] non-finite rhs
+    int* d_flag = nullptr;        // 4 ints: [0] rhs refused (1 not finite, 2 incompatible), [1] tests,
+                                  // [2] cycles used up, [3] partial sums a mode
     double* d_scal = nullptr;     // 8 doubles of scratch scalars
     void* graph_exec = nullptr;   // cached batched replay (hipGraphExec_t)
     void* host_pinned = nullptr;  // pinned buffer that kernels report to

@@ -158,9 +158,12 @@ template <typename T, int FORM, bool ZIN, bool NRM, bool ADD = false, bool ODD =
 struct March {
     static constexpr bool C = FORM != kPre, R = FORM != kPost;
     // rows loaded ahead: at most the ring minus the rows the last stage still reads.  Six
-    // in the odd forms too: with eight, hipcc 7.2 gave a register of a row still to be
-    // relaxed to a diagonal in the FP32 PRE form (seen in its assembly), and two of
-    // eight restricted rows were wrong.
+    // in the odd forms too: with eight, hipcc 7.2 overwrites the black value of one row of
+    // the sixteen in the FP32 PRE form from zero before its only use (following every
+    // loaded register of that form through its assembly: row 5's upper half has no
+    // reader; with six, and in the even forms, every one has), and two of eight
+    // restricted rows were wrong.  tests/test_gpu_cycle_cells.py holds every form to a
+    // single cycle's values, cell by cell.
     static constexpr int kAhead = FORM == kCycle || ADD || ODD ? 6 : 8;
 
     // strip constants
