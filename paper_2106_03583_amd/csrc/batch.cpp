@@ -300,7 +300,7 @@ int solve_batch(mbp_plan* const* plans, const double* const* rhs, double* const*
                     stages.push_back(group_pair32(gb, cs, l, true, k, inner));
                     stages.push_back(group_march32(gb, cs, l, false, k == 0));
                 }
-                for (int form = 0; form < 3; ++form) stages.push_back(group_coarse32(gb, cs, form));
+                for (int form = 0; form < 3; ++form) stages.push_back(group_coarse32(gb, cs, form, k, inner));
                 stages.push_back(group_lds32(gb, cs));
                 for (int l = maxL - 1; l >= 0; --l) {
                     stages.push_back(group_pair32(gb, cs, l, false, k, inner));

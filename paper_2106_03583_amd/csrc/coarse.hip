@@ -1082,8 +1082,10 @@ void launch_coarse_full(const mbp_plan* P, double* p, const double* f, const int
 }
 
 // The LDS stage of the problems of one form (0: two cells of a colour per thread,
-// 1: four, 2: odd rings), one launch: threads and LDS of the largest.
-GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form) {
+// 1: four, 2: odd rings), one launch: threads and LDS of the largest.  A hierarchy that
+// fits LDS whole runs all of its inner cycles in the launch of the first (k = 0), as
+// alone; every launch starts from zero.
+GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form, int k, int inner) {
     std::vector<CArgs<float>> jobs;
     std::vector<int> gx, gy;
     GStage st;
@@ -1093,7 +1095,9 @@ GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form)
         const mbp_plan* P = c->P;
         if (!P->coarse.ok || (P->coarse.odd ? 2 : P->coarse.per == 2 ? 0 : 1) != form) continue;
         const int L = P->lds_level32;
+        if (L == 0 && k > 0) continue;
         CArgs<float> a = coarse_args<float>(P, L, P->p32[L], P->f32[L], P->d_act, P->d_nact);
+        if (L == 0) a.ncyc = inner;
         jobs.push_back(a);
         gx.push_back(c->nitems);
         gy.push_back(1);

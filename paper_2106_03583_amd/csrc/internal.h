@@ -516,7 +516,7 @@ void group_launch_march(const GStage& st, const unsigned char* dev, hipStream_t 
 // The pair-march levels of inner cycle k of `inner`: on the way down (down) or up.
 GStage group_pair32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int level, bool down, int k, int inner);
 void group_launch_pair(const GStage& st, const unsigned char* dev, hipStream_t s);
-GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form);
+GStage group_coarse32(GroupBlob& gb, const std::vector<SolveCtx*>& cs, int form, int k, int inner);
 void group_launch_coarse(const GStage& st, const unsigned char* dev, hipStream_t s);
 
 }  // namespace mbp
