@@ -4,6 +4,8 @@
 //     many modes each workgroup runs in turn), and
 //   * per fused level, the pre-smoothing form: LDS strip tiles or the
 //     register march.
+// Levels of the pair march and those in LDS have one schedule: a plan without strip
+// levels is timed once.
 // The schedule only changes how the same arithmetic is distributed; every
 // candidate runs the same red-black sweeps.
 #include <algorithm>
@@ -64,8 +66,13 @@ int plan_autotune(mbp_plan* P, const double* rhs, hipStream_t s, mbp_tuning* out
     P->wg_target = 256 * 3;
     const float t_default = time_cycles(c, s, a, b, reps);
     float best = t_default;
+    const int Lg = c.mixed ? P->lds_level32 : P->lds_level;
+    auto strips = [&](int l) { return l < Lg && P->march_ok[l] && !P->pair_ok[l] && P->rtile_cnt[l] > 0; };
+    bool any = false;
+    for (int l = 0; l < P->nlev; ++l) any = any || strips(l);
     // workgroups per launch (sets the modes each workgroup runs in turn)
     for (int target : {256 * 1, 256 * 12}) {
+        if (!any) break;
         const int keep = P->wg_target;
         P->wg_target = target;
         const float t = time_cycles(c, s, a, b, reps);
@@ -74,7 +81,7 @@ int plan_autotune(mbp_plan* P, const double* rhs, hipStream_t s, mbp_tuning* out
     }
     // pre-smoothing form per fused level (finest first)
     for (int l = 0; l < P->nlev; ++l) {
-        if (!P->march_ok[l] || P->rtile_cnt[l] == 0) continue;
+        if (!strips(l)) continue;
         P->use_rmarch[l] = 1;
         const float t = time_cycles(c, s, a, b, reps);
         if (t < 0.98f * best) best = t;
