@@ -473,7 +473,6 @@ GStage group_build(GroupBlob& gb, int kind, const std::vector<Job>& jobs, const 
     st.job_off = gb.add(jobs.data(), jobs.size() * sizeof(Job));
     return st;
 }
-// Job of this workgroup in a grouped launch, and its (bx, by) inside the job.
 // A record every lane of the wave read from the same address: say so, so
 // that what is computed from it stays in scalar registers.
 template <typename R>
@@ -487,6 +486,7 @@ __device__ __forceinline__ R wave_uniform(const R& v) {
     return out;
 }
 
+// Job of this workgroup in a grouped launch, and its (bx, by) inside the job.
 __device__ __forceinline__ int group_locate(const GEnt* __restrict__ e, int n, int& bx, int& by) {
     const int g = blockIdx.x;
     int lo = 0, hi = n - 1;
@@ -501,7 +501,7 @@ __device__ __forceinline__ int group_locate(const GEnt* __restrict__ e, int n, i
     return e[lo].job;
 }
 // A problem joins the grouped form when every level above its LDS-resident
-// ones runs the strip kernels (mixed precision, one pre- and one post-sweep).
+// ones runs the pair march or the strip kernels (mixed precision, one pre- and one post-sweep).
 bool group_ok(const SolveCtx& c);
 // Stage tables for the problems `cs` (phase 1, host only) ...
 GStage group_res32(GroupBlob& gb, const std::vector<SolveCtx*>& cs);

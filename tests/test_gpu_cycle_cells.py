@@ -3,7 +3,8 @@ written out in numpy (vcycle.py): the march's forms (pre-smoothing and restricti
 zero and from an iterate, correction and post-smoothing, whole cycles, the FP32 sweep that
 adds to the FP64 iterate) on even and odd planes, FP64 and FP32, alone and in grouped
 launches, strips of every width and height, and the LDS-resident levels, odd rings among
-them.  A wrong transfer that only slows convergence cannot pass.
+them.  A wrong transfer that only slows convergence cannot pass, nor a cell that was left
+from another solve on the same plan.
 
 Tolerance: eight roundings a residual; their errors are independent from cell to cell, so
 the smooth part that a cycle amplifies (by the square of the cells across) is smaller by
@@ -54,11 +55,13 @@ def test_cells_of_fp64_cycles(prob):
     import paper_2106_03583_amd as m
     print(f"cells fp64 {prob.name}", flush=True)
     ref = _ref(prob)
-    f, start = W.rhs(prob, 81), 1e-3 * W.rhs(prob, 82)
-    fd, sd = torch.from_numpy(f).cuda(), torch.from_numpy(start).cuda()
+    f, start, other = W.rhs(prob, 81), 1e-3 * W.rhs(prob, 82), 1e3 * W.rhs(prob, 86)
+    fd, sd, od = (torch.from_numpy(a).cuda() for a in (f, start, other))
     for cycles in (1, 2, 3):
         plan = m.Plan(prob, max_cycles=cycles)
         for flags in (0, m.RETIRE, m.WARM_START):
+            p = torch.zeros_like(fd)  # (leaves other values in every buffer of the plan)
+            plan.solve(od, p, rtol=1e-15, flags=m.PROJECT_RHS | m.RETIRE, raise_on_error=False)
             p = sd.clone()
             plan.solve(fd, p, rtol=1e-15, flags=m.PROJECT_RHS | flags, raise_on_error=False)
             want = ref.solve(f, cycles, start=start if flags & m.WARM_START else None)
@@ -73,11 +76,12 @@ def test_cells_of_mixed_cycles(prob, inner):
     import paper_2106_03583_amd as m
     print(f"cells mixed {prob.name} {inner}", flush=True)
     f = W.rhs(prob, 83)
-    fd = torch.from_numpy(f).cuda()
+    fd, od = torch.from_numpy(f).cuda(), torch.from_numpy(1e3 * W.rhs(prob, 86)).cuda()
     want = _ref(prob).solve(f, 1, inner)
     plan = m.Plan(prob, precision="mixed", max_cycles=1, inner=inner)
     for flags in (0, m.RETIRE):
         p = torch.zeros_like(fd)
+        plan.solve(od, p, rtol=1e-15, flags=m.PROJECT_RHS, raise_on_error=False)
         plan.solve(fd, p, rtol=1e-15, flags=m.PROJECT_RHS | flags, raise_on_error=False)
         _close(prob, p.cpu().numpy(), want, 24, inner)
     plan.close()
@@ -93,6 +97,7 @@ def test_cells_of_grouped_cycles(name, probs, inner):
     fd = [torch.from_numpy(a).cuda() for a in f]
     plans = [m.Plan(pr, precision="mixed", max_cycles=1, inner=inner) for pr in probs]
     x = [torch.zeros_like(a) for a in fd]
+    m.solve_batch(plans, [1e3 * a.flip(0) for a in fd], x, rtol=1e-15, flags=m.PROJECT_RHS, raise_on_error=False)
     m.solve_batch(plans, fd, x, rtol=1e-15, flags=m.PROJECT_RHS, raise_on_error=False)
     for pr, a, b in zip(probs, f, x):
         _close(pr, b.cpu().numpy(), _ref(pr).solve(a, 1, inner), 24, inner)
