@@ -215,7 +215,6 @@ struct mbp_plan {
     int* d_flag = nullptr;        // 4 ints: [0] rhs refused (1 not finite, 2 incompatible), [1] tests,
                                   // [2] cycles used up, [3] partial sums a mode
     double* d_scal = nullptr;     // 8 doubles of scratch scalars
-    void* graph_exec = nullptr;   // cached batched replay (hipGraphExec_t)
     void* host_pinned = nullptr;  // pinned buffer that kernels report to
     void* pinned_dev = nullptr;   //   its device address
     // kernel timing (mbp_profile_*): event pairs around finest-level sweeps

@@ -493,8 +493,8 @@ int ctx_info(SolveCtx& c, hipStream_t s, mbp_solve_info* info) {
 // Algorithm 1 for one problem: forward transform, per-mode multigrid to the
 // tolerance, inverse transform.  Host-driven, but the host reads the state of a test
 // only after the next V-cycle and test are queued, and the checks of the rhs with
-// the first of them, so the device never waits for the host (the batched form
-// replays captured cycles instead).  Once every mode has retired or, in lockstep, passed,
+// the first of them, so the device never waits for the host (batches off the grouped
+// form work the same way).  Once every mode has retired or, in lockstep, passed,
 // the queued work runs on an empty active list (no-op launches).  State reaches the
 // host through memory that kernels write: with a copy kernel per item and a wait per
 // cycle, a lockstep solve of 203 x 157 x 90 took 2.53 ms (now 2.30) and one of 32^3
