@@ -773,10 +773,15 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
     const Geometry& g = P->g;
     const int nl = P->nlev - L, nb = g.nb;
     std::vector<CLev> lev(nl);
-    std::vector<std::vector<CRec>> recs(nl);
-    std::vector<std::vector<double>> tabs(nl);
-    std::vector<int> patches(nl);
-    std::vector<std::vector<unsigned short>> place(nl);  // plane offset -> place in the LDS iterate
+    std::vector<int> patches(nl), first(nl + 1, 0);  // first record of each level
+    for (int k = 0; k < nl; ++k) first[k + 1] = first[k] + int(P->levels[L + k].plane);
+    std::vector<unsigned short> place(first[nl]);  // plane offset -> place in the LDS iterate
+    // records go straight to the int pool, tables to the double pool
+    while (P->hint.size() & 3) P->hint.push_back(0);
+    const int words = int(sizeof(CRec) / sizeof(int)), r0 = int(P->hint.size());
+    P->hint.resize(P->hint.size() + size_t(first[nl]) * words, 0);
+    CRec* recs = reinterpret_cast<CRec*>(P->hint.data() + r0);
+    ci.tab0 = int(P->hdbl.size());
     std::vector<int> pgrid;  // patches of the level above: first of each block, row pitch
     int elems = 0;
     for (int k = 0; k < nl; ++k) {
@@ -797,15 +802,45 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
             pg[2 * b + 1] = (F.nx[b] + 1) / 2;
             np += pg[2 * b + 1] * ((F.ny[b] + 1) / 2);
         }
-        tabs[k].assign(size_t(ne) * kTab, 0.0);
+        const size_t t0 = P->hdbl.size();
+        P->hdbl.resize(t0 + size_t(ne) * kTab, 0.0);
+        cl.ltab = ci.ntab;
+        ci.ntab += ne;
         const bool transfer = k + 1 < nl;
-        std::vector<CRec> byc[4];
-        byc[0].reserve(transfer ? cl.ncell / 2 + nb : cl.ncell);
-        if (transfer) byc[1].reserve(cl.ncell / 2 + nb);
+        // a ring of odd length (of one block or several) has one face whose two
+        // sides would share colours: its lower side takes the extra ones
+        auto ends = [&](const DBlock& d, bool& ox, bool& oy) {
+            const int kx = d.nbr[XP], ky = d.nbr[YP];
+            ox = kx >= 0 && ((d.par + d.nx + P->hblk[F.blk_off + kx].par) & 1);
+            oy = ky >= 0 && ((d.par + d.ny + P->hblk[F.blk_off + ky].par) & 1);
+        };
+        // cells per colour (the coarsest level's records are read in plane order)
+        int n[4] = {0, 0, 0, 0};
+        if (!transfer) n[0] = cl.ncell;
+        for (int b = 0; b < nb && transfer; ++b) {
+            const DBlock& d = P->hblk[F.blk_off + b];
+            bool ox, oy;
+            ends(d, ox, oy);
+            const int mx = d.nx - (ox ? 1 : 0), my = d.ny - (oy ? 1 : 0);
+            n[d.par] += (mx * my + 1) / 2;
+            n[d.par ^ 1] += mx * my / 2;
+            for (int j = 0; j < my && ox; ++j) ++n[2 + ((mx + j + d.par) & 1)];
+            for (int i = 0; i < d.nx && oy; ++i) ++n[2 + ((i + my + d.par) & 1)];
+        }
+        cl.n0 = n[0];
+        cl.n1 = n[1];
+        cl.n2 = n[2];
+        cl.n3 = n[3];
+        CRec* rec = recs + first[k];
+        unsigned short* pl = place.data() + first[k];
+        int next[4] = {0, n[0], n[0] + n[1], n[0] + n[1] + n[2]};  // places by colour
         for (int b = 0; b < nb; ++b) {
             const DBlock& d = P->hblk[F.blk_off + b];
+            const DBlock* e = transfer ? &P->hblk[P->levels[L + k + 1].blk_off + b] : nullptr;
+            bool ox, oy;
+            ends(d, ox, oy);
             auto entry = [&](int e, int c, int n, int i, int rw, int pw) {
-                double* t = &tabs[k][size_t(e + i) * kTab];
+                double* t = &P->hdbl[t0 + size_t(e + i) * kTab];
                 t[0] = P->hdbl[c + i];
                 t[1] = P->hdbl[c + n + i];
                 t[2] = P->hdbl[c + 2 * n + i];
@@ -818,8 +853,12 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
             for (int j = 0; j < d.ny; ++j) entry(yb[b], d.cy, d.ny, j, d.rwy, d.pwy);
             for (int j = 0; j < d.ny; ++j)
                 for (int i = 0; i < d.nx; ++i) {
-                    CRec r{};
                     const int self = d.off + j * d.nx + i;
+                    int c = (i + j + d.par) & 1;
+                    if ((ox && i == d.nx - 1) || (oy && j == d.ny - 1)) c += 2;
+                    const int to = next[transfer ? c : 0]++;
+                    pl[self] = (unsigned short)to;
+                    CRec r{};
                     r.self = (unsigned short)self;
                     const bool inner = i > 0 && i < d.nx - 1 && j > 0 && j < d.ny - 1;
                     if (inner) {
@@ -853,17 +892,16 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
                     const int patch = pg[2 * b] + (j / 2) * pg[2 * b + 1] + i / 2;
                     r.s = (unsigned short)(cl.ns == 2 ? 2 * patch + (j & 1) : 4 * patch + 2 * (j & 1) + (i & 1));
                     if (transfer) {
-                        const Level& C = P->levels[L + k + 1];
                         const int I = P->hint[d.pcx + i], J = P->hint[d.pcy + j];
-                        const DBlock& e = P->hblk[C.blk_off + b];
-                        if (I >= 0 && I + 1 < e.nx && J >= 0 && J + 1 < e.ny) {
-                            const int at = e.off + J * e.nx + I;
+                        if (I >= 0 && I + 1 < e->nx && J >= 0 && J + 1 < e->ny) {
+                            const int at = e->off + J * e->nx + I;
                             r.c[0] = (unsigned short)at;
                             r.c[1] = (unsigned short)(at + 1);
-                            r.c[2] = (unsigned short)(at + e.nx);
-                            r.c[3] = (unsigned short)(at + e.nx + 1);
+                            r.c[2] = (unsigned short)(at + e->nx);
+                            r.c[3] = (unsigned short)(at + e->nx + 1);
                         } else {
-                            for (int c = 0; c < 4; ++c) r.c[c] = coarse_ref(P, C, b, I + (c & 1), J + (c >> 1));
+                            for (int c = 0; c < 4; ++c)
+                                r.c[c] = coarse_ref(P, P->levels[L + k + 1], b, I + (c & 1), J + (c >> 1));
                         }
                     }
                     if (k > 0) {
@@ -872,35 +910,22 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
                         r.gp = (unsigned short)(pgrid[2 * b + 1] | (i == d.nx - 1 && U.nx[b] > 2 * d.nx ? 0x4000 : 0) |
                                                 (j == d.ny - 1 && U.ny[b] > 2 * d.ny ? 0x8000 : 0));
                     }
-                    int c = (i + j + d.par) & 1;
-                    // a ring of odd length (of one block or several) has one face whose two
-                    // sides would share colours: its lower side takes the extra ones
-                    const int kx = d.nbr[XP], ky = d.nbr[YP];
-                    const bool cx = i == d.nx - 1 && kx >= 0 && ((d.par + d.nx + P->hblk[F.blk_off + kx].par) & 1);
-                    const bool cy = j == d.ny - 1 && ky >= 0 && ((d.par + d.ny + P->hblk[F.blk_off + ky].par) & 1);
-                    if (cx || cy) c += 2;
-                    // the coarsest level's records are read in plane order
-                    byc[transfer ? c : 0].push_back(r);
+                    rec[to] = r;
                 }
         }
-        cl.n0 = int(byc[0].size());
-        cl.n1 = int(byc[1].size());
-        cl.n2 = int(byc[2].size());
-        cl.n3 = int(byc[3].size());
-        recs[k].reserve(cl.ncell);
-        for (const auto& v : byc) recs[k].insert(recs[k].end(), v.begin(), v.end());
-        place[k].resize(cl.ncell);
-        for (int i = 0; i < cl.ncell; ++i) place[k][recs[k][i].self] = (unsigned short)i;
         pgrid = pg;
         patches[k] = np;
     }
     // neighbours and coarse values by place
-    for (int k = 0; k < nl; ++k)
-        for (CRec& r : recs[k]) {
-            for (unsigned short& o : r.n) o = place[k][o];
-            if (k + 1 < nl)
-                for (unsigned short& o : r.c) o = (unsigned short)((o & 0x8000) | place[k + 1][o & 0x7fff]);
+    for (int k = 0; k < nl; ++k) {
+        const unsigned short* pl = place.data() + first[k];
+        const unsigned short* below = k + 1 < nl ? place.data() + first[k + 1] : nullptr;
+        for (int i = first[k]; i < first[k + 1]; ++i) {
+            for (unsigned short& o : recs[i].n) o = pl[o];
+            if (below)
+                for (unsigned short& o : recs[i].c) o = (unsigned short)((o & 0x8000) | below[o & 0x7fff]);
         }
+    }
     // threads: two cells of each colour each, or as many as kCoarseThreads threads need
     const int n = std::max(lev[0].n0, lev[0].n1);
     ci.ncell = n;
@@ -913,25 +938,15 @@ void coarse_build(mbp_plan* P, int L, int64_t elem) {
         elems += lev[k].ns * patches[k];
     }
     ci.nslot = elems - ci.oS;
-    // pools: tables of every level in order, records of every level in order
-    ci.tab0 = int(P->hdbl.size());
-    for (int k = 0; k < nl; ++k) {
-        lev[k].ltab = ci.ntab;
-        ci.ntab += int(tabs[k].size()) / kTab;
-        P->hdbl.insert(P->hdbl.end(), tabs[k].begin(), tabs[k].end());
-    }
-    while (P->hint.size() & 3) P->hint.push_back(0);
     // records in LDS from the second level on where that costs no workgroup of
     // the CU (its 8 waves of this kernel), else from the third
     const int64_t share = P->lds_limit / std::max(1, kCoarseThreads / ci.nthr);
     const int first_rec = coarse_lds_need(P, L, elem) + int64_t(lev[1].ncell) * 32 <= share ? 1 : 2;
     for (int k = 0; k < nl; ++k) {
-        if (k == first_rec) ci.rec0 = int(P->hint.size());
-        lev[k].rec = int(P->hint.size());
+        lev[k].rec = r0 + first[k] * words;
+        if (k == first_rec) ci.rec0 = lev[k].rec;
         lev[k].lrec = k >= first_rec ? ci.nrec : -1;
-        if (k >= first_rec) ci.nrec += int(recs[k].size());
-        const int* s = reinterpret_cast<const int*>(recs[k].data());
-        P->hint.insert(P->hint.end(), s, s + recs[k].size() * (sizeof(CRec) / sizeof(int)));
+        if (k >= first_rec) ci.nrec += lev[k].ncell;
     }
     ci.lev = int(P->hint.size());
     for (const CLev& c : lev) {

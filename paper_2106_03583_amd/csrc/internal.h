@@ -344,6 +344,8 @@ void march_post(const mbp_plan* P, int l, const T* pold, T* pnew, const T* f, co
 bool pair_level_ok(const mbp_plan* P, int l);
 void pair_build(mbp_plan* P, int l, int halo, std::vector<unsigned char>& bytes, std::vector<PairSet>& sets);
 int pair_max_strips(const mbp_plan* P, int l);
+size_t pair_block_doubles(int nx, int ny);  // what the tables of one block take of the pools at the most
+size_t pair_block_ints(int nx);
 template <typename T>
 void pair_pre(const mbp_plan* P, int l, const T* p, const T* f, T* fc, const int* act, const int* nact, int nitems,
               hipStream_t s);

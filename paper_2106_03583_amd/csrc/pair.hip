@@ -613,6 +613,10 @@ bool pair_level_ok(const mbp_plan* P, int l) {
     return true;
 }
 
+static size_t most_strips(int nx) { return size_t(nx + 1 + 111) / 112; }  // (the narrower strips)
+size_t pair_block_doubles(int nx, int ny) { return 3 * size_t(ny + 2 * kPad) * kYw + most_strips(nx) * kXTab; }
+size_t pair_block_ints(int nx) { return most_strips(nx) * (kOTab + 3); }
+
 // Tables and strips of level l; appends to the pools and the strip list.
 // halo: lanes of halo on each side (4 for the cycle form, which runs on the
 // finest level; 2 otherwise).

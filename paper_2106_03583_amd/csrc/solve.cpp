@@ -134,6 +134,21 @@ static void plan_march_tables(mbp_plan* P) {
     pbytes.clear();
     const bool mixed = P->opt.precision == MBP_MIXED;
     const int Lg = mixed ? P->lds_level32 : P->lds_level;
+    {
+        // room for all that the two append to the pools: growing them record by record
+        // copied and faulted in the pools anew, half of the time these tables took
+        size_t ints = P->hint.size(), dbls = P->hdbl.size() + 2 * size_t(P->coarse_n) * P->coarse_n;
+        for (int l = 0; l < P->nlev; ++l) {
+            const Level& F = P->levels[l];
+            if (l >= Lg) ints += size_t(F.plane) * 8 + 16;
+            for (int b = 0; b < F.nb; ++b) {
+                dbls += l >= Lg ? 6 * size_t(F.nx[b] + F.ny[b]) : pair_block_doubles(F.nx[b], F.ny[b]);
+                if (l < Lg) ints += pair_block_ints(F.nx[b]);
+            }
+        }
+        P->hint.reserve(ints);
+        P->hdbl.reserve(dbls);
+    }
     coarse_build(P, Lg, mixed ? 4 : 8);
     for (int l = 0; l < Lg; ++l) {
         if (!pair_level_ok(P, l)) continue;
