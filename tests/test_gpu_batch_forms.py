@@ -1,8 +1,8 @@
 """The two forms of a batched solve and sets that need both: FP64 problems alone, FP64
 beside mixed ones, mixed problems off the group (an odd ring on a global level, another
 inner cycle count, two sweeps), one problem alone, problems that end at once or are
-refused, and whole hierarchies in LDS; with and without tuning, and again on the same
-plans.  Bounds: rtol on the residual, 10 rtol on the error, against the oracle."""
+refused, and whole hierarchies in LDS; with and without tuning, again on the same plans,
+and from a warm start.  Bounds: rtol on the residual, 10 rtol on the error, against the oracle."""
 import numpy as np
 import pytest
 
@@ -25,6 +25,7 @@ SETS = {
     "off_group": [(BIG[0], "mixed", {}), (ODD, "mixed", {}), (BIG[1], "mixed", {"inner": 2}),
                   (BIG[3], "mixed", {"nu1": 2, "nu2": 2}), (BIG[2], "mixed", {})],
     "lds_only": [(p, "fp64", {}) for p in LDS],
+    "grouped": [(p, "mixed", {}) for p in BIG + LDS],
 }
 
 
@@ -35,18 +36,21 @@ def test_batch_forms(name):
     print(f"batch forms {name}", flush=True)
     probs = [p for p, _, _ in SETS[name]]
     plans = [m.Plan(p, precision=prec, **kw) for p, prec, kw in SETS[name]]
-    for n, flags in enumerate((0, m.AUTOTUNE, 0)):
+    for n, flags in enumerate((0, m.AUTOTUNE, 0, m.WARM_START)):
         f = [W.rhs(p, 70 + 10 * n + i) for i, p in enumerate(probs)]
         fd = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in f]
-        x = [torch.full_like(a, float("nan")) for a in fd]
+        if flags & m.WARM_START:
+            x = [torch.from_numpy(0.5 * oracle.solve(p, a)).cuda() for p, a in zip(probs, f)]
+        else:
+            x = [torch.full_like(a, float("nan")) for a in fd]
         infos = m.solve_batch(plans, fd, x, rtol=1e-10, flags=m.PROJECT_RHS | flags)
         for p, a, b, info in zip(probs, f, x, infos):
             assert info.status == 0 and info.cycles == max(info.cycles_per_mode)
             fp = oracle.project_compatible(p, a) if oracle.is_singular(p) else a
             assert oracle.rel_residual(p, b.cpu().numpy(), fp) <= 1e-10
             assert oracle.rel_error(b.cpu().numpy(), oracle.solve(p, a)) <= 1e-9
-    if name not in ("lds_only",):
-        assert m.batch_schedule(plans)[0] > 0  # never the grouped form alone
+    if name != "lds_only":  # streams: 0 where every problem was grouped
+        assert (m.batch_schedule(plans)[0] == 0) == (name == "grouped")
     for pl in plans:
         pl.close()
 
