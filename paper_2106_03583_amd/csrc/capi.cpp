@@ -53,7 +53,17 @@ int mbp_plan_check(const mbp_block_desc* blocks, int nblocks, const mbp_synth_de
         out->coarse_cells = P->coarse_n;
         out->singular = P->g.singular ? 1 : 0;
         out->nblocks = P->g.nb;
-        out->workspace_bytes = int64_t(plan_device_bytes(P));
+        // no device is asked for here; the plan on one has more LDS to use, which may save
+        // buffers or take larger tables: the larger of the two covers it
+        mbp_plan* D = new (std::nothrow) mbp_plan();
+        const int sd = D ? build_plan_host_limits(blocks, nblocks, z, opt, kDeviceLds, D, &err) : MBP_ERR_NOMEM;
+        if (sd != MBP_OK) {
+            delete D;
+            delete P;
+            return sd;
+        }
+        out->workspace_bytes = int64_t(std::max(plan_device_bytes(P), plan_device_bytes(D)));
+        delete D;
         for (int b = 0; b < P->g.nb && b < 64; ++b)
             for (int f = 0; f < 4; ++f) out->nbr[b][f] = P->g.nbr[b][f];
     }

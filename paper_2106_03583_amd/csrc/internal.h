@@ -118,6 +118,8 @@ struct CoarseInfo {
 };
 constexpr int kCoarseInLds = 32;  // coarsest planes up to this many cells have their matrices in LDS
 
+constexpr int64_t kDeviceLds = 160 * 1024;  // LDS bytes of a gfx950 workgroup
+
 constexpr int kWidePer = 16;  // values a thread of the wide transform holds
 
 struct FFTPlan {
